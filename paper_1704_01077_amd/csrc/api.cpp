@@ -64,6 +64,9 @@ struct WsItem {
     size_t bytes;
     bool zero;
 };
+// levels the ring engine's tables hold for a graph of n vertices
+static size_t ring_lcap(int32_t n) { return (size_t)std::min<int64_t>((int64_t)n + 4, TKC_RING_LCAP); }
+
 // layout of every buffer a query may use
 static size_t ws_items(Workspace& ws, const WsShape& sh, std::vector<WsItem>& items) {
     size_t n = (size_t)sh.n, nw = (size_t)sh.nw, W = (size_t)sh.W;
@@ -109,6 +112,12 @@ static size_t ws_items(Workspace& ws, const WsShape& sh, std::vector<WsItem>& it
         {(void**)&ws.s_vis, 4 * words * (size_t)sh.swarm_blocks, true},
         {(void**)&ws.s_queue, 4 * (size_t)sh.qcap * (size_t)sh.swarm_blocks, false},
         {(void**)&ws.s_deferred, 4 * n, false},
+        // ring engine
+        {(void**)&ws.r_queue, sh.ring ? 4 * (size_t)RING_QSTRIDE(n) * (size_t)sh.ring : 8, false},
+        {(void**)&ws.r_off, sh.ring ? 4 * ring_lcap(sh.n) * (size_t)sh.ring : 8, false},
+        {(void**)&ws.r_lev, sh.ring ? 8 * ring_lcap(sh.n) * (size_t)sh.ring : 8, false},
+        {(void**)&ws.r_comb, sh.ring ? 8 * n : 8, false}, {(void**)&ws.r_dec, sh.ring ? 4 * words : 8, false},
+        {(void**)&ws.r_ell, sh.ring ? 16 * n : 8, false},
     };
     size_t total = 0;
     for (auto& it : items) total += align_up(it.bytes);
@@ -591,6 +600,11 @@ WsShape tkc_shape_for(const EngineTuning& t, tkc_graph* g, int32_t k, bool lb) {
     return sh;
 }
 
+WsShape tkc_shape_ring(WsShape sh, tkc_graph* g) {
+    if (sh.lb) sh.ring = tkc_ring_blocks(g->view());
+    return sh;
+}
+
 // step 1: reachability into ws.alpha / ws.omega (/ ws.scc)
 int tkc_step_reach(tkc_ctx* c, tkc_graph* g, Workspace& ws) {
     hipStream_t s = c->stream;
@@ -951,10 +965,16 @@ int tkc_run_query(tkc_ctx* c, tkc_graph* g, int32_t k, int32_t variant, int32_t 
     const int lbl = tkc_lb_level(variant);
     const bool lb = lbl != 0;
     const bool nb = tkc_is_nb(variant);
+    int32_t ring = 0;   // workgroups of the ring engine, 0: not used
     {
         WsShape sh = tkc_shape_for(c->tune, g, k, lb);
         sh.ties = ties;
-        rc = tkc_ws_reserve(c, ws, sh);
+        // complete searches of a low-degree graph: the ring engine, unless its
+        // buffers do not fit
+        const WsShape rs = lb && !harm && mode != TKC_PLAIN && c->ring_ok ? tkc_shape_ring(sh, g) : sh;
+        rc = tkc_ws_reserve(c, ws, rs);
+        ring = rc == TKC_OK ? rs.ring : 0;
+        if (rc == TKC_ENOMEM && rs.ring) rc = tkc_ws_reserve(c, ws, sh);
     }
     if (rc) return rc;
     int32_t rounds = 0;
@@ -1007,11 +1027,50 @@ int tkc_run_query(tkc_ctx* c, tkc_graph* g, int32_t k, int32_t variant, int32_t 
         rb_ready = true;
     } else if (mode == TKC_BATCHED) {
         trace_reset(c);
-        // one launch, or slices of slice_batches batches (the cursor, stop
-        // flag, top k and bounds live in device memory between them)
+        // launches of slice_batches batches each when that is set (the
+        // cursor, stop flag, top k and bounds live in device memory between
+        // them), else one launch
         const int32_t slice = c->tune.slice_batches > 0 ? c->tune.slice_batches : 0;
         int32_t pos = 0;
-        for (;;) {
+        bool more = true;
+        if (ring) {
+            int32_t* small = (int32_t*)ws.small;
+            const int32_t* pin = (const int32_t*)c->pinned;
+            RingWork rw{};
+            rw.queue = ws.r_queue;
+            rw.levoff = ws.r_off;
+            rw.levtab = ws.r_lev;
+            rw.comb = ws.r_comb;
+            rw.dec = ws.r_dec;
+            rw.ell = ws.r_ell;
+            rw.lcap = (int32_t)ring_lcap(n);
+            rw.cursor = small + 4;
+            rw.stop = small + 5;
+            rw.started = small + 6;
+            rw.nblocks = ring;
+            // a slice runs two searches per workgroup
+            const int32_t limit = slice ? 2 * ring : 0;
+            HIPCHK(hipMemsetAsync(small + 4, 0, 2 * sizeof(int32_t), s));
+            if (tkc_launch_ring_begin(dg, rcv, bv, rw, s)) return tkc_fail(TKC_EDEVICE, "bound kernel failed");
+            do {
+                HIPCHK(hipMemsetAsync(small + 6, 0, sizeof(int32_t), s));
+                EngineTimer tm(c, &ms_eng[2], &nl_eng[2]);
+                if (tkc_launch_ring(dg, rcv, ov, bv, tk, rw, st_swarm, lbl, limit, s))
+                    return tkc_fail(TKC_EDEVICE, "ring engine launch failed: %s", hipGetErrorString(hipGetLastError()));
+                if ((rc = tm.done([&] {
+                         HIPCHK(hipMemcpyAsync(c->pinned, small + 4, 2 * sizeof(int32_t), hipMemcpyDeviceToHost, s));
+                         return readback();
+                     })))
+                    return rc;
+                pos = std::min(pin[0], n);
+            } while (limit && !pin[1] && pos < n);
+            rb_ready = true;
+            // closed by a search deeper than its tables: the batched engine
+            // takes the rest
+            more = pin[1] == 2 && pos < n;
+            if (more && tkc_launch_ring_end(dg, rcv, bv, rw, s)) return tkc_fail(TKC_EDEVICE, "bound kernel failed");
+        }
+        while (more) {
             {
                 EngineTimer tm(c, &ms_eng[1], &nl_eng[1]);
                 int e = tkc_launch_batch(dg, rcv, ov, bv, tk, tkc_batch_view(ws), st_batch, nullptr, 0, pos, slice, lbl,
@@ -1026,6 +1085,7 @@ int tkc_run_query(tkc_ctx* c, tkc_graph* g, int32_t k, int32_t variant, int32_t 
                 }
             }
             if (!slice) break;
+            rb_ready = false;
             int64_t hs[ST_COUNT];
             memcpy(hs, pin_at<int64_t>(ws, st_batch), sizeof(hs));
             if (hs[ST_STOP] || hs[ST_CURSOR] >= n) break;

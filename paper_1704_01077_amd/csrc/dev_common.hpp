@@ -355,6 +355,29 @@ TKC_DEV XVal read_x(TopkState* st, const XRec* ring) {
     }
 }
 
+// read_x without fences, for engines whose workgroups poll x while others
+// search: an agent-scope acquire drops the whole XCD's cached lines, and one
+// search's poll would empty the L2 that 31 others read their graph from.
+// The record's address depends on the first load of seq, and the second is
+// issued only after the record has arrived; all loads are coherent.
+TKC_DEV XVal read_x_poll(TopkState* st, const XRec* ring) {
+    XVal x;
+    for (;;) {
+        const int64_t s1 = ld_rlx(&st->seq);
+        if (s1 < 0) { x.num = 0; x.den = 0; x.id = 0x7fffffff; return x; }
+        const XRec* rc = ring + (s1 % TKC_XRING);
+        const int64_t S = ld_rlx(&rc->S), r = ld_rlx(&rc->r), id = ld_rlx(&rc->id);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        const int64_t s2 = ld_rlx(&st->seq);
+        if (s2 - s1 < TKC_XRING - 1) {
+            x.num = S;
+            x.den = r <= 1 ? 0 : sq64(r - 1);
+            x.id = (int32_t)id;
+            return x;
+        }
+    }
+}
+
 TKC_DEV void tie_keep(TopkState* st, int64_t S, int64_t r, int32_t id) {
     const int32_t t = ld_rlx(&st->tcnt);
     if (t < st->tcap) {
@@ -369,10 +392,9 @@ TKC_DEV void tie_keep(TopkState* st, int64_t S, int64_t r, int32_t id) {
 // all-ties mode every entry that leaves the top k, or is refused by it, is
 // kept for the final tie filter, and x carries id +inf, which turns every
 // lexicographic cut, skip and stop test into a strict "farness above x".
-TKC_DEV void topk_insert(TopkState* st, XRec* ring, int64_t* tS, int64_t* tR, int32_t* tI,
-                         int64_t S, int64_t r, int32_t id) {
-    while (__hip_atomic_exchange(&st->lock, 1, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) != 0)
-        __builtin_amdgcn_s_sleep(2);
+// (topk_insert_locked: the caller holds the lock)
+TKC_DEV void topk_insert_locked(TopkState* st, XRec* ring, int64_t* tS, int64_t* tR, int32_t* tI,
+                                int64_t S, int64_t r, int32_t id) {
     int32_t k = ld_rlx(&st->k);
     int32_t cnt = ld_rlx(&st->cnt);
     int64_t den = r <= 1 ? 0 : sq64(r - 1);
@@ -407,7 +429,18 @@ TKC_DEV void topk_insert(TopkState* st, XRec* ring, int64_t* tS, int64_t* tR, in
         }
     }
     fadd_rlx(&st->n_inserts, (int64_t)1);
-    __hip_atomic_store(&st->lock, 0, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+}
+TKC_DEV bool topk_try_lock(TopkState* st) {
+    return ld_rlx(&st->lock) == 0 &&
+           __hip_atomic_exchange(&st->lock, 1, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) == 0;
+}
+TKC_DEV void topk_unlock(TopkState* st) { __hip_atomic_store(&st->lock, 0, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT); }
+TKC_DEV void topk_insert(TopkState* st, XRec* ring, int64_t* tS, int64_t* tR, int32_t* tI,
+                         int64_t S, int64_t r, int32_t id) {
+    while (__hip_atomic_exchange(&st->lock, 1, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) != 0)
+        __builtin_amdgcn_s_sleep(2);
+    topk_insert_locked(st, ring, tS, tR, tI, S, r, id);
+    topk_unlock(st);
 }
 
 // ----------------------------------------------------- BFSCut bound (Sect. 6)

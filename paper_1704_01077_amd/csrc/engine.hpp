@@ -269,3 +269,35 @@ int tkc_launch_swarm(const DevGraph& g, DevReach rc, OrderView ov, BoundsView bv
                      SwarmWork w, int64_t* stats, int32_t start_pos, const EngineTuning& tune,
                      hipStream_t s);
 int tkc_swarm_max_blocks(int block);
+
+// k_ring.hip: complete searches with level-based updates, one per workgroup,
+// visited set in LDS (undirected graphs of low degree).
+struct RingWork {
+    int32_t* queue;      // nblocks * RING_QSTRIDE(n), 16-byte aligned
+    int32_t* levoff;     // nblocks * lcap: first queue position of each level
+    int64_t* levtab;     // nblocks * lcap: Lev table of the finished search
+    int64_t* comb;       // n: bound numerator + degree (what Lev values are compared with)
+    uint32_t* dec;       // n bits: bound already above the k-th farness, no more updates
+    int4* ell;           // n: every vertex's first arcs (k_ring_begin)
+    int32_t lcap;        // a deeper search closes the engine (stop bit 1)
+    int32_t* cursor;     // next position of the order
+    int32_t* stop;       // bit 0 stop rule fired, bit 1 engine closed
+    int32_t* started;    // searches of this launch (when limited)
+    int32_t nblocks;
+};
+#define TKC_RING_LCAP 8192
+#define RING_QSTRIDE(n) (((int64_t)(n) + 3) & ~(int64_t)3)
+// workgroups the engine runs with on g, 0 where it does not apply: directed
+// graphs (a bound's denominator may differ), vertices of more than HEAVY_DEG
+// arcs or more than 8 arcs a vertex on average (one workgroup per search
+// then loses to the batched engine's shared reads), bitmaps beyond LDS
+int tkc_ring_blocks(const DevGraph& g);
+// bounds into the engine's form before its first launch, and back after the
+// last when another engine goes on with them
+int tkc_launch_ring_begin(const DevGraph& g, const DevReach& rc, const BoundsView& bv, const RingWork& w,
+                          hipStream_t s);
+int tkc_launch_ring_end(const DevGraph& g, const DevReach& rc, const BoundsView& bv, const RingWork& w, hipStream_t s);
+// searches the order from *cursor on; limit > 0: about that many searches,
+// then the launch ends with the cursor where the next one resumes
+int tkc_launch_ring(const DevGraph& g, DevReach rc, OrderView ov, BoundsView bv, DevTopk tk, RingWork w,
+                    int64_t* stats, int lb_mode, int32_t limit, hipStream_t s);

@@ -14,9 +14,11 @@ struct WsShape {
     int32_t n = 0, W = 64, nw = 1, kcap = 1, lcap = 0, qcap = 0, swarm_blocks = 0, nchunks = 0;
     bool lb = false;
     bool ties = false;   // all-ties buffers
+    int32_t ring = 0;    // workgroups of the ring engine (0: not used)
     bool covers(const WsShape& o) const {
         return n >= o.n && nw >= o.nw && W >= o.W && kcap >= o.kcap && lcap >= o.lcap && qcap >= o.qcap &&
-               swarm_blocks >= o.swarm_blocks && nchunks >= o.nchunks && (lb || !o.lb) && (ties || !o.ties);
+               swarm_blocks >= o.swarm_blocks && nchunks >= o.nchunks && (lb || !o.lb) && (ties || !o.ties) &&
+               ring >= o.ring;
     }
 };
 
@@ -63,6 +65,11 @@ struct Workspace {
     // per-workgroup engine
     uint32_t* s_vis;
     int32_t *s_queue, *s_deferred;
+    // ring engine
+    int32_t *r_queue, *r_off;
+    int64_t *r_lev, *r_comb;
+    uint32_t* r_dec;
+    int4* r_ell;
     int64_t* trace = nullptr;   // optional level trace (separate allocation)
 };
 
@@ -78,6 +85,7 @@ struct tkc_ctx {
     hipEvent_t evq[4] = {nullptr, nullptr, nullptr, nullptr};
     // between two launches timed as one span (the seed batch and the swarm)
     hipEvent_t evm = nullptr;
+    bool ring_ok = true;      // a query may take the ring engine's buffers (servers: they fit the budget)
     void* pinned = nullptr;   // 4 KiB of pinned host memory for small readbacks
 };
 
@@ -187,6 +195,8 @@ bool tkc_prep_cached(tkc_ctx* c, tkc_graph* g, bool nb, int32_t* rounds);
 // build that cache from c's workspace after a query computed it
 int tkc_prep_store(tkc_ctx* c, tkc_graph* g, bool nb, int32_t rounds);
 WsShape tkc_shape_for(const EngineTuning& t, tkc_graph* g, int32_t k, bool lb);
+// the same with the ring engine's buffers where it applies to g (lb queries)
+WsShape tkc_shape_ring(WsShape sh, tkc_graph* g);
 // the knobs a TKC_MODE_AUTO query on g runs with, given the context's own
 EngineTuning tkc_effective_tuning(const EngineTuning& ctx_tune, tkc_graph* g);
 size_t tkc_ws_bytes(const WsShape& sh);

@@ -1,0 +1,571 @@
+// Ring engine: complete searches for the level-based updates (Sect. 7) on
+// graphs of low degree and high diameter (street networks), one search per
+// workgroup with its visited set in LDS.
+//
+// Such a search is a thin ring that moves out over hundreds of levels.  The
+// batched engine pays a grid barrier and several trips to memory for every
+// one of those levels; here a level is separated by one workgroup barrier
+// and its chain is queue -> row -> arc -> LDS bit, all inside one compute
+// unit.  A visited bitmap of n bits fits the 160 KB of LDS up to about 1.2 M
+// vertices, so every compute unit runs a search of its own and no arc costs
+// an atomic outside LDS.
+//
+// A finished search leaves its vertices in level order in its queue; the
+// workgroup then raises the bound of each of them (level by level, one wave
+// per level) with an atomic maximum, which is sound in any order because
+// every value written is a valid lower bound.  Numerators share one
+// denominator per component ((r - 1)^2, exact for undirected graphs), so one
+// 64-bit maximum updates a bound.
+//
+// What bounds it: on small graphs the latency of that chain (1.6 us a level on
+// a grid of 2 10^4 vertices), on large ones cache lines from beyond the L2
+// (82 of 110 ms on a grid of 10^6: 7 10^9 vertices expanded, about one 128 B
+// line each, the rate at which random lines reach the chip being 55 G/s).
+// Measured against the batched engine: 20.9 -> 2.0 ms and 690 -> 111 ms.
+#include "dev_common.hpp"
+#include "engine.hpp"
+
+// threads of a workgroup (512 measured the same, 256 lost 19 % on 2 10^4 vertices)
+#define RING_T 1024
+// results a workgroup may hold back while the top k's lock is taken
+#define RING_PEND 8
+// vertices of a level kept in LDS beside the queue, levels whose offsets are
+#define RING_FRONT 1024
+#define RING_LEVELS 512
+
+struct RingArgs {
+    DevGraph g;
+    DevReach rc;
+    OrderView ov;
+    BoundsView bv;
+    DevTopk tk;
+    RingWork w;
+    int64_t* stats;
+    int32_t words;
+    int32_t lb_mode;
+    int32_t limit;   // searches of this launch (0: no limit)
+};
+
+// The bound of a vertex is num / (r - 1)^2; Lev(l) - deg(w) is compared with
+// num, so the engine keeps comb = num + deg and compares Lev(l) alone: one
+// gather per vertex instead of two.  Deg bounds start as 0 / 1, and any other
+// denominator than (r - 1)^2 falls back to the bound 0.  ell holds every
+// vertex's first arcs in one 16-byte record (-1: none; more than four arcs:
+// three, then -2 - the position of the fourth), so a search touches one
+// cache line per vertex where row pointer and arcs took two (150 -> 82 ms of
+// search time on a grid of 10^6 vertices).
+__global__ void k_ring_begin(int32_t n, const int64_t* __restrict__ omega, const int32_t* __restrict__ deg,
+                             const int64_t* __restrict__ num, const int64_t* __restrict__ den, int64_t* comb,
+                             uint32_t* dec, const int32_t* __restrict__ rp, const int32_t* __restrict__ ci,
+                             int4* __restrict__ ell) {
+    const int32_t v = blockIdx.x * blockDim.x + threadIdx.x;
+    if (v >= n) return;
+    const int32_t b = rp[v], dv = rp[v + 1] - b;
+    int4 r{-1, -1, -1, -1};
+    if (dv > 0) r.x = ci[b];
+    if (dv > 1) r.y = ci[b + 1];
+    if (dv > 2) r.z = ci[b + 2];
+    if (dv == 4) r.w = ci[b + 3];
+    else if (dv > 4) r.w = -2 - (b + 3);
+    ell[v] = r;
+    const int64_t d = den[v], want = sq64(omega[v] - 1);
+    comb[v] = deg[v] + (d == want ? num[v] : 0);
+    if ((v & 31) == 0) dec[v >> 5] = 0;
+}
+__global__ void k_ring_end(int32_t n, const int64_t* __restrict__ omega, const int32_t* __restrict__ deg,
+                           const int64_t* __restrict__ comb, int64_t* num, int64_t* den) {
+    const int32_t v = blockIdx.x * blockDim.x + threadIdx.x;
+    if (v >= n || omega[v] <= 1) return;
+    num[v] = comb[v] - deg[v];
+    den[v] = sq64(omega[v] - 1);
+}
+
+// Marks the targets w (negative: none) of one pass in the LDS bitmap, each
+// new one by exactly one thread, and appends those to the queue at out[...]
+// and to the LDS copy of the next level (as far as that reaches), in the
+// order of one LDS counter.  DEG: also sums the new vertices' degrees.
+template <bool DEG>
+TKC_DEV void ring_visit(const int32_t (&w)[4], const int32_t* __restrict__ deg, uint32_t* bits, int32_t spare,
+                        int32_t* out, int32_t* front, int32_t* tail, uint64_t below, int64_t& my_deg) {
+    // the four words are read together (no target: the spare word, which is
+    // read but never marked: lanes that mark one word take turns)
+    uint32_t word[4];
+#pragma unroll
+    for (int j = 0; j < 4; j++)
+        word[j] = __hip_atomic_load(&bits[w[j] >= 0 ? w[j] >> 5 : spare], __ATOMIC_RELAXED,
+                                    __HIP_MEMORY_SCOPE_WORKGROUP);
+    bool isnew[4];
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+        const uint32_t bit = 1u << (w[j] & 31);
+        isnew[j] = w[j] >= 0 && !(word[j] & bit);
+        if (isnew[j]) word[j] = for_wg(&bits[w[j] >> 5], bit);
+    }
+#pragma unroll
+    for (int j = 0; j < 4; j++) isnew[j] = isnew[j] && !((word[j] >> (w[j] & 31)) & 1u);
+    uint64_t m[4];
+    int32_t c = 0;
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+        m[j] = __ballot(isnew[j]);
+        c += __popcll(m[j]);
+    }
+    if (c == 0) return;
+    // the first active lane adds for all: the compiler may run the wave's
+    // lanes through here in groups
+    const int lane = lane_id();
+    int32_t at = 0;
+    if (lane == __builtin_amdgcn_readfirstlane(lane)) at = atomicAdd(tail, c);
+    at = __builtin_amdgcn_readfirstlane(at);
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+        if (isnew[j]) {
+            const int32_t i = at + __popcll(m[j] & below);
+            out[i] = w[j];
+            front[i < RING_FRONT ? i : RING_FRONT] = w[j];   // the slot behind takes the rest
+            if (DEG) my_deg += deg[w[j]];
+        }
+        at += __popcll(m[j]);
+    }
+}
+
+// Expands the frontier vertices base + thread: one aligned 16-byte load
+// brings a vertex's first four arcs (ell); the few vertices with more go on
+// through their rows.  cur is the LDS copy of the level or its part of the
+// queue.  (Two or four vertices per thread and pass, or four threads per
+// vertex, measured the same: the waves of a compute unit hide each other's
+// latency.)
+template <int T, bool DEG>
+TKC_DEV void ring_expand(const RingArgs& a, uint32_t* bits, const int32_t* cur, int32_t items, int32_t base,
+                         int32_t* out, int32_t* front, int32_t* tail, uint64_t below, int64_t& my_deg,
+                         int64_t& arcs) {
+    const int32_t i = base + (int32_t)threadIdx.x;
+    const int32_t u = i < items ? cur[i] : -1;
+    int4 r{-1, -1, -1, -1};
+    if (u >= 0) r = a.w.ell[u];
+    int32_t w[4] = {r.x, r.y, r.z, r.w};
+    int32_t b = 0, e = 0;
+    if (w[3] < -1) {   // -2 - position of the fourth arc
+        b = -2 - w[3];
+        e = a.g.rp[u + 1];
+        w[3] = -1;
+    }
+    arcs += (w[0] >= 0) + (w[1] >= 0) + (w[2] >= 0) + (w[3] >= 0) + (e - b);
+    ring_visit<DEG>(w, a.g.deg, bits, a.words, out, front, tail, below, my_deg);
+    while (__any(b < e)) {
+#pragma unroll
+        for (int j = 0; j < 4; j++) w[j] = b + j < e ? a.g.ci[b + j] : -1;
+        b += 4;
+        ring_visit<DEG>(w, a.g.deg, bits, a.words, out, front, tail, below, my_deg);
+    }
+}
+
+// workgroup barrier that waits for this wave's LDS operations only: global
+// stores (the queue, the level offsets) stay in flight
+TKC_DEV void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+template <int T>
+__global__ void __launch_bounds__(T) k_ring(RingArgs a) {
+    extern __shared__ uint32_t s_bits[];
+    __shared__ int32_t s_tail[3];
+    __shared__ uint64_t s_mask[T / 64], s_omask[T / 64];
+    __shared__ int32_t s_front[2][RING_FRONT + 1];
+    __shared__ int32_t s_off[RING_LEVELS];
+    __shared__ int64_t s_w64[T / 64];
+    __shared__ int64_t s_x[3];
+    __shared__ int64_t s_deg[3];
+    __shared__ int64_t s_pS[RING_PEND], s_pR[RING_PEND], s_thr;
+    __shared__ int32_t s_pI[RING_PEND];
+    __shared__ int32_t s_pos, s_dec, s_cur;
+
+    const int tid = threadIdx.x;
+    const int lane = lane_id();
+    const int wv = tid >> 6;
+    const int32_t n = a.g.n;
+    const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+    const int32_t* __restrict__ deg = a.g.deg;
+    int32_t* q = a.w.queue + (int64_t)blockIdx.x * RING_QSTRIDE(n);
+    int32_t* off = a.w.levoff + (int64_t)blockIdx.x * a.w.lcap;
+    int64_t* lev = a.w.levtab + (int64_t)blockIdx.x * a.w.lcap;
+    const int32_t count = a.ov.count;
+    int64_t st_mvis = 0, st_started = 0, st_exact = 0, st_cut = 0, st_skip = 0, st_maxl = 0, st_bytes = 0;
+
+    for (int32_t i = tid; i < a.words; i += T) s_bits[i] = 0;
+    // Alg. 1's tests of one position: 1 stop, 2 skip, 3 reaches nothing, 0 search
+    auto judge = [&](int32_t p, const XVal& x) -> int {
+        const int32_t v = a.ov.ord[p];
+        const uint32_t key = a.ov.key[p];
+        if (a.ov.key_is_bound ? key_stops(key, x) : (key == 0xffffffffu && x.den != 0)) return 1;
+        const int64_t om = a.rc.omega[v];
+        const int64_t num = ld_rlx(&a.w.comb[v]) - deg[v];
+        if (lex_after(num, om <= 1 ? 0 : sq64(om - 1), TKC_OID(a.g, v), x.num, x.den, x.id)) return 2;
+        return om <= 1 ? 3 : 0;
+    };
+    // Results wait in LDS until the top k's lock is free (thread 0): hundreds
+    // of searches end at about the same time, and a workgroup that spun for
+    // its turn would hold its compute unit and slow the lock's owner.  What
+    // the top k would refuse by now leaves first (in all-ties mode x carries
+    // the largest id, so that cannot tie with the k-th).
+    int32_t npend = 0;
+    auto offer = [&](bool wait) {
+        while (npend > 0) {
+            const XVal x = read_x_poll(a.tk.st, a.tk.ring);
+            int32_t m = 0;
+            for (int32_t i = 0; i < npend; i++) {
+                if (lex_after(s_pS[i], s_pR[i] <= 1 ? 0 : sq64(s_pR[i] - 1), s_pI[i], x.num, x.den, x.id)) continue;
+                s_pS[m] = s_pS[i];
+                s_pR[m] = s_pR[i];
+                s_pI[m++] = s_pI[i];
+            }
+            npend = m;
+            if (m == 0) return;
+            if (topk_try_lock(a.tk.st)) {
+                for (int32_t i = 0; i < m; i++)
+                    topk_insert_locked(a.tk.st, a.tk.ring, a.tk.S, a.tk.R, a.tk.I, s_pS[i], s_pR[i], s_pI[i]);
+                topk_unlock(a.tk.st);
+                npend = 0;
+                return;
+            }
+            if (!wait) return;
+            __builtin_amdgcn_s_sleep(64);
+        }
+    };
+    auto pend = [&](int64_t S, int64_t r, int32_t id) {
+        s_pS[npend] = S;
+        s_pR[npend] = r;
+        s_pI[npend++] = id;
+        offer(npend == RING_PEND);
+    };
+
+    for (;;) {
+        // ---- the next candidate: one position from the shared cursor; if it
+        // is skipped, T positions at a time are judged and the cursor moves
+        // past the skipped ones and the first that is not (compare-and-swap,
+        // so no workgroup holds positions it is not working on; when another
+        // was faster, the judged window serves for the next try)
+        if (tid == 0) {
+            int32_t p = 0, d = 4;   // 4: no more work for this workgroup
+            offer(false);
+            if (ld_rlx(a.w.stop) == 0 && (a.limit == 0 || ld_rlx(a.w.started) < a.limit)) {
+                p = fadd_rlx(a.w.cursor, 1);
+                if (p < count) {
+                    d = judge(p, read_x_poll(a.tk.st, a.tk.ring));
+                    st_skip += d == 2;
+                }
+            }
+            s_pos = p;
+            s_dec = d;
+        }
+        __syncthreads();
+        int dec = s_dec;
+        while (dec == 2) {
+            __syncthreads();
+            if (tid == 0) {
+                s_cur = ld_rlx(a.w.cursor);
+                const XVal x = read_x_poll(a.tk.st, a.tk.ring);
+                s_x[0] = x.num; s_x[1] = x.den; s_x[2] = x.id;
+            }
+            __syncthreads();
+            const int32_t c = s_cur;
+            if (c >= count) { dec = 4; break; }   // uniform
+            const XVal x{s_x[0], s_x[1], (int32_t)s_x[2]};
+            const int d = c + tid < count ? judge(c + tid, x) : 2;
+            const uint64_t m = __ballot(d != 2), mo = __ballot(d == 1 || d == 3);
+            if (lane == 0) {
+                s_mask[wv] = m;
+                s_omask[wv] = mo;
+            }
+            __syncthreads();
+            if (tid == 0) {
+                const int32_t lim = count - c < T ? count - c : T;
+                int32_t at = 0;   // the cursor, relative to the window
+                s_dec = 2;
+                while (at < lim) {
+                    int32_t f = lim;
+                    for (int w = at >> 6; w < T / 64; w++) {
+                        const uint64_t mm = w == at >> 6 ? s_mask[w] & (~0ull << (at & 63)) : s_mask[w];
+                        if (mm) { f = w * 64 + __ffsll((long long)mm) - 1; break; }
+                    }
+                    int32_t seen = c + at;
+                    if (__hip_atomic_compare_exchange_strong(a.w.cursor, &seen, c + (f < lim ? f + 1 : lim),
+                                                             __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                             __HIP_MEMORY_SCOPE_AGENT)) {
+                        st_skip += f - at;
+                        s_pos = c + f;
+                        if (f < lim) s_dec = (s_omask[f >> 6] >> (f & 63)) & 1 ? judge(c + f, x) : 0;
+                        break;
+                    }
+                    at = seen - c;
+                }
+            }
+            __syncthreads();
+            dec = s_dec;
+        }
+        if (dec == 4) break;
+        const int32_t pos = s_pos;
+        if (dec == 1) {
+            if (tid == 0) for_rlx(a.w.stop, 1);
+            break;
+        }
+        const int32_t v = a.ov.ord[pos];
+        if (dec == 3) {
+            if (tid == 0) {
+                st_started++;
+                st_exact++;
+                pend(0, 1, TKC_OID(a.g, v));
+            }
+            __syncthreads();
+            continue;
+        }
+        // ---- the search
+        const int64_t av = a.rc.alpha[v], omv = a.rc.omega[v];
+        if (tid == 0) {
+            if (a.limit) fadd_rlx(a.w.started, 1);
+            s_bits[v >> 5] |= 1u << (v & 31);
+            q[0] = v;
+            s_front[0][0] = v;
+            off[0] = 0;
+            s_off[0] = 0;
+            s_tail[0] = 0;
+            s_tail[1] = 0;
+            s_tail[2] = 0;
+            s_deg[0] = 0;
+            s_deg[1] = 0;
+            s_deg[2] = 0;
+        }
+        __syncthreads();
+        // level D holds q[ls, le); level D + 1 is appended at q[le ...) through
+        // the counter of parity D % 3, which is cleared one level ahead
+        int32_t D = 0, ls = 0, le = 1;
+        int64_t SD = 0, U = deg[v];
+        bool cut = false;
+        const bool shallow_cuts = a.lb_mode == 2;
+        for (;;) {
+            const int c3 = D % 3;
+            if (shallow_cuts && D <= CUTLB_DEPTH) {
+                if (tid == 0) {
+                    const XVal x = read_x_poll(a.tk.st, a.tk.ring);
+                    int64_t bn, bd;
+                    cut_bound(SD, le, U, D, av, omv, &bn, &bd);
+                    s_dec = lex_after(bn, bd, TKC_OID(a.g, v), x.num, x.den, x.id) ? 1 : 0;
+                }
+                __syncthreads();
+                if (s_dec) { cut = true; break; }
+            }
+            if (tid == 0) {
+                const int nx = D % 3 == 2 ? 0 : c3 + 1;
+                s_tail[nx] = 0;
+                s_deg[nx] = 0;
+                if (D + 1 < a.w.lcap) off[D + 1] = le;
+                if (D + 1 < RING_LEVELS) s_off[D + 1] = le;
+            }
+            const int32_t items = le - ls;
+            int32_t* front = s_front[(D + 1) & 1];
+            int64_t my_deg = 0;
+            if (shallow_cuts && D <= CUTLB_DEPTH) {
+                const int32_t* cur = items <= RING_FRONT ? s_front[D & 1] : q + ls;
+                for (int32_t b = 0; b < items; b += T)
+                    ring_expand<T, true>(a, s_bits, cur, items, b, q + le, front, &s_tail[c3], below, my_deg,
+                                            st_mvis);
+                my_deg = wave_sum_i64(my_deg);
+                if (lane == 0 && my_deg) atomicAdd((unsigned long long*)&s_deg[c3], (unsigned long long)my_deg);
+            } else if (items <= RING_FRONT) {
+                for (int32_t b = 0; b < items; b += T)
+                    ring_expand<T, false>(a, s_bits, s_front[D & 1], items, b, q + le, front, &s_tail[c3], below,
+                                             my_deg, st_mvis);
+            } else {
+                for (int32_t b = 0; b < items; b += T)
+                    ring_expand<T, false>(a, s_bits, q + ls, items, b, q + le, front, &s_tail[c3], below, my_deg,
+                                               st_mvis);
+            }
+            lds_barrier();
+            const int32_t cnt = s_tail[c3];
+            if (shallow_cuts && D <= CUTLB_DEPTH) U = s_deg[c3] - cnt;
+            D++;
+            SD += (int64_t)D * cnt;
+            ls = le;
+            le += cnt;
+            if (cnt == 0) break;
+            // a level wider than its LDS copy is read from the queue
+            if (cnt > RING_FRONT) __syncthreads();
+        }
+        // complete: D - 1 is the last level, q[0, le) the vertices in level
+        // order, off[l] the start of level l for l <= D
+        __syncthreads();   // the queue and the offsets are written
+        const int32_t r = le;
+        const int32_t maxD = D - 1;
+        if (tid == 0) {
+            st_started++;
+            const int64_t md = cut ? D : maxD;
+            if (md > st_maxl) st_maxl = md;
+            st_bytes += 12 * (int64_t)le;
+            if (cut) {
+                st_cut++;
+            } else {
+                st_exact++;
+                pend(SD, r, TKC_OID(a.g, v));
+                // a bound above thr is above x: no later search need raise it
+                const XVal x = read_x_poll(a.tk.st, a.tk.ring);
+                const int64_t bden = sq64((int64_t)r - 1);
+                int64_t thr = INT64_MAX - HEAVY_DEG;
+                if (x.den == bden) {
+                    thr = x.num;
+                } else if (x.den != 0) {
+                    const double t = (double)x.num * ((double)bden / (double)x.den) * (1.0 + 1e-9) + 2.0;
+                    if (t < 9e18) thr = (int64_t)t;
+                }
+                s_thr = thr;
+            }
+        }
+        // the bitmap has done its work: it takes the bits of the vertices whose
+        // bound needs no update, all of one pass's tests then stay in LDS
+        const bool update = !cut && maxD >= 1 && D + 1 < a.w.lcap;
+        for (int32_t i = tid; i < a.words; i += T) s_bits[i] = update ? ld_rlx(&a.w.dec[i]) : 0;
+        if (!update) {
+            // deeper than the level tables: no update, and the batched engine
+            // takes the rest of the order
+            if (!cut && maxD >= 1 && tid == 0) for_rlx(a.w.stop, 2);
+        } else {
+            // Lev(l) for l >= 1 (off[D] = r closes the table): Lev(1) from the
+            // sums, then prefix sums of the steps
+            // low_l - (r - pre_l), low_l = vertices at level <= l - 3,
+            // pre_l = vertices at level <= l + 1
+            int64_t run = SD - r + 1 + 2 * (int64_t)(off[2 <= D ? 2 : D] - off[1]) +
+                          (maxD >= 2 ? (int64_t)(off[3] - off[2]) : 0);
+            if (tid == 0) lev[1] = run;
+            for (int32_t b = 2; b <= maxD; b += T) {
+                const int32_t l = b + tid;
+                int64_t step = 0;
+                if (l <= maxD)
+                    step = (l >= 3 ? (int64_t)off[l - 2] : 0) - ((int64_t)r - off[l + 2 <= D ? l + 2 : D]);
+                int64_t inc = step;
+#pragma unroll
+                for (int o = 1; o < 64; o <<= 1) {
+                    const int64_t y = __shfl_up(inc, o, 64);
+                    if (lane >= o) inc += y;
+                }
+                if (lane == 63) s_w64[wv] = inc;
+                __syncthreads();
+                int64_t before = run, all = run;
+                for (int w = 0; w < T / 64; w++) {
+                    if (w < wv) before += s_w64[w];
+                    all += s_w64[w];
+                }
+                if (l <= maxD) lev[l] = before + inc;
+                run = all;
+                __syncthreads();
+            }
+            __syncthreads();
+            const int64_t thr = s_thr + HEAVY_DEG;
+            const int32_t* lo_off = D < RING_LEVELS ? s_off : off;
+            // (a vertex raised above thr is taken off by who raised it; one
+            // that was above already, by the workgroups its word falls to:
+            // hundreds of searches pass over the same words)
+            for (int32_t i0 = 4 * tid; i0 < r; i0 += 4 * T) {
+                const int4 w4 = *(const int4*)(q + i0);   // q is 16-byte aligned and has room
+                const int32_t w[4] = {w4.x, w4.y, w4.z, w4.w};
+                bool todo[4], any = false;
+#pragma unroll
+                for (int j = 0; j < 4; j++) {
+                    todo[j] = i0 + j > 0 && i0 + j < r;
+                    todo[j] = todo[j] && !((s_bits[todo[j] ? w[j] >> 5 : 0] >> (w[j] & 31)) & 1u);
+                    any |= todo[j];
+                }
+                if (!any) continue;
+                // cached copies of the bounds may be old, never too high
+                int64_t cc[4];
+#pragma unroll
+                for (int j = 0; j < 4; j++) cc[j] = todo[j] ? a.w.comb[w[j]] : 0;
+                // level: the last whose first position is not behind i
+                int32_t lo = 1, hi = D;
+                while (hi - lo > 1) {
+                    const int32_t mid = (lo + hi) >> 1;
+                    if (lo_off[mid] <= i0) lo = mid; else hi = mid;
+                }
+#pragma unroll
+                for (int j = 0; j < 4; j++) {
+                    while (lo + 1 < D && lo_off[lo + 1] <= i0 + j) lo++;
+                    if (!todo[j]) continue;
+                    const uint32_t bit = 1u << (w[j] & 31);
+                    const int64_t L = lev[lo];
+                    int64_t c = cc[j];
+                    if (L > c) c = ld_rlx(&a.w.comb[w[j]]);
+                    if (L > c) {
+                        __hip_atomic_fetch_max(&a.w.comb[w[j]], L, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        if (L > thr) for_rlx(&a.w.dec[w[j] >> 5], bit);
+                    } else if (c > thr && (((w[j] >> 5) ^ (int32_t)blockIdx.x) & 31) == 0) {
+                        for_rlx(&a.w.dec[w[j] >> 5], bit);
+                    }
+                }
+            }
+            __syncthreads();
+            for (int32_t i = tid; i < a.words; i += T) s_bits[i] = 0;
+        }
+        __syncthreads();
+    }
+    if (tid == 0) offer(true);
+    st_mvis = wave_sum_i64(st_mvis);
+    if (lane == 0 && st_mvis) {
+        fadd_rlx(&a.stats[ST_MVIS], st_mvis);
+        fadd_rlx(&a.stats[ST_BYTES], 4 * st_mvis);
+    }
+    if (tid == 0) {
+        int64_t* s = a.stats;
+        if (st_started) fadd_rlx(&s[ST_STARTED], st_started);
+        if (st_exact) fadd_rlx(&s[ST_EXACT], st_exact);
+        if (st_cut) fadd_rlx(&s[ST_CUT], st_cut);
+        if (st_skip) fadd_rlx(&s[ST_SKIPPED], st_skip);
+        if (st_bytes) fadd_rlx(&s[ST_BYTES], st_bytes);
+        __hip_atomic_fetch_max(&s[ST_MAXLEVEL], st_maxl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
+// the kernels' static LDS: two level copies, the offsets, and under 1 KiB more
+#define RING_STATIC_LDS (4 * (2 * RING_FRONT + RING_LEVELS) + 1024)
+
+static int ring_lds_limit() {
+    int dev = 0, v = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return 0;
+    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess) return 0;
+    return v;
+}
+// the bitmap and a spare word
+static size_t ring_lds_bytes(int32_t n) { return 4 * (((size_t)n + 31) / 32 + 1); }
+
+int tkc_ring_blocks(const DevGraph& g) {
+    if (g.directed || g.nheavy > 0 || g.m > 8 * (int64_t)g.n || g.n < 2) return 0;
+    if (ring_lds_bytes(g.n) + RING_STATIC_LDS > (size_t)ring_lds_limit()) return 0;
+    const int cus = tkc_cu_count();
+    return cus > 0 ? cus : 0;
+}
+
+int tkc_launch_ring_begin(const DevGraph& g, const DevReach& rc, const BoundsView& bv, const RingWork& w,
+                          hipStream_t s) {
+    hipLaunchKernelGGL(k_ring_begin, dim3((g.n + 255) / 256), dim3(256), 0, s, g.n, rc.omega, (const int32_t*)g.deg,
+                       (const int64_t*)bv.num, (const int64_t*)bv.den, w.comb, w.dec, g.rp, g.ci, w.ell);
+    return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+int tkc_launch_ring_end(const DevGraph& g, const DevReach& rc, const BoundsView& bv, const RingWork& w, hipStream_t s) {
+    hipLaunchKernelGGL(k_ring_end, dim3((g.n + 255) / 256), dim3(256), 0, s, g.n, rc.omega, (const int32_t*)g.deg,
+                       (const int64_t*)w.comb, bv.num, bv.den);
+    return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+int tkc_launch_ring(const DevGraph& g, DevReach rc, OrderView ov, BoundsView bv, DevTopk tk, RingWork w,
+                    int64_t* stats, int lb_mode, int32_t limit, hipStream_t s) {
+    if (!w.queue || !w.levoff || !w.levtab || !w.comb || !w.dec || !w.ell || !w.cursor || !w.stop || !w.started || w.nblocks < 1 || w.lcap < 4)
+        return -2;
+    if (g.directed || g.nheavy > 0 || bv.harm || lb_mode < 1) return -2;
+    const size_t lds = ring_lds_bytes(g.n);
+    if (lds + RING_STATIC_LDS > (size_t)ring_lds_limit()) return -2;
+    RingArgs a{};
+    a.g = g; a.rc = rc; a.ov = ov; a.bv = bv; a.tk = tk; a.w = w;
+    a.stats = stats;
+    a.words = (int32_t)(lds / 4) - 1;
+    a.lb_mode = lb_mode;
+    a.limit = limit;
+    const void* fn = (const void*)k_ring<RING_T>;
+    if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) hipGetLastError();
+    hipLaunchKernelGGL(k_ring<RING_T>, dim3(w.nblocks), dim3(RING_T), lds, s, a);
+    return hipGetLastError() == hipSuccess ? 0 : -1;
+}

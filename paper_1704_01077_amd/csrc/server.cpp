@@ -53,6 +53,7 @@ struct Request {
     std::vector<int64_t> S, R;
     std::vector<double> F;
     size_t need = 0;        // workspace bytes this request needs
+    bool ring = false;      // ... with the ring engine's buffers
 };
 
 }  // namespace
@@ -219,6 +220,7 @@ struct tkc_server {
                 std::lock_guard<std::mutex> lk(mu);
                 skip = rq->cancelled;
             }
+            c->ring_ok = rq->ring;
             if (!skip)
                 st = tkc_run_query(c, g, k, rq->variant, TKC_MODE_AUTO, rq->ids.data(), rq->S.data(), rq->R.data(),
                                    rq->F.data(), &got, nullptr);
@@ -293,7 +295,15 @@ extern "C" int tkc_server_submit(tkc_server* s, int32_t graph_id, int32_t k, int
     rq->variant = variant;
     rq->t_submit = now_ms();
     bool lb = tkc_lb_level(variant) != 0 || variant == TKC_AUTO;
-    rq->need = tkc_ws_bytes(tkc_shape_for(tkc_effective_tuning(s->ctx->tune, g), g, std::min(k, g->n), lb));
+    const WsShape sh = tkc_shape_for(tkc_effective_tuning(s->ctx->tune, g), g, std::min(k, g->n), lb);
+    rq->need = tkc_ws_bytes(sh);
+    // the ring engine's larger buffers only where they fit beside the other
+    // slots' share of the budget
+    const WsShape rs = tkc_shape_ring(sh, g);
+    if (rs.ring && tkc_ws_bytes(rs) <= s->budget / (size_t)s->slots_n) {
+        rq->need = tkc_ws_bytes(rs);
+        rq->ring = true;
+    }
     if (rq->need > s->budget) return tkc_fail(TKC_EBUSY, "request needs %zu bytes, budget is %zu", rq->need, s->budget);
     s->queue.push_back(rq);
     s->all[rq->ticket] = rq;
