@@ -439,45 +439,41 @@ extern "C" int tkc_graph_upload(tkc_ctx* c, int32_t n, int64_t m, const int32_t*
             }
         }
     }
-    // in-arc chunks of the hubs (in-degree above HUB_IN_DEG)
-    std::vector<int32_t> bcb, bce, bcv;
+    // pull items over the in-arcs
+    std::vector<int4> items;
     {
         const int32_t* irp = directed ? hrrp.data() : hrp.data();
-        for (int32_t u = 0; u < n; u++) {
-            if (irp[u + 1] - irp[u] <= HUB_IN_DEG) continue;
-            for (int32_t b = irp[u]; b < irp[u + 1]; b += CHUNK_ARCS) {
-                bcb.push_back(b);
-                bce.push_back(std::min(b + CHUNK_ARCS, irp[u + 1]));
-                bcv.push_back(u);
-            }
-        }
-    }
-    g->bnchunks = (int32_t)bcb.size();
-    // mid in-degree vertices packed into segments (edge-balanced pulls)
-    std::vector<int32_t> mvtx, mseg(1, 0);
-    {
-        const int32_t* irp = directed ? hrrp.data() : hrp.data();
-        int64_t arcs = 0;
+        int4 cur{0, 0, 0, 0};
+        auto close = [&] {
+            if (cur.z) items.push_back(cur);
+            cur.z = cur.w = 0;
+        };
         for (int32_t u = 0; u < n; u++) {
             const int32_t d = irp[u + 1] - irp[u];
-            if (d <= HEAVY_DEG || d > HUB_IN_DEG) continue;
-            const int32_t cnt = (int32_t)mvtx.size() - mseg.back();
-            if (cnt > 0 && (cnt == 64 || arcs + d > MID_ARCS)) {
-                mseg.push_back((int32_t)mvtx.size());
-                arcs = 0;
+            if (d > PULL_ARCS) {
+                close();
+                for (int32_t b = irp[u]; b < irp[u + 1]; b += PULL_ARCS)
+                    items.push_back(int4{u, b, 1, std::min(PULL_ARCS, irp[u + 1] - b) | PULL_SPLIT |
+                                                      (b == irp[u] ? PULL_FIRST : 0)});
+                continue;
             }
-            mvtx.push_back(u);
-            arcs += d;
+            if (cur.z == 64 || cur.w + d > PULL_ARCS) close();
+            if (cur.z == 0) {
+                cur.x = u;
+                cur.y = irp[u];
+            }
+            cur.z++;
+            cur.w += d;
         }
-        if ((int32_t)mvtx.size() > mseg.back()) mseg.push_back((int32_t)mvtx.size());
+        close();
     }
-    g->nmseg = (int32_t)mseg.size() - 1;
+    g->nitems = (int32_t)items.size();
     g->nheavy = (int32_t)hv.size();
     g->nchunks = (int32_t)cb.size();
     g->rnchunks = directed ? (int32_t)rcb.size() : g->nchunks;
     size_t bytes = 4 * (size_t)(n + 1) + 4 * (size_t)(m ? m : 1) + 4 * (size_t)n + 4 * (hv.size() + 1) +
-                   4 * hcb.size() + 12 * (cb.size() + 1) + 12 * (rcb.size() + 1) + 12 * (bcb.size() + 1) +
-                   4 * (mvtx.size() + 1) + 4 * mseg.size() + 16 * 256;
+                   4 * hcb.size() + 12 * (cb.size() + 1) + 12 * (rcb.size() + 1) +
+                   16 * items.size() + ((size_t)m + 64) + 16 * 256;
     if (directed) bytes += 4 * (size_t)(n + 1) + 4 * (size_t)(m ? m : 1);
     if (g->relabeled) bytes += 8 * (size_t)n + 512;
     if (hipMalloc(&g->dbase, bytes + 1024) != hipSuccess) {
@@ -504,11 +500,8 @@ extern "C" int tkc_graph_upload(tkc_ctx* c, int32_t n, int64_t m, const int32_t*
         g->rch_end = g->ch_end;
         g->rch_vtx = g->ch_vtx;
     }
-    g->bch_beg = (int32_t*)take(4 * (bcb.size() + 1));
-    g->bch_end = (int32_t*)take(4 * (bcb.size() + 1));
-    g->bch_vtx = (int32_t*)take(4 * (bcb.size() + 1));
-    g->mid_vtx = (int32_t*)take(4 * (mvtx.size() + 1));
-    g->mseg = (int32_t*)take(4 * mseg.size());
+    g->items = (int4*)take(16 * items.size());
+    g->own = (uint8_t*)take((size_t)m + 64);
     if (directed) {
         g->rrp = (int32_t*)take(4 * (size_t)(n + 1));
         g->rci = (int32_t*)take(4 * (size_t)(m ? m : 1));
@@ -542,15 +535,11 @@ extern "C" int tkc_graph_upload(tkc_ctx* c, int32_t n, int64_t m, const int32_t*
                 (rcb.size() && (hipMemcpyAsync(g->rch_beg, rcb.data(), 4 * rcb.size(), hipMemcpyHostToDevice, s) ||
                                 hipMemcpyAsync(g->rch_end, rce.data(), 4 * rce.size(), hipMemcpyHostToDevice, s) ||
                                 hipMemcpyAsync(g->rch_vtx, rcv.data(), 4 * rcv.size(), hipMemcpyHostToDevice, s))) ||
-                (bcb.size() && (hipMemcpyAsync(g->bch_beg, bcb.data(), 4 * bcb.size(), hipMemcpyHostToDevice, s) ||
-                                hipMemcpyAsync(g->bch_end, bce.data(), 4 * bce.size(), hipMemcpyHostToDevice, s) ||
-                                hipMemcpyAsync(g->bch_vtx, bcv.data(), 4 * bcv.size(), hipMemcpyHostToDevice, s))) ||
-                (mvtx.size() && hipMemcpyAsync(g->mid_vtx, mvtx.data(), 4 * mvtx.size(), hipMemcpyHostToDevice, s)) ||
-                hipMemcpyAsync(g->mseg, mseg.data(), 4 * mseg.size(), hipMemcpyHostToDevice, s)))
+                hipMemcpyAsync(g->items, items.data(), 16 * items.size(), hipMemcpyHostToDevice, s)))
         rc = tkc_fail(TKC_EDEVICE, "heavy-vertex table copy failed");
     if (!rc) {
         DevGraph dg = g->view();
-        if (tkc_launch_degrees(dg, s) || hipStreamSynchronize(s) != hipSuccess)
+        if (tkc_launch_degrees(dg, s) || tkc_launch_own(dg, g->own, s) || hipStreamSynchronize(s) != hipSuccess)
             rc = tkc_fail(TKC_EDEVICE, "degree kernel failed");
     }
     if (rc) {

@@ -33,19 +33,12 @@ struct DevGraph {
     const int32_t* rch_beg;
     const int32_t* rch_end;
     int32_t rnchunks;
-    // in-arc chunks of the hubs only (more than HUB_IN_DEG in-arcs): the
-    // batched engine's pull sends every other vertex through its
-    // edge-balanced path, which shares a wave's in-arcs over all its lanes
-    const int32_t* bch_vtx;
-    const int32_t* bch_beg;
-    const int32_t* bch_end;
-    int32_t bnchunks;
-    // vertices with HEAVY_DEG < in-degree <= HUB_IN_DEG, ascending, packed
-    // into segments of at most 64 vertices and MID_ARCS in-arcs (a segment
-    // of one vertex may exceed it); segment s is mid_vtx[mseg[s] .. mseg[s+1])
-    const int32_t* mid_vtx;
-    const int32_t* mseg;
-    int32_t nmseg;
+    // pull items: the vertices in id order, cut into runs of at most 64
+    // vertices and PULL_ARCS in-arcs, longer rows into pieces of their own;
+    // item = {first vertex, first in-arc, vertices, in-arcs | flags}
+    const int4* items;
+    int32_t nitems;
+    const uint8_t* own;      // per in-arc: its vertex's place in its item
     // relabelled graphs (TKC_RELABEL): the caller's id of each vertex and
     // the vertex of each caller id; null otherwise (ids are the caller's)
     const int32_t* oid = nullptr;
@@ -55,8 +48,10 @@ struct DevGraph {
 #define TKC_OID(g, v) ((g).oid ? (g).oid[v] : (v))
 #define HEAVY_DEG 64
 #define CHUNK_ARCS 512
-#define HUB_IN_DEG 1024
-#define MID_ARCS 1024
+#define PULL_ARCS 256
+#define PULL_SPLIT 0x10000   // a piece of a longer row
+#define PULL_FIRST 0x20000   // ... its first piece
+#define PULL_CNT 0xffff
 
 // reachability and bounds of one query
 struct DevReach {
@@ -123,6 +118,8 @@ int tkc_occupancy(const void* fn, int block);
 
 // k_prep.hip
 int tkc_launch_degrees(const DevGraph& g, hipStream_t s);
+// g.own from g.items (g.rrp gives the rows)
+int tkc_launch_own(const DevGraph& g, uint8_t* own, hipStream_t s);
 // size holds n+2 int64; in_giant n bytes; sample_host is unused (the
 // dominant component is found on the device)
 int tkc_launch_cc(const DevGraph& g, int32_t* parent, int64_t* size, int64_t* alpha, int64_t* omega,

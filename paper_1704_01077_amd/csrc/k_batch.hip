@@ -28,9 +28,9 @@
 #include "dev_common.hpp"
 #include "engine.hpp"
 
-#define BB 256
+#define BB 512
 #define MAXW 256
-#define PUSH_SUB 4   // work items per heavy-vertex chunk in a push
+#define PUSH_SUB 8   // work items per heavy-vertex chunk in a push
 
 // ctr layout (int64)
 #define C_CNT(p, l) ((p) * 2 * MAXW + (l))
@@ -102,15 +102,20 @@ struct Mask {
     }
 };
 
-// Appends to the next level's vertex lists.  One tail counter per list
-// takes every append, and a large level makes tens of thousands of them, so
-// light vertices (the vast majority) are first staged in a per-wave LDS
-// buffer and reserved in the list once per STAGE entries; heavy vertices
-// (rare) are appended directly, together with their arc chunks.
-#define STAGE 1024
+// Appends to the next level's vertex lists.  One tail counter per list takes
+// every append, adds to one address are done one after another (6 to 13 ns
+// each), and a large level appends from tens of thousands of places: new
+// vertices are first staged in LDS, light ones in STAGE slots per wave, heavy
+// ones in HSTAGE, a full buffer takes its place in the list with one add
+// (heavy: one more for the vertices' arc chunks), and what is left at the
+// end of the level goes out with one add per list and workgroup.  (R-MAT of
+// 10^6 vertices, W = 256: with an add per item that finds a heavy vertex,
+// 65,000 a level, a pull level takes 0.86 ms, staged 0.28.)
+#define STAGE 256
+#define HSTAGE 128
 struct Stage {
-    int32_t* buf;   // this wave's LDS slots
-    int32_t n;      // filled slots (wave-uniform)
+    int32_t* buf;    // this wave's LDS slots: light, then heavy
+    int32_t n, nh;   // filled slots (wave-uniform)
 };
 struct NextLists {
     int32_t* light;
@@ -121,15 +126,49 @@ struct NextLists {
     int64_t* ctail;
     const int32_t* rp;
 };
-TKC_DEV void stage_flush(Stage& st, int32_t* list, int64_t* tail) {
-    if (st.n == 0) return;
-    int64_t b = 0;
-    if (lane_id() == 0) b = fadd_rlx(tail, (int64_t)st.n);
-    b = shfl64b(b, 0);
-    __builtin_amdgcn_wave_barrier();
+// the list's places from b on take this wave's staged light vertices
+TKC_DEV void stage_put(const Stage& st, int32_t* list, int64_t b) {
     for (int32_t i = lane_id(); i < st.n; i += 64) list[b + i] = st.buf[i];
-    __builtin_amdgcn_wave_barrier();
-    st.n = 0;
+}
+// the chunks of staged heavy vertex i (0 beyond them)
+TKC_DEV int32_t stage_chunks(const Stage& st, const int32_t* rp, int32_t i, int32_t* v) {
+    if (i >= st.nh) return 0;
+    *v = st.buf[STAGE + i];
+    return (rp[*v + 1] - rp[*v] + CHUNK_ARCS - 1) / CHUNK_ARCS;
+}
+TKC_DEV int32_t wave_excl_sum(int32_t v, int32_t* tot) {
+    int32_t x = v;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int32_t y = __shfl_up(x, o, 64);
+        if (lane_id() >= o) x += y;
+    }
+    *tot = __shfl(x, 63, 64);
+    return x - v;
+}
+// staged heavy vertices to places b ... of their list, their chunks to places
+// c0 ... of the chunk list
+TKC_DEV void stage_put_heavy(const Stage& st, const NextLists& L, int64_t b, int64_t c0) {
+    for (int32_t i0 = 0; i0 < st.nh; i0 += 64) {
+        const int32_t i = i0 + lane_id();
+        int32_t v = 0, tot = 0;
+        const int32_t nck = stage_chunks(st, L.rp, i, &v);
+        const int32_t pre = wave_excl_sum(nck, &tot);
+        if (nck) {
+            L.heavy[b + i] = v;
+            const int32_t r0 = L.rp[v];
+            for (int32_t j = 0; j < nck; j++) {
+                L.cu[c0 + pre + j] = v;
+                L.cb[c0 + pre + j] = r0 + j * CHUNK_ARCS;
+            }
+        }
+        c0 += tot;
+    }
+}
+TKC_DEV int32_t stage_chunk_total(const Stage& st, const int32_t* rp) {
+    int32_t c = 0, v;
+    for (int32_t i = lane_id(); i < st.nh; i += 64) c += stage_chunks(st, rp, i, &v);
+    return wave_sum_i32(c);
 }
 // called by all 64 lanes of a wave
 TKC_DEV void list_append(bool isnew, int32_t w, int32_t dw, const NextLists& L, Stage& st) {
@@ -138,97 +177,127 @@ TKC_DEV void list_append(bool isnew, int32_t w, int32_t dw, const NextLists& L, 
     const uint64_t mh = __ballot(isnew && heavy);
     const uint64_t bm = below_mask();
     if (mh) {
-        int64_t b = 0;
-        if (lane_id() == 0) b = fadd_rlx(&L.tails[1], (int64_t)__popcll(mh));
-        b = shfl64b(b, 0);
-        const int32_t nck = (isnew && heavy) ? (dw + CHUNK_ARCS - 1) / CHUNK_ARCS : 0;
-        int32_t pre = nck;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            int32_t y = __shfl_up(pre, o, 64);
-            if (lane_id() >= o) pre += y;
-        }
-        const int32_t tot = __shfl(pre, 63, 64);
-        pre -= nck;
-        int64_t c0 = 0;
-        if (lane_id() == 0) c0 = fadd_rlx(L.ctail, (int64_t)tot);
-        c0 = shfl64b(c0, 0);
-        if (isnew && heavy) {
-            L.heavy[b + __popcll(mh & bm)] = w;
-            const int32_t r0 = L.rp[w];
-            for (int32_t j = 0; j < nck; j++) {
-                L.cu[c0 + pre + j] = w;
-                L.cb[c0 + pre + j] = r0 + j * CHUNK_ARCS;
+        const int32_t c = __popcll(mh);
+        if (st.nh + c > HSTAGE) {
+            const int32_t nck = stage_chunk_total(st, L.rp);
+            int64_t b = 0, c0 = 0;
+            if (lane_id() == 0) {
+                b = fadd_rlx(&L.tails[1], (int64_t)st.nh);
+                c0 = fadd_rlx(L.ctail, (int64_t)nck);
             }
+            stage_put_heavy(st, L, shfl64b(b, 0), shfl64b(c0, 0));
+            __builtin_amdgcn_wave_barrier();
+            st.nh = 0;
         }
+        if (isnew && heavy) st.buf[STAGE + st.nh + __popcll(mh & bm)] = w;
+        st.nh += c;
     }
     if (ml) {
         const int32_t c = __popcll(ml);
-        if (st.n + c > STAGE) stage_flush(st, L.light, &L.tails[0]);
+        if (st.n + c > STAGE) {
+            int64_t b = 0;
+            if (lane_id() == 0) b = fadd_rlx(&L.tails[0], (int64_t)st.n);
+            stage_put(st, L.light, shfl64b(b, 0));
+            __builtin_amdgcn_wave_barrier();
+            st.n = 0;
+        }
         if (isnew && !heavy) st.buf[st.n + __popcll(ml & bm)] = w;
         st.n += c;
     }
 }
+// what is staged at the end of a level, called by the whole workgroup;
+// sh: 3 int32 per wave and 3 int64 behind them
+template <int NWAVES>
+TKC_DEV void stage_flush(Stage& st, const NextLists& L, int32_t (*sh)[3], int64_t* base) {
+    const int wv = threadIdx.x >> 6;
+    const int32_t nck = st.nh ? stage_chunk_total(st, L.rp) : 0;
+    if (lane_id() == 0) {
+        sh[wv][0] = st.n;
+        sh[wv][1] = st.nh;
+        sh[wv][2] = nck;
+    }
+    __syncthreads();
+    if (threadIdx.x < 3) {
+        const int c = threadIdx.x;
+        int32_t t = 0;
+        for (int i = 0; i < NWAVES; i++) {
+            const int32_t x = sh[i][c];
+            sh[i][c] = t;
+            t += x;
+        }
+        base[c] = t ? fadd_rlx(c == 2 ? L.ctail : &L.tails[c], (int64_t)t) : 0;
+    }
+    __syncthreads();
+    if (st.n) stage_put(st, L.light, base[0] + sh[wv][0]);
+    if (st.nh) stage_put_heavy(st, L, base[1] + sh[wv][1], base[2] + sh[wv][2]);
+    st.n = st.nh = 0;
+}
 
-// Per-lane tallies of newly reached vertices: count and out-degree sum per
-// lane, in the workgroup's LDS.
-// Sparse masks (push): each thread adds its own bits.
+// Per-search tallies of newly reached vertices: lane l of a wave keeps the
+// count and out-degree sum of searches l, 64 + l, ... in registers for a
+// whole level and adds them to the workgroup's LDS once at its end.
 template <int NW>
-TKC_DEV void tally_bits(const Mask<NW>& nb, int32_t dw, int32_t* cnt, int64_t* dsum) {
+struct Tally {
+    int32_t cnt[NW];
+    int64_t dsum[NW];
+    TKC_DEV void clear() {
 #pragma unroll
-    for (int j = 0; j < NW; j++) {
-        uint64_t m = nb.w[j];
-        while (m) {
-            int l = j * 64 + __ffsll((long long)m) - 1;
-            m &= m - 1;
-            atomicAdd(&cnt[l], 1);
-            atomicAdd((unsigned long long*)&dsum[l], (unsigned long long)dw);
+        for (int j = 0; j < NW; j++) { cnt[j] = 0; dsum[j] = 0; }
+    }
+    TKC_DEV void flush(int32_t* c, int64_t* d) {
+#pragma unroll
+        for (int j = 0; j < NW; j++) {
+            if (cnt[j]) {
+                atomicAdd(&c[j * 64 + lane_id()], cnt[j]);
+                atomicAdd((unsigned long long*)&d[j * 64 + lane_id()], (unsigned long long)dsum[j]);
+            }
         }
     }
+};
+TKC_DEV uint64_t readlane64(uint64_t v, int l) {
+    return (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, l) |
+           ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(v >> 32), l) << 32);
 }
-// Dense masks (pull, one vertex per lane), called by all 64 lanes: the
-// wave transposes each word's 64 x 64 bit matrix, so lane l holds the
-// vertices that search lane j * 64 + l reached; their count is a popcount
-// and their out-degree sum is taken bit slice by bit slice of the degrees
-// (one ballot per slice).  One LDS add per lane and word.
+// One vertex per lane (new searches nb, out-degree dw), called by all 64
+// lanes.  Few vertices: one after another, each lane tests its searches'
+// bits of the vertex's words.  Many: the wave transposes each word's 64 x 64
+// bit matrix, so lane l holds the vertices that search j * 64 + l reached;
+// their count is a popcount and their out-degree sum is taken bit slice by
+// bit slice of the degrees (one ballot per slice).
+#define TALLY_FEW 20
 template <int NW>
-TKC_DEV void tally_dense(const Mask<NW>& nb, int32_t dw, int32_t* cnt, int64_t* dsum) {
+TKC_DEV void tally(const Mask<NW>& nb, int32_t dw, Tally<NW>& ty) {
+    uint64_t some = __ballot(nb.any());
+    if (!some) return;   // wave-uniform
     const int lane = lane_id();
+    if (__popcll(some) <= TALLY_FEW) {
+        while (some) {
+            const int v = __ffsll((long long)some) - 1;
+            some &= some - 1;
+            const int32_t d = __builtin_amdgcn_readlane(dw, v);
+#pragma unroll
+            for (int j = 0; j < NW; j++) {
+                const uint64_t w = readlane64(nb.w[j], v);
+                const bool hit = (w >> lane) & 1ull;
+                ty.cnt[j] += hit;
+                ty.dsum[j] += hit ? d : 0;
+            }
+        }
+        return;
+    }
     uint64_t col[NW];
-    int64_t ds[NW];
 #pragma unroll
     for (int j = 0; j < NW; j++) {
         col[j] = __ballot(nb.w[j] != 0) ? wave_transpose64(nb.w[j]) : 0;
-        ds[j] = 0;
+        ty.cnt[j] += __popcll(col[j]);
     }
-    const uint32_t d = (uint32_t)dw;
+    const uint32_t d = nb.any() ? (uint32_t)dw : 0;
     for (int b = 0; b < 32; b++) {
         const uint64_t slice = __ballot((d >> b) & 1u);
         if (!__ballot((d >> b) != 0u)) break;   // wave-uniform
 #pragma unroll
-        for (int j = 0; j < NW; j++) ds[j] += (int64_t)__popcll(col[j] & slice) << b;
+        for (int j = 0; j < NW; j++) ty.dsum[j] += (int64_t)__popcll(col[j] & slice) << b;
     }
-#pragma unroll
-    for (int j = 0; j < NW; j++) {
-        const int c = __popcll(col[j]);
-        if (c) {
-            atomicAdd(&cnt[j * 64 + lane], c);
-            atomicAdd((unsigned long long*)&dsum[j * 64 + lane], (unsigned long long)ds[j]);
-        }
-    }
-}
-// Called by all 64 lanes: the wave picks the cheaper way from two ballots.
-// No new bits -> nothing; a lane with more than four new bits -> the
-// transposition (fixed cost); otherwise each thread adds its own bits (at
-// most four LDS adds per thread and counter kind).
-template <int NW>
-TKC_DEV void tally(const Mask<NW>& nb, int32_t dw, int32_t* cnt, int64_t* dsum) {
-    int32_t bits = 0;
-#pragma unroll
-    for (int j = 0; j < NW; j++) bits += __popcll(nb.w[j]);
-    if (!__ballot(bits != 0)) return;   // wave-uniform
-    if (__ballot(bits > 4)) tally_dense<NW>(nb, dw, cnt, dsum);
-    else tally_bits<NW>(nb, dw, cnt, dsum);
 }
 
 // level of every newly reached lane (level-based bound of Sect. 7)
@@ -245,67 +314,64 @@ TKC_DEV void record_levels(const Mask<NW>& nb, int32_t w, uint16_t* lvl, int W, 
     }
 }
 
-// Edge-balanced pull over up to 64 vertices, one per lane: the lane's
-// vertex has in-arcs [eb, eb + len) and misses the lanes in `miss`; *acc
-// receives the frontier lanes among its in-neighbours, restricted to miss.
-// The wave's lanes share all the arcs: each arc finds its vertex by binary
-// search over the prefix sums and ORs into the vertex's LDS accumulator.
-// Called by all 64 lanes; the LDS slots belong to the calling wave.
+// In-arcs of one pull item: vertex place o of the item misses the lanes
+// c_miss[o], and c_acc[o] (zeroed) receives the frontier lanes among its
+// in-neighbours restricted to those.  NW lanes share an arc, one word each,
+// and every lane takes 4 NW consecutive arcs, so one load brings four
+// indices, one four places, and an accumulator goes to LDS only where the
+// place changes: a long row costs one LDS OR per lane, not one per arc
+// (which all hit one address and take turns).  Words that
+// miss nothing are not read.  Called by all 64 lanes; the LDS slots belong to
+// the calling wave.  The 16-byte and 4-byte loads may run past the item's
+// last arc, never past the graph's allocation.  What bounds it: random 8-byte
+// reads of frontier words (10.4 M arcs of a BA graph of 2^20 vertices in
+// 115-125 us, 83-90 G/s, where a loop of nothing but such reads over 8 MB
+// reaches 108 G/s); on smaller graphs, whose words stay in the L2, the few
+// items each wave gets (2 M arcs: 137 -> 25 us a level).
 template <int NW>
-TKC_DEV void pull_shared(int32_t eb, int32_t len, const Mask<NW>& miss, const uint64_t* Fc,
-                         const int32_t* __restrict__ rci, int32_t* c_pre, int32_t* c_beg, uint64_t* c_miss,
-                         uint64_t* c_acc, Mask<NW>* acc, int64_t* scanned) {
+TKC_DEV void pull_item(int32_t eb, int32_t ne, const uint64_t* Fc, const int32_t* __restrict__ rci,
+                       const uint8_t* __restrict__ own, const uint64_t* c_miss, uint64_t* c_acc, int64_t* scanned) {
     const int lane = lane_id();
-    int32_t pre = len;
+    const int jw = lane & (NW - 1);
+    const int32_t e0 = (lane / NW) * (4 * NW);
+    const int32_t left = ne - e0;
+    // every index and place of the lane, then every missing word, then every
+    // word that is missing: three round trips for all 4 NW arcs
+    int32_t u[4 * NW];
+    uint32_t o4[NW];
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        int32_t y = __shfl_up(pre, o, 64);
-        if (lane >= o) pre += y;
-    }
-    const int32_t tot = __shfl(pre, 63, 64);
-    pre -= len;
-    c_pre[lane] = pre;
-    c_beg[lane] = eb;
-#pragma unroll
-    for (int j = 0; j < NW; j++) {
-        c_miss[lane * NW + j] = miss.w[j];
-        c_acc[lane * NW + j] = 0;
-    }
-    __builtin_amdgcn_wave_barrier();
-    // each lane takes four consecutive arcs per pass: one owner search, then
-    // four index loads and four frontier loads in flight together
-    for (int32_t t0 = lane * 4; t0 < tot; t0 += 256) {
-        int32_t lo = 0, hi = 64;   // owner: last vertex whose range starts at or before t0
-        while (hi - lo > 1) {
-            const int32_t mid = (lo + hi) >> 1;
-            if (c_pre[mid] <= t0) lo = mid; else hi = mid;
+    for (int g = 0; g < NW; g++) {
+        o4[g] = 0;
+        if (left > 4 * g) {
+            __builtin_memcpy(u + 4 * g, rci + eb + e0 + 4 * g, 16);
+            __builtin_memcpy(&o4[g], own + eb + e0 + 4 * g, 4);
         }
-        int32_t own[4], u[4];
+    }
+    uint64_t m[4 * NW], f[4 * NW];
 #pragma unroll
-        for (int q = 0; q < 4; q++) {
-            const int32_t t = t0 + q;
-            own[q] = -1;
-            u[q] = 0;
-            if (t < tot) {
-                while (lo < 63 && c_pre[lo + 1] <= t) lo++;
-                own[q] = lo;
-                u[q] = rci[c_beg[lo] + (t - c_pre[lo])];
-            }
-        }
+    for (int t = 0; t < 4 * NW; t++)
+        m[t] = t < left ? c_miss[((o4[t >> 2] >> (8 * (t & 3))) & 63u) * NW + jw] : 0;
 #pragma unroll
-        for (int q = 0; q < 4; q++) {
-            if (own[q] < 0) continue;
+    for (int t = 0; t < 4 * NW; t++) {
+        f[t] = 0;
+        if (m[t]) {
+            f[t] = Fc[(int64_t)u[t] * NW + jw];
             (*scanned)++;
-#pragma unroll
-            for (int j = 0; j < NW; j++) {
-                const uint64_t f = Fc[(int64_t)u[q] * NW + j] & c_miss[own[q] * NW + j];
-                if (f) atomicOr((unsigned long long*)&c_acc[own[q] * NW + j], (unsigned long long)f);
-            }
         }
     }
-    __builtin_amdgcn_wave_barrier();
+    int32_t cur = 0;
+    uint64_t acc = 0;
 #pragma unroll
-    for (int j = 0; j < NW; j++) acc->w[j] = c_acc[lane * NW + j];
+    for (int t = 0; t < 4 * NW; t++) {
+        const int32_t o = (o4[t >> 2] >> (8 * (t & 3))) & 63u;
+        if (t < left && o != cur) {
+            if (acc) for_wg(&c_acc[cur * NW + jw], acc);
+            acc = 0;
+            cur = o;
+        }
+        acc |= f[t] & m[t];
+    }
+    if (acc) for_wg(&c_acc[cur * NW + jw], acc);
     __builtin_amdgcn_wave_barrier();
 }
 
@@ -470,8 +536,11 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
     __shared__ int32_t s_red_cnt[MAXW];
     __shared__ int64_t s_red_deg[MAXW];
     __shared__ int64_t s_scal[8];
-    __shared__ int32_t s_stage[BB / 64][STAGE];
+    __shared__ int32_t s_stage[BB / 64][STAGE + HSTAGE];
+    __shared__ int32_t s_fl[BB / 64][3];
+    __shared__ int64_t s_flb[3];
     __shared__ int64_t s_blk[4];
+    __shared__ int64_t s_x0[3];
     __shared__ int64_t s_ph[BB / 64][6];
     int64_t ph[6] = {0, 0, 0, 0, 0, 0};
     uint64_t tp = 0;
@@ -482,7 +551,7 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
         ph[i] += (int64_t)(t_ - tp);               \
         tp = t_;                                   \
     }
-    // edge-balanced pull: per-wave vertex ranges, missing lanes, accumulators
+    // per wave: rows of a push, missing lanes and accumulators of a pull item
     __shared__ int32_t s_cpre[BB / 64][64];
     __shared__ int32_t s_cbeg[BB / 64][64];
     __shared__ uint64_t s_cmiss[BB / 64][64 * NW];
@@ -547,8 +616,15 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
         if (nsel == 0) break;
 
         // ------------------------------------------------------ lane init
-        XVal xb{0, 0, 0};
-        if (a.npreq == 0) xb = read_x(a.tk.st, a.tk.ring);
+        // (no fence: the barrier just passed published x)
+        if (a.npreq == 0 && tid == 0) {
+            const XVal x = read_x_poll(a.tk.st, a.tk.ring);
+            s_x0[0] = x.num;
+            s_x0[1] = x.den;
+            s_x0[2] = x.id;
+        }
+        __syncthreads();
+        const XVal xb{s_x0[0], s_x0[1], (int32_t)s_x0[2]};
         if (tid < MAXW) {
             int l = tid;
             if (l < nsel) {
@@ -562,7 +638,7 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
                     off = a.preq[r].off;
                     al = a.preq[r].rc.alpha;
                     om = a.preq[r].rc.omega;
-                    xl = read_x(a.preq[r].tk.st, a.preq[r].tk.ring);
+                    xl = read_x_poll(a.preq[r].tk.st, a.preq[r].tk.ring);
                 }
                 s_v[l] = v;
                 // s_v[l] - s_off[l] is the source's id as the caller numbers
@@ -635,7 +711,8 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
         int64_t fc_len = ld_rlx(&ctr[C_CT(0)]);
         int64_t ol_len = 0, oh_len = 0;
         int64_t ucnt = fl_len + fh_len, udeg = 0;
-        for (int l = 0; l < nsel; l++) udeg += s_mf[l];
+        for (int l = lane; l < nsel; l += 64) udeg += s_mf[l];
+        udeg = wave_sum_i64(udeg);
         // out-arcs of vertices that every active lane has reached: a pull
         // step never scans their in-arcs again
         int64_t ddone = 0;
@@ -718,8 +795,10 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
                                &ctr[C_CT((D + 1) % 3)], rp};
             const int32_t stamp = (int32_t)(D + 1);
             const bool rec_lvl = a.lb_mode && D + 1 < a.w.lcap;
-            Stage stg{&s_stage[tid >> 6][0], 0};
+            Stage stg{&s_stage[tid >> 6][0], 0, 0};
             int64_t my_dd = 0, my_ud = 0;
+            Tally<NW> ty;
+            ty.clear();
             if (trb) tp = wall_clock64();
             // algorithmic bytes: clearing reads a list entry and writes the
             // old frontier word; push reads each frontier vertex's row and
@@ -744,56 +823,25 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
             }
             PHASE(0);
             if (!bu) {
-                if (fl_len <= nwaves) {
-                    // small frontier: one wave per light vertex, one out-arc
-                    // per lane (light vertices have at most 64)
-                    for (int64_t i = gwave; i < fl_len; i += nwaves) {
-                        const int32_t u = fl[i];
-                        Mask<NW> f;
-                        bool done = true;
-#pragma unroll
-                        for (int j = 0; j < NW; j++) {
-                            const uint64_t fw = Fc[(int64_t)u * NW + j];
-                            const uint64_t vn = vis[(int64_t)u * NW + j] | fw;
-                            f.w[j] = fw & act.w[j];
-                            done &= (act.w[j] & ~vn) == 0;
-                            if (lane == 0) vis[(int64_t)u * NW + j] = vn;
-                        }
-                        const int32_t b = rp[u], e1 = rp[u + 1];
-                        if (lane == 0 && done) my_dd += e1 - b;
-                        if (!f.any()) continue;   // wave-uniform
-                        const int32_t e = b + lane;
-                        bool isnew = false;
-                        int32_t w = 0, dw = 0;
-                        Mask<NW> fr;
-#pragma unroll
-                        for (int j = 0; j < NW; j++) fr.w[j] = 0;
-                        if (e < e1) {
-                            w = ci[e];
-                            Mask<NW> nb;
-#pragma unroll
-                            for (int j = 0; j < NW; j++)
-                                nb.w[j] = f.w[j] & ~(vis[(int64_t)w * NW + j] | Fc[(int64_t)w * NW + j]);
-                            if (nb.any()) {
-                                isnew = discover<NW>(Fn, a.mark, w, nb, stamp, &fr);
-                                if (isnew || fr.any()) dw = deg[w];
-                                if (rec_lvl && fr.any()) record_levels<NW>(fr, w, a.w.lvl, W, D + 1);
-                            }
-                        }
-                        tally<NW>(fr, dw, s_red_cnt, s_red_deg);
-                        if (isnew) my_ud += dw;
-                        list_append(isnew, w, dw, nl, stg);
-                    }
-                } else {
-                    // push, light frontier vertices: one per lane; the owner
-                    // folds F_D into the visited word
-                    for (int64_t base = gwave * 64; base < fl_len; base += nwaves * 64) {
-                        int64_t i = base + lane;
-                        int32_t e = 0, end = 0;
+                // push, light frontier vertices: a wave takes up to 64 of them
+                // (fewer when they would not go round), one lane each for the
+                // fold and the row, then shares their out-arcs, one per lane
+                // and pass: the rows with arcs lie side by side in LDS, and
+                // an arc's row is found by counting the rows that start up to
+                // it in a 64-bit mask of the pass
+                {
+                    int64_t per = (fl_len + nwaves - 1) / nwaves;
+                    if (per > 64) per = 64;
+                    int32_t* c_pre = &s_cpre[tid >> 6][0];
+                    int32_t* c_beg = &s_cbeg[tid >> 6][0];
+                    uint64_t* c_f = &s_cmiss[tid >> 6][0];
+                    for (int64_t base = gwave * per; base < fl_len; base += nwaves * per) {
+                        const int64_t i = base + lane;
+                        int32_t eb = 0, len = 0;
                         Mask<NW> f;
 #pragma unroll
                         for (int j = 0; j < NW; j++) f.w[j] = 0;
-                        if (i < fl_len) {
+                        if (lane < per && i < fl_len) {
                             const int32_t u = fl[i];
                             bool done = true;
 #pragma unroll
@@ -804,34 +852,57 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
                                 f.w[j] = fw & act.w[j];
                                 done &= (act.w[j] & ~vn) == 0;
                             }
-                            e = rp[u];
-                            end = rp[u + 1];
-                            if (done) my_dd += end - e;
-                            if (!f.any()) end = e;
+                            eb = rp[u];
+                            len = rp[u + 1] - eb;
+                            if (done) my_dd += len;
+                            if (!f.any()) len = 0;
                         }
-                        while (__any(e < end)) {
+                        int32_t pre = len;
+#pragma unroll
+                        for (int o = 1; o < 64; o <<= 1) {
+                            const int32_t y = __shfl_up(pre, o, 64);
+                            if (lane >= o) pre += y;
+                        }
+                        const int32_t tot = __shfl(pre, 63, 64);
+                        pre -= len;
+                        const uint64_t rows = __ballot(len > 0);
+                        const int rk = __popcll(rows & below_mask());
+                        if (len > 0) {
+                            c_pre[rk] = pre;
+                            c_beg[rk] = eb - pre;
+#pragma unroll
+                            for (int j = 0; j < NW; j++) c_f[rk * NW + j] = f.w[j];
+                        }
+                        __builtin_amdgcn_wave_barrier();
+                        int32_t seen = 0;   // rows that start before this pass
+                        for (int32_t t0 = 0; t0 < tot; t0 += 64) {
+                            const uint64_t starts =
+                                wave_or_u64(len > 0 && pre >= t0 && pre < t0 + 64 ? 1ull << (pre - t0) : 0ull);
+                            const int32_t t = t0 + lane;
                             bool isnew = false;
                             int32_t w = 0, dw = 0;
                             Mask<NW> fr;
 #pragma unroll
                             for (int j = 0; j < NW; j++) fr.w[j] = 0;
-                            if (e < end) {
-                                w = ci[e];
-                                e++;
+                            if (t < tot) {
+                                const int row = seen + __popcll(starts & (~0ull >> (63 - lane))) - 1;
+                                w = ci[c_beg[row] + t];
                                 Mask<NW> nb;
 #pragma unroll
                                 for (int j = 0; j < NW; j++)
-                                    nb.w[j] = f.w[j] & ~(vis[(int64_t)w * NW + j] | Fc[(int64_t)w * NW + j]);
+                                    nb.w[j] = c_f[row * NW + j] & ~(vis[(int64_t)w * NW + j] | Fc[(int64_t)w * NW + j]);
                                 if (nb.any()) {
                                     isnew = discover<NW>(Fn, a.mark, w, nb, stamp, &fr);
                                     if (isnew || fr.any()) dw = deg[w];
                                     if (rec_lvl && fr.any()) record_levels<NW>(fr, w, a.w.lvl, W, D + 1);
                                 }
                             }
-                            tally<NW>(fr, dw, s_red_cnt, s_red_deg);
+                            seen += __popcll(starts);
+                            tally<NW>(fr, dw, ty);
                             if (isnew) my_ud += dw;
                             list_append(isnew, w, dw, nl, stg);
                         }
+                        __builtin_amdgcn_wave_barrier();
                     }
                 }
                 PHASE(2);
@@ -880,209 +951,82 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
                                 if (rec_lvl && fr.any()) record_levels<NW>(fr, w, a.w.lvl, W, D + 1);
                             }
                         }
-                        tally<NW>(fr, dw, s_red_cnt, s_red_deg);
+                        tally<NW>(fr, dw, ty);
                         if (isnew) my_ud += dw;
                         list_append(isnew, w, dw, nl, stg);
                     }
                 }
             } else {
-                // pull: one lane per vertex.  A frontier vertex folds F_D into
-                // its visited words here (readers use vis | F_D, so the
-                // fold's timing does not matter).  Light vertices (few
-                // in-arcs) scan their in-arcs, in groups of four (four
-                // independent index loads, then four independent frontier
-                // loads), until every missing active lane is found
+                // pull: one wave per item, one lane per vertex for what
+                // concerns vertices, the item's arcs shared by all lanes.  A
+                // frontier vertex folds F_D into its visited words here
+                // (readers use vis | F_D, so the fold's timing does not
+                // matter).  The item after next is named one item ahead
                 PHASE(1);
-                // the next pass's frontier and visited words and row
-                // pointers are loaded before this pass's dependent loads, so
-                // they arrive while this pass waits for its own (only this
-                // wave folds these vertices' visited words, and F_D does not
-                // change during the level)
-                uint64_t pf_f[NW], pf_v[NW];
-                int32_t pf_b = 0, pf_e = 0;
-                {
-                    const int64_t w0 = gwave * 64 + lane;
-#pragma unroll
-                    for (int j = 0; j < NW; j++) { pf_f[j] = 0; pf_v[j] = 0; }
-                    if (w0 < n) {
-#pragma unroll
-                        for (int j = 0; j < NW; j++) {
-                            pf_f[j] = Fc[w0 * NW + j];
-                            pf_v[j] = vis[w0 * NW + j];
-                        }
-                        pf_b = a.g.rrp[w0];
-                        pf_e = a.g.rrp[w0 + 1];
-                    }
-                }
-                for (int64_t base = gwave * 64; base < n; base += nwaves * 64) {
-                    const int32_t w = (int32_t)(base + lane);
-                    uint64_t cur_f[NW], cur_v[NW];
-#pragma unroll
-                    for (int j = 0; j < NW; j++) { cur_f[j] = pf_f[j]; cur_v[j] = pf_v[j]; }
-                    const int32_t cur_b = pf_b, cur_e = pf_e;
-                    {
-                        const int64_t w2 = base + nwaves * 64 + lane;
-                        if (w2 < n) {
-#pragma unroll
-                            for (int j = 0; j < NW; j++) {
-                                pf_f[j] = Fc[w2 * NW + j];
-                                pf_v[j] = vis[w2 * NW + j];
-                            }
-                            pf_b = a.g.rrp[w2];
-                            pf_e = a.g.rrp[w2 + 1];
-                        }
-                    }
-                    bool isnew = false;
-                    int32_t dw = 0;
+                uint64_t* c_miss = &s_cmiss[tid >> 6][0];
+                uint64_t* c_acc = &s_cacc[tid >> 6][0];
+                int4 nx{0, 0, 0, 0};
+                if (gwave < a.g.nitems) nx = a.g.items[gwave];
+                for (int64_t it = gwave; it < a.g.nitems; it += nwaves) {
+                    const int4 d = nx;
+                    if (it + nwaves < a.g.nitems) nx = a.g.items[it + nwaves];
+                    const int32_t w = d.x + lane;
+                    const bool split = (d.w & PULL_SPLIT) != 0;
                     Mask<NW> acc, miss;
-                    int32_t eb = 0, len = 0;
+                    bool inF = false;
 #pragma unroll
                     for (int j = 0; j < NW; j++) { acc.w[j] = 0; miss.w[j] = 0; }
-                    if (w < n) {
-                        uint64_t vn[NW];
-                        bool inF = false;
+                    if (lane < d.z) {
+                        uint64_t fw[NW], vn[NW];
+#pragma unroll
+                        for (int j = 0; j < NW; j++) fw[j] = Fc[(int64_t)w * NW + j];
+#pragma unroll
+                        for (int j = 0; j < NW; j++) vn[j] = vis[(int64_t)w * NW + j] | fw[j];
 #pragma unroll
                         for (int j = 0; j < NW; j++) {
-                            const uint64_t fw = cur_f[j];
-                            vn[j] = cur_v[j] | fw;
-                            inF |= fw != 0;
+                            inF |= fw[j] != 0;
                             miss.w[j] = act.w[j] & ~vn[j];
                         }
-                        if (inF) {
+                        if (inF && (!split || (d.w & PULL_FIRST))) {
 #pragma unroll
                             for (int j = 0; j < NW; j++) vis[(int64_t)w * NW + j] = vn[j];
                             if (!miss.any()) my_dd += deg[w];
                         }
-                        eb = cur_b;
-                        const int32_t d_in = cur_e - eb;
-                        if (d_in <= HEAVY_DEG && miss.any()) len = d_in;
                     }
-                    int32_t* c_pre = &s_cpre[tid >> 6][0];
-                    int32_t* c_beg = &s_cbeg[tid >> 6][0];
-                    uint64_t* c_miss = &s_cmiss[tid >> 6][0];
-                    uint64_t* c_acc = &s_cacc[tid >> 6][0];
-                    if (wave_max_i32(len) > 8) {
-                        // skewed in-degrees: the wave's lanes share the arcs
-                        pull_shared<NW>(eb, len, miss, Fc, a.g.rci, c_pre, c_beg, c_miss, c_acc, &acc, &my_scan);
-                    } else if (len > 0) {
-                        {
-                            const int32_t ee = eb + len;
-                            for (int32_t e = eb; e < ee; e += 4) {
-                                my_scan += (ee - e < 4 ? ee - e : 4);
-                                int32_t u[4];
-#pragma unroll
-                                for (int t = 0; t < 4; t++) u[t] = e + t < ee ? a.g.rci[e + t] : -1;
-                                bool full = true;
-#pragma unroll
-                                for (int j = 0; j < NW; j++) {
-                                    uint64_t fo = 0;
-#pragma unroll
-                                    for (int t = 0; t < 4; t++)
-                                        if (u[t] >= 0) fo |= Fc[(int64_t)u[t] * NW + j];
-                                    acc.w[j] |= fo & miss.w[j];
-                                    full &= acc.w[j] == miss.w[j];
-                                }
-                                if (full) break;
-                            }
-                        }
-                    }
-                    if (acc.any()) {
-                        // a light vertex has one pulling thread: plain stores
-#pragma unroll
-                        for (int j = 0; j < NW; j++) Fn[(int64_t)w * NW + j] = acc.w[j];
-                        isnew = true;
-                        dw = deg[w];
-                        if (rec_lvl) record_levels<NW>(acc, w, a.w.lvl, W, D + 1);
-                    }
-                    tally<NW>(acc, dw, s_red_cnt, s_red_deg);
-                    if (isnew) my_ud += dw;
-                    list_append(isnew, w, dw, nl, stg);
-                }
-                PHASE(2);
-                // pull, mid in-degree vertices: packed segments of about
-                // MID_ARCS in-arcs, one wave each, edge-balanced.  Segments,
-                // then hub chunks, are dealt from the last wave down: low
-                // vertex ids tend to have high degrees (preferential
-                // attachment, R-MAT), so the first waves' light blocks are
-                // the heaviest ones
-                for (int64_t sg = nwaves - 1 - gwave; sg < a.g.nmseg; sg += nwaves) {
-                    const int32_t v0 = a.g.mseg[sg], v1 = a.g.mseg[sg + 1];
-                    const int32_t idx = v0 + lane;
-                    int32_t w = 0, eb = 0, len = 0;
-                    Mask<NW> miss, acc;
-#pragma unroll
-                    for (int j = 0; j < NW; j++) { miss.w[j] = 0; acc.w[j] = 0; }
-                    if (idx < v1) {
-                        w = a.g.mid_vtx[idx];
-#pragma unroll
-                        for (int j = 0; j < NW; j++)
-                            miss.w[j] = act.w[j] & ~(vis[(int64_t)w * NW + j] | Fc[(int64_t)w * NW + j]);
-                        eb = a.g.rrp[w];
-                        if (miss.any()) len = a.g.rrp[w + 1] - eb;
-                    }
-                    if (wave_max_i32(len) > 0)
-                        pull_shared<NW>(eb, len, miss, Fc, a.g.rci, &s_cpre[tid >> 6][0], &s_cbeg[tid >> 6][0],
-                                        &s_cmiss[tid >> 6][0], &s_cacc[tid >> 6][0], &acc, &my_scan);
-                    bool isnew = false;
-                    int32_t dw = 0;
-                    if (acc.any()) {
-                        // a mid vertex lies in one segment: one pulling wave, plain stores
-#pragma unroll
-                        for (int j = 0; j < NW; j++) Fn[(int64_t)w * NW + j] = acc.w[j];
-                        isnew = true;
-                        dw = deg[w];
-                        if (rec_lvl) record_levels<NW>(acc, w, a.w.lvl, W, D + 1);
-                    }
-                    tally<NW>(acc, dw, s_red_cnt, s_red_deg);
-                    if (isnew) my_ud += dw;
-                    list_append(isnew, w, dw, nl, stg);
-                }
-                // pull, hubs: one wave per chunk of their in-arcs; chunk c
-                // goes to wave nwaves - 1 - (nmseg + c) mod nwaves
-                for (int64_t c = ((nwaves - 1 - gwave - a.g.nmseg) % nwaves + nwaves) % nwaves; c < a.g.bnchunks;
-                     c += nwaves) {
-                    const int32_t w = a.g.bch_vtx[c];
-                    Mask<NW> miss, acc;
+                    if (!__any(miss.any())) continue;
 #pragma unroll
                     for (int j = 0; j < NW; j++) {
-                        miss.w[j] = __shfl(act.w[j] & ~(vis[(int64_t)w * NW + j] | Fc[(int64_t)w * NW + j]), 0, 64);
-                        acc.w[j] = 0;
+                        c_miss[lane * NW + j] = miss.w[j];
+                        c_acc[lane * NW + j] = 0;
                     }
-                    if (!miss.any()) continue;   // wave-uniform
-                    const int32_t eb = a.g.bch_beg[c], ee = a.g.bch_end[c];
-                    for (int32_t e0 = eb; e0 < ee; e0 += 64) {
-                        const int32_t e = e0 + lane;
-                        my_scan += e < ee ? 1 : 0;
-                        if (e < ee) {
-                            const int32_t u = a.g.rci[e];
+                    __builtin_amdgcn_wave_barrier();
+                    pull_item<NW>(d.y, d.w & PULL_CNT, Fc, a.g.rci, a.g.own, c_miss, c_acc, &my_scan);
 #pragma unroll
-                            for (int j = 0; j < NW; j++) acc.w[j] |= Fc[(int64_t)u * NW + j] & miss.w[j];
-                        }
-                        bool full = true;
-#pragma unroll
-                        for (int j = 0; j < NW; j++) {
-                            acc.w[j] = wave_or_u64(acc.w[j]);
-                            full &= acc.w[j] == miss.w[j];
-                        }
-                        if (full) break;
-                    }
+                    for (int j = 0; j < NW; j++) acc.w[j] = c_acc[lane * NW + j];
+                    __builtin_amdgcn_wave_barrier();
                     bool isnew = false;
                     int32_t dw = 0;
-                    Mask<NW> fr;
+                    if (acc.any()) {
+                        if (!split) {
+                            // the vertex's only wave: plain stores
 #pragma unroll
-                    for (int j = 0; j < NW; j++) fr.w[j] = 0;
-                    if (lane == 0 && acc.any()) {
-                        isnew = discover<NW>(Fn, a.mark, w, acc, stamp, &fr);
-                        if (isnew || fr.any()) dw = deg[w];
-                        if (rec_lvl && fr.any()) record_levels<NW>(fr, w, a.w.lvl, W, D + 1);
+                            for (int j = 0; j < NW; j++) Fn[(int64_t)w * NW + j] = acc.w[j];
+                            isnew = true;
+                        } else {
+                            const Mask<NW> nb = acc;
+                            isnew = discover<NW>(Fn, a.mark, w, nb, stamp, &acc);
+                        }
+                        if (isnew || acc.any()) dw = deg[w];
+                        if (rec_lvl) record_levels<NW>(acc, w, a.w.lvl, W, D + 1);
                     }
-                    tally<NW>(fr, dw, s_red_cnt, s_red_deg);
+                    tally<NW>(acc, dw, ty);
                     if (isnew) my_ud += dw;
                     list_append(isnew, w, dw, nl, stg);
                 }
             }
             PHASE(3);
-            stage_flush(stg, nl.light, nl.tails);
+            stage_flush<BB / 64>(stg, nl, s_fl, s_flb);
+            ty.flush(s_red_cnt, s_red_deg);
             // workgroup totals into this level's counters
             my_dd = wave_sum_i64(my_dd);
             my_ud = wave_sum_i64(my_ud);
@@ -1387,6 +1331,15 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
     if (boss) stats[ST_CURSOR] = pos;
 }
 
+// workgroups of a launch: about one pull item per wave, at least 8, at most
+// the whole GPU (a grid barrier costs 1.8 us for 16 workgroups, 3.4 for 64,
+// 6.2 for 256)
+static int batch_grid(int full, const DevGraph& g) {
+    int64_t want = ((int64_t)g.nitems + BB / 64 - 1) / (BB / 64);
+    if (want < 8) want = 8;
+    return (int)(want < full ? want : full);
+}
+
 int tkc_launch_batch(const DevGraph& g, DevReach rc, OrderView ov, BoundsView bv, DevTopk tk,
                      BatchWork w, int64_t* stats, const int32_t* list, int32_t list_count,
                      int32_t start_pos, int32_t max_batches, int lb_mode, bool no_cut,
@@ -1411,7 +1364,7 @@ int tkc_launch_batch(const DevGraph& g, DevReach rc, OrderView ov, BoundsView bv
     if (occ < 1) return -1;
     const int want = tune.blocks_per_cu > 0 ? tune.blocks_per_cu : 2;
     int per = occ < want ? occ : want;
-    const int grid = tkc_grid_for(cus, per, g.n);
+    const int grid = batch_grid(cus * per, g);
     if (grid_out) *grid_out = grid;
     BatchArgs a{};
     a.g = g; a.rc = rc; a.ov = ov; a.bv = bv; a.tk = tk; a.w = w;

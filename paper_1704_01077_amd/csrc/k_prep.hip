@@ -17,6 +17,21 @@ __global__ void k_degrees(int32_t n, const int32_t* __restrict__ rp, int32_t* __
 }
 
 
+// the place of every in-arc's vertex in its pull item: one wave per item,
+// each lane fills its vertex's row (a piece of a longer row has place 0)
+__global__ void k_own(int32_t nitems, const int4* __restrict__ items, const int32_t* __restrict__ rrp,
+                      uint8_t* __restrict__ own) {
+    const int32_t it = (int32_t)(((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6);
+    if (it >= nitems) return;
+    const int4 d = items[it];
+    const int lane = lane_id();
+    if (d.w & PULL_SPLIT) {
+        for (int32_t e = lane; e < (d.w & PULL_CNT); e += 64) own[d.y + e] = 0;
+    } else if (lane < d.z) {
+        for (int32_t e = rrp[d.x + lane]; e < rrp[d.x + lane + 1]; e++) own[e] = (uint8_t)lane;
+    }
+}
+
 // ----------------------------------------------- connected components
 // r(v) of an undirected graph is the size of v's component (Sect. 4).
 // Lock-free union-find in the style of Afforest (Sutton, Ben-Nun, Barak,
@@ -565,6 +580,11 @@ static inline int nblk(int64_t n, int b) { return (int)((n + b - 1) / b); }
 int tkc_launch_degrees(const DevGraph& g, hipStream_t s) {
     int32_t n = g.n;
     hipLaunchKernelGGL(k_degrees, dim3(nblk(n, 256)), dim3(256), 0, s, n, g.rp, g.deg);
+    return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+int tkc_launch_own(const DevGraph& g, uint8_t* own, hipStream_t s) {
+    hipLaunchKernelGGL(k_own, dim3(nblk((int64_t)g.nitems * 64, 256)), dim3(256), 0, s, g.nitems, g.items, g.rrp, own);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
