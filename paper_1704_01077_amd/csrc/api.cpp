@@ -103,7 +103,7 @@ static size_t ws_items(Workspace& ws, const WsShape& sh, std::vector<WsItem>& it
         {(void**)&ws.b_vis, 8 * n * nw, true}, {(void**)&ws.b_frt0, 8 * n * nw, true},
         {(void**)&ws.b_frt1, 8 * n * nw, true}, {(void**)&ws.b_nxt, 8 * n * nw, true},
         {(void**)&ws.b_list, 32 * n + 16 * ((size_t)sh.nchunks + 64), false}, {(void**)&ws.b_mark, 4 * n, true},
-        {(void**)&ws.b_ctr, 8 * 2048, true}, {(void**)&ws.b_cand, 8 * 256, false},
+        {(void**)&ws.b_ctr, 8 * 4096, true}, {(void**)&ws.b_cand, 4 * 1024, false},
         {(void**)&ws.b_hist, sh.lb ? 8 * lcap * W : 8, false},
         {(void**)&ws.b_levtab, sh.lb ? 8 * lcap * W : 8, false},
         {(void**)&ws.b_lvl, sh.lb ? 2 * n * W : 8, false},
@@ -706,7 +706,7 @@ BatchWork tkc_batch_view(Workspace& ws) {
     w.ccap = (int64_t)ws.shape.nchunks + 64;
     w.lvl = ws.b_lvl; w.hist = ws.b_hist; w.levtab = ws.b_levtab; w.lcap = ws.shape.lcap;
     w.cand = ws.b_cand;
-    w.cand_req = ws.b_cand + 256;
+    w.cand_req = ws.b_cand + 512;
     w.trace = ws.trace;
     w.trace_cap = ws.trace ? 4096 : 0;
     w.bar = ws.bar;

@@ -216,14 +216,14 @@ struct BatchWork {
     int32_t* list;       // level lists: 8 n vertex entries (4 slots x light/heavy) + 4 ccap chunk entries
     int64_t ccap;        // chunk entries per list
     int32_t* touched;    // every vertex touched in the batch (for clearing), cap n
-    int64_t* ctr;        // per-lane level counters, 3 * 2 * 256 + misc
+    int64_t* ctr;        // two batches' turns of per-lane level counters, 3 * 2 * 256 + misc
     int64_t* lanes;      // per-lane state
     uint16_t* lvl;       // n * W levels (level-based updates), may be null
     int64_t* hist;       // LCAP * W vertices per level per lane
     int64_t* levtab;     // LCAP * W Lev tables
     int32_t lcap;
-    int32_t* cand;       // selected candidates of a batch (W)
-    int32_t* cand_req;   // the request of each candidate (W; packed launches)
+    int32_t* cand;       // selected candidates, two batches' turns of 256
+    int32_t* cand_req;   // the request of each candidate (packed launches)
     int64_t* trace;      // optional per-level records (16 int64 from word 8), [0] = count
     int64_t trace_cap;
     uint32_t* bar;       // grid barrier state (zeroed once)

@@ -30,6 +30,11 @@
 
 #define BB 512
 #define MAXW 256
+// LDS words of a pull item by word, then vertex place: the lanes of a wave
+// touch neighbouring banks, and the NW words of one place different ones (by
+// place, then word, 64 lanes fell on 8 banks: 11.5 against 9.9 ms on R-MAT of
+// 2^20 vertices, W = 256)
+#define LSTR 66
 #define PUSH_SUB 8   // work items per heavy-vertex chunk in a push
 
 // ctr layout (int64)
@@ -49,7 +54,7 @@
 #define C_POS (C_BASE + 25)
 #define C_STOP (C_BASE + 26)
 #define C_XDONE (C_BASE + 27)   // until_x: x became finite in this batch
-#define C_TOTAL (C_BASE + 32)
+#define C_TOTAL (C_BASE + 32)   // one set; batches take turns at two
 
 struct BatchArgs {
     DevGraph g;
@@ -277,24 +282,34 @@ TKC_DEV void tally(const Mask<NW>& nb, int32_t dw, Tally<NW>& ty) {
             const int32_t d = __builtin_amdgcn_readlane(dw, v);
 #pragma unroll
             for (int j = 0; j < NW; j++) {
-                const uint64_t w = readlane64(nb.w[j], v);
-                const bool hit = (w >> lane) & 1ull;
+                const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)nb.w[j], v);
+                const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(nb.w[j] >> 32), v);
+                const int32_t hit = (int32_t)(((lane < 32 ? lo : hi) >> (lane & 31)) & 1u);
                 ty.cnt[j] += hit;
-                ty.dsum[j] += hit ? d : 0;
+                ty.dsum[j] += (uint32_t)(-hit & d);
             }
         }
         return;
     }
     uint64_t col[NW];
+    uint32_t part[NW];   // sums of the low 26 bits of 64 degrees
 #pragma unroll
     for (int j = 0; j < NW; j++) {
         col[j] = __ballot(nb.w[j] != 0) ? wave_transpose64(nb.w[j]) : 0;
         ty.cnt[j] += __popcll(col[j]);
+        part[j] = 0;
     }
     const uint32_t d = nb.any() ? (uint32_t)dw : 0;
-    for (int b = 0; b < 32; b++) {
+    int b = 0;
+    for (; b < 26 && __ballot((d >> b) != 0u); b++) {   // wave-uniform
         const uint64_t slice = __ballot((d >> b) & 1u);
-        if (!__ballot((d >> b) != 0u)) break;   // wave-uniform
+#pragma unroll
+        for (int j = 0; j < NW; j++) part[j] += (uint32_t)__popcll(col[j] & slice) << b;
+    }
+#pragma unroll
+    for (int j = 0; j < NW; j++) ty.dsum[j] += part[j];
+    for (; b < 32 && __ballot((d >> b) != 0u); b++) {
+        const uint64_t slice = __ballot((d >> b) & 1u);
 #pragma unroll
         for (int j = 0; j < NW; j++) ty.dsum[j] += (int64_t)__popcll(col[j] & slice) << b;
     }
@@ -315,63 +330,70 @@ TKC_DEV void record_levels(const Mask<NW>& nb, int32_t w, uint16_t* lvl, int W, 
 }
 
 // In-arcs of one pull item: vertex place o of the item misses the lanes
-// c_miss[o], and c_acc[o] (zeroed) receives the frontier lanes among its
-// in-neighbours restricted to those.  NW lanes share an arc, one word each,
+// c_miss[. + o], and c_acc[. + o] (zeroed) receives the frontier lanes among its
+// in-neighbours (the caller keeps the missing ones).  NW lanes share an arc, one word each,
 // and every lane takes 4 NW consecutive arcs, so one load brings four
 // indices, one four places, and an accumulator goes to LDS only where the
 // place changes: a long row costs one LDS OR per lane, not one per arc
 // (which all hit one address and take turns).  Words that
 // miss nothing are not read.  Called by all 64 lanes; the LDS slots belong to
-// the calling wave.  The 16-byte and 4-byte loads may run past the item's
+// the calling wave.  The indices (ItemArcs::load) are asked for
+// together with the vertices own words; these 16-byte and 4-byte loads may run
+// past the item's
 // last arc, never past the graph's allocation.  What bounds it: random 8-byte
 // reads of frontier words (10.4 M arcs of a BA graph of 2^20 vertices in
 // 115-125 us, 83-90 G/s, where a loop of nothing but such reads over 8 MB
 // reaches 108 G/s); on smaller graphs, whose words stay in the L2, the few
 // items each wave gets (2 M arcs: 137 -> 25 us a level).
 template <int NW>
-TKC_DEV void pull_item(int32_t eb, int32_t ne, const uint64_t* Fc, const int32_t* __restrict__ rci,
-                       const uint8_t* __restrict__ own, const uint64_t* c_miss, uint64_t* c_acc, int64_t* scanned) {
-    const int lane = lane_id();
-    const int jw = lane & (NW - 1);
-    const int32_t e0 = (lane / NW) * (4 * NW);
-    const int32_t left = ne - e0;
-    // every index and place of the lane, then every missing word, then every
-    // word that is missing: three round trips for all 4 NW arcs
+struct ItemArcs {
     int32_t u[4 * NW];
     uint32_t o4[NW];
+    int32_t left;
+    TKC_DEV void load(int32_t eb, int32_t ne, const int32_t* __restrict__ rci, const uint8_t* __restrict__ own) {
+        const int32_t e0 = (lane_id() / NW) * (4 * NW);
+        left = ne - e0;
 #pragma unroll
-    for (int g = 0; g < NW; g++) {
-        o4[g] = 0;
-        if (left > 4 * g) {
-            __builtin_memcpy(u + 4 * g, rci + eb + e0 + 4 * g, 16);
-            __builtin_memcpy(&o4[g], own + eb + e0 + 4 * g, 4);
+        for (int g = 0; g < NW; g++) {
+            o4[g] = 0;
+            if (left > 4 * g) {
+                __builtin_memcpy(u + 4 * g, rci + eb + e0 + 4 * g, 16);
+                __builtin_memcpy(&o4[g], own + eb + e0 + 4 * g, 4);
+            }
         }
     }
-    uint64_t m[4 * NW], f[4 * NW];
+};
+template <int NW>
+TKC_DEV void pull_item(const ItemArcs<NW>& ar, const uint64_t* Fc, const uint64_t* c_miss, uint64_t* c_acc,
+                       int64_t* scanned) {
+    const int jw = lane_id() & (NW - 1);
+    const int32_t left = ar.left;
+    uint32_t need = 0;   // arcs whose vertex misses lanes of this word
 #pragma unroll
-    for (int t = 0; t < 4 * NW; t++)
-        m[t] = t < left ? c_miss[((o4[t >> 2] >> (8 * (t & 3))) & 63u) * NW + jw] : 0;
+    for (int t = 0; t < 4 * NW; t++) {
+        const int32_t o = (ar.o4[t >> 2] >> (8 * (t & 3))) & 63u;
+        need |= (uint32_t)(t < left && c_miss[jw * LSTR + o] != 0) << t;
+    }
+    *scanned += __popc(need);
+    uint64_t f[4 * NW];
 #pragma unroll
     for (int t = 0; t < 4 * NW; t++) {
         f[t] = 0;
-        if (m[t]) {
-            f[t] = Fc[(int64_t)u[t] * NW + jw];
-            (*scanned)++;
-        }
+        if ((need >> t) & 1u) f[t] = Fc[(int64_t)ar.u[t] * NW + jw];
     }
     int32_t cur = 0;
     uint64_t acc = 0;
 #pragma unroll
     for (int t = 0; t < 4 * NW; t++) {
-        const int32_t o = (o4[t >> 2] >> (8 * (t & 3))) & 63u;
+        const int32_t o = (ar.o4[t >> 2] >> (8 * (t & 3))) & 63u;
         if (t < left && o != cur) {
-            if (acc) for_wg(&c_acc[cur * NW + jw], acc);
+            if (acc) for_wg(&c_acc[jw * LSTR + cur], acc);
             acc = 0;
             cur = o;
         }
-        acc |= f[t] & m[t];
+        acc |= f[t];
     }
-    if (acc) for_wg(&c_acc[cur * NW + jw], acc);
+    if (acc) for_wg(&c_acc[jw * LSTR + cur], acc);
     __builtin_amdgcn_wave_barrier();
 }
 
@@ -514,7 +536,6 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
     const int32_t* __restrict__ rp = a.g.rp;
     const int32_t* __restrict__ ci = a.g.ci;
     const int32_t* __restrict__ deg = a.g.deg;
-    int64_t* ctr = a.w.ctr;
     uint64_t* vis = a.w.vis;
     int64_t* stats = a.stats;
     const bool order_mode = (a.list == nullptr);
@@ -541,6 +562,7 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
     __shared__ int64_t s_flb[3];
     __shared__ int64_t s_blk[4];
     __shared__ int64_t s_x0[3];
+    __shared__ int32_t s_un[MAXW];
     __shared__ int64_t s_ph[BB / 64][6];
     int64_t ph[6] = {0, 0, 0, 0, 0, 0};
     uint64_t tp = 0;
@@ -554,8 +576,8 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
     // per wave: rows of a push, missing lanes and accumulators of a pull item
     __shared__ int32_t s_cpre[BB / 64][64];
     __shared__ int32_t s_cbeg[BB / 64][64];
-    __shared__ uint64_t s_cmiss[BB / 64][64 * NW];
-    __shared__ uint64_t s_cacc[BB / 64][64 * NW];
+    __shared__ uint64_t s_cmiss[BB / 64][LSTR * NW];
+    __shared__ uint64_t s_cacc[BB / 64][LSTR * NW];
 
     int32_t pos = a.start_pos;
     int32_t batches = 0;
@@ -564,7 +586,12 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
         s_pk_stop[tid] = 0;
     }
     __syncthreads();
+    if (blockIdx.x == 0)
+        for (int i = tid; i < C_NSEL; i += BB) a.w.ctr[i] = 0;
     while (batches < a.max_batches) {
+        int64_t* const ctr = a.w.ctr + (batches & 1) * C_TOTAL;
+        int32_t* const cand = a.w.cand + (batches & 1) * MAXW;
+        int32_t* const cand_req = a.w.cand_req + (batches & 1) * MAXW;
         // ---------------------------------------------- candidate selection
         if (blockIdx.x == 0 && tid < 64) {
             int32_t nsel = 0;
@@ -574,7 +601,7 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
                 const SelIn in{order_mode ? a.ov.ord : a.list, order_mode ? a.ov.key : nullptr, count,
                                a.ov.key_is_bound, a.bv.num, a.bv.den, a.rc.omega, a.tk, a.bv.harm, a.no_cut, 0,
                                a.g.oid};
-                select_cands(in, pos, a.Wsel, a.w.cand, nsel, stop, skipped, r1);
+                select_cands(in, pos, a.Wsel, cand, nsel, stop, skipped, r1);
             } else {
                 // the requests of a pack take turns: first up to an even
                 // share of the lanes each, then whatever is left over
@@ -588,8 +615,8 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
                         const int32_t before = nsel;
                         const int32_t cap = pass == 0 ? (nsel + share < a.Wsel ? nsel + share : a.Wsel) : a.Wsel;
                         int32_t rpos = s_pk_pos[r], rstop = s_pk_stop[r];
-                        select_cands(in, rpos, cap, a.w.cand, nsel, rstop, skipped, r1);
-                        for (int32_t c = before + lane; c < nsel; c += 64) a.w.cand_req[c] = r;
+                        select_cands(in, rpos, cap, cand, nsel, rstop, skipped, r1);
+                        for (int32_t c = before + lane; c < nsel; c += 64) cand_req[c] = r;
                         __builtin_amdgcn_wave_barrier();
                         if (lane == 0) {
                             s_pk_pos[r] = rpos;
@@ -628,13 +655,13 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
         if (tid < MAXW) {
             int l = tid;
             if (l < nsel) {
-                int32_t v = a.w.cand[l];
+                int32_t v = cand[l];
                 int32_t off = 0, r = 0;
                 const int64_t* al = a.rc.alpha;
                 const int64_t* om = a.rc.omega;
                 XVal xl = xb;
                 if (a.npreq) {
-                    r = a.w.cand_req[l];
+                    r = cand_req[l];
                     off = a.preq[r].off;
                     al = a.preq[r].rc.alpha;
                     om = a.preq[r].rc.omega;
@@ -660,57 +687,45 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
             }
         }
         __syncthreads();   // every lane's source is in s_v
-        if (blockIdx.x == 0) {
-            // level-0 frontier (list slot 0): light sources, heavy sources
-            // and the heavy sources' arc chunks.  A source list may name one
-            // vertex twice: F_0 takes atomic ORs, the lists take it once.
-            if (tid < 3) s_blk[tid] = 0;
-            __syncthreads();
-            if (tid < nsel) {
-                const int l = tid;
-                const int32_t v = s_v[l];
-                for_rlx(&fsel(a.w, 0)[(int64_t)v * NW + (l >> 6)], (uint64_t)1 << (l & 63));
-                if (a.lb_mode) { a.w.lvl[(int64_t)v * W + l] = 0; a.w.hist[l] = 1; }
-                bool dup = false;
-                for (int q = 0; q < l; q++) dup |= s_v[q] == v;
-                if (!dup) {
-                    const int32_t dv = deg[v];
-                    if (dv > HEAVY_DEG) {
-                        const int32_t nck = (dv + CHUNK_ARCS - 1) / CHUNK_ARCS;
-                        const int64_t h = (int64_t)atomicAdd((unsigned long long*)&s_blk[1], 1ull);
-                        const int64_t c0 = (int64_t)atomicAdd((unsigned long long*)&s_blk[2], (unsigned long long)nck);
-                        VL(1, 0)[h] = v;
-                        const int32_t r0 = rp[v];
-                        for (int32_t j = 0; j < nck; j++) {
-                            CU(0)[c0 + j] = v;
-                            CB(0)[c0 + j] = r0 + j * CHUNK_ARCS;
-                        }
-                    } else {
-                        const int64_t h = (int64_t)atomicAdd((unsigned long long*)&s_blk[0], 1ull);
-                        VL(0, 0)[h] = v;
-                    }
-                }
+        // Level 0 needs no lists: every workgroup knows the sources, and cuts
+        // their rows into units of 64 arcs (s_un: first unit of each source)
+        int32_t units = 0;
+        {
+            const int wv = tid >> 6;
+            int32_t pre = 0;
+            if (tid < MAXW) {
+                int32_t tot;
+                pre = wave_excl_sum(tid < nsel ? (int32_t)((s_mf[tid] + 63) >> 6) : 0, &tot);
+                if (lane == 0) s_fl[wv][0] = tot;
             }
-            // per-lane counters of every parity (C_CNT, C_DEG)
-            for (int i = tid; i < C_BASE; i += BB) ctr[i] = 0;
             __syncthreads();
-            if (tid == 0) {
-                for (int p = 0; p < 3; p++) { ctr[C_UDEG(p)] = 0; ctr[C_DDONE(p)] = 0; ctr[C_CT(p)] = 0; }
-                for (int q = 0; q < 4; q++) { ctr[C_LT(q, 0)] = 0; ctr[C_LT(q, 1)] = 0; }
-                ctr[C_LT(0, 0)] = s_blk[0];
-                ctr[C_LT(0, 1)] = s_blk[1];
-                ctr[C_CT(0)] = s_blk[2];
+            for (int w = 0; w < MAXW / 64; w++) {
+                if (w < wv) pre += s_fl[w][0];
+                units += s_fl[w][0];
             }
+            if (tid < MAXW) s_un[tid] = pre;
         }
-        grid_barrier(a.bar, gridDim.x);
+        if (blockIdx.x == 0) {
+            if (tid < nsel) {
+                const int32_t v = s_v[tid];
+                // (a source list may name one vertex twice)
+                for_rlx(&vis[(int64_t)v * NW + (tid >> 6)], (uint64_t)1 << (tid & 63));
+                if (a.lb_mode) { a.w.lvl[(int64_t)v * W + tid] = 0; a.w.hist[tid] = 1; }
+            }
+            // the next batch's counters: every workgroup has passed the barrier
+            // behind the batch that used them last
+            int64_t* nctr = a.w.ctr + ((batches + 1) & 1) * C_TOTAL;
+            for (int i = tid; i < C_NSEL; i += BB) nctr[i] = 0;
+        }
+        __syncthreads();
 
         int64_t D = 0;
-        // lengths of the current level's lists (L_D) and of the previous
-        // level's (L_{D-1}, whose frontier words are cleared during level D)
-        int64_t fl_len = ld_rlx(&ctr[C_LT(0, 0)]), fh_len = ld_rlx(&ctr[C_LT(0, 1)]);
-        int64_t fc_len = ld_rlx(&ctr[C_CT(0)]);
+        // lengths of the current level's lists (L_D; none at level 0) and of
+        // the previous level's (L_{D-1}, whose frontier words are cleared
+        // during level D)
+        int64_t fl_len = 0, fh_len = 0, fc_len = 0;
         int64_t ol_len = 0, oh_len = 0;
-        int64_t ucnt = fl_len + fh_len, udeg = 0;
+        int64_t ucnt = nsel, udeg = 0;
         for (int l = lane; l < nsel; l += 64) udeg += s_mf[l];
         udeg = wave_sum_i64(udeg);
         // out-arcs of vertices that every active lane has reached: a pull
@@ -768,8 +783,12 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
             // scanned.  A pull also needs a frontier of at least n / beta
             // vertices, the size below which a pull returns to push, so the
             // choice cannot flip back and forth between small levels.
-            const bool big = ucnt >= (int64_t)n / a.beta_bu;
-            bool want_bu = bu ? big : (big && udeg > (a.g.m - ddone) / a.alpha_td);
+            // (big: by vertices or by arcs, a frontier of few hubs has many.  An
+            // arc of a push costs about twice its share of Beamer's alpha: BA
+            // of 300,000 vertices, 280,000 of 4.8 M arcs pushed in 62 us, all
+            // of them pulled in 44.)
+            const bool big = ucnt >= (int64_t)n / a.beta_bu || udeg >= a.g.m / a.beta_bu;
+            const bool want_bu = D > 0 && (bu ? big : (big && 2 * udeg > (a.g.m - ddone) / a.alpha_td));
             bu = want_bu;
             tslot = -1;
             if (boss && a.w.trace) {
@@ -809,8 +828,7 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
             // and per scanned in-arc reads the index and a frontier word
             // (counted in my_scan)
             bytes += (ol_len + oh_len) * (4 + 8 * NW) +
-                     (bu ? (int64_t)n * (8 + 16 * NW) + (fl_len + fh_len) * (8 * NW)
-                         : (fl_len + fh_len) * (8 + 24 * NW) + udeg * (4 + 24 * NW));
+                     (bu ? (int64_t)n * (8 + 16 * NW) + ucnt * (8 * NW) : ucnt * (8 + 24 * NW) + udeg * (4 + 24 * NW));
             // (1) F_{D-1} is no longer read: clear its words through L_{D-1}
             {
                 const int32_t* ofl = VL(0, sO);
@@ -822,7 +840,43 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
                 }
             }
             PHASE(0);
-            if (!bu) {
+            if (D == 0) {
+                // a source's neighbours are all new to its search: one arc per
+                // lane, no visited or frontier word to read
+                for (int64_t un = gwave; un < units; un += nwaves) {
+                    int32_t l = 0, hi = nsel;   // the last source whose units start up to un
+                    while (hi - l > 1) {
+                        const int32_t mid = (l + hi) >> 1;
+                        if (s_un[mid] <= un) l = mid; else hi = mid;
+                    }
+                    if (s_st[l] != 1) continue;   // wave-uniform
+                    const int32_t u = s_v[l];
+                    const int32_t e = rp[u] + ((int32_t)un - s_un[l]) * 64 + lane;
+                    bool isnew = false;
+                    int32_t w = 0, dw = 0;
+                    Mask<NW> fr;
+#pragma unroll
+                    for (int j = 0; j < NW; j++) fr.w[j] = 0;
+                    if (e < rp[u + 1]) {
+                        w = ci[e];
+                        Mask<NW> nb;
+#pragma unroll
+                        for (int j = 0; j < NW; j++) nb.w[j] = j == (l >> 6) ? (uint64_t)1 << (l & 63) : 0;
+                        isnew = discover<NW>(Fn, a.mark, w, nb, stamp, &fr);
+                        dw = deg[w];
+                        if (rec_lvl) record_levels<NW>(fr, w, a.w.lvl, W, D + 1);
+                    }
+                    // every arc counts once for search l
+                    const int64_t ds = wave_sum_i64(fr.any() ? dw : 0);
+                    const uint64_t hit = __ballot(fr.any());
+                    if (lane == 0 && hit) {
+                        atomicAdd(&s_red_cnt[l], (int32_t)__popcll(hit));
+                        atomicAdd((unsigned long long*)&s_red_deg[l], (unsigned long long)ds);
+                    }
+                    if (isnew) my_ud += dw;
+                    list_append(isnew, w, dw, nl, stg);
+                }
+            } else if (!bu) {
                 // push, light frontier vertices: a wave takes up to 64 of them
                 // (fewer when they would not go round), one lane each for the
                 // fold and the row, then shares their out-arcs, one per lane
@@ -871,7 +925,7 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
                             c_pre[rk] = pre;
                             c_beg[rk] = eb - pre;
 #pragma unroll
-                            for (int j = 0; j < NW; j++) c_f[rk * NW + j] = f.w[j];
+                            for (int j = 0; j < NW; j++) c_f[j * LSTR + rk] = f.w[j];
                         }
                         __builtin_amdgcn_wave_barrier();
                         int32_t seen = 0;   // rows that start before this pass
@@ -890,7 +944,7 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
                                 Mask<NW> nb;
 #pragma unroll
                                 for (int j = 0; j < NW; j++)
-                                    nb.w[j] = c_f[row * NW + j] & ~(vis[(int64_t)w * NW + j] | Fc[(int64_t)w * NW + j]);
+                                    nb.w[j] = c_f[j * LSTR + row] & ~(vis[(int64_t)w * NW + j] | Fc[(int64_t)w * NW + j]);
                                 if (nb.any()) {
                                     isnew = discover<NW>(Fn, a.mark, w, nb, stamp, &fr);
                                     if (isnew || fr.any()) dw = deg[w];
@@ -974,10 +1028,17 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
                     const bool split = (d.w & PULL_SPLIT) != 0;
                     Mask<NW> acc, miss;
                     bool inF = false;
+                    int32_t dv = 0;
+                    // (the widest batches have no registers left for the early
+                    // load: 11.2 against 10.6 ms on R-MAT of 2^20 vertices;
+                    // narrower ones gain 3 to 5 %)
+                    ItemArcs<NW> ar;
+                    if (NW < 4) ar.load(d.y, d.w & PULL_CNT, a.g.rci, a.g.own);
 #pragma unroll
                     for (int j = 0; j < NW; j++) { acc.w[j] = 0; miss.w[j] = 0; }
                     if (lane < d.z) {
                         uint64_t fw[NW], vn[NW];
+                        dv = deg[w];
 #pragma unroll
                         for (int j = 0; j < NW; j++) fw[j] = Fc[(int64_t)w * NW + j];
 #pragma unroll
@@ -990,19 +1051,20 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
                         if (inF && (!split || (d.w & PULL_FIRST))) {
 #pragma unroll
                             for (int j = 0; j < NW; j++) vis[(int64_t)w * NW + j] = vn[j];
-                            if (!miss.any()) my_dd += deg[w];
+                            if (!miss.any()) my_dd += dv;
                         }
                     }
                     if (!__any(miss.any())) continue;
+                    if (NW == 4) ar.load(d.y, d.w & PULL_CNT, a.g.rci, a.g.own);
 #pragma unroll
                     for (int j = 0; j < NW; j++) {
-                        c_miss[lane * NW + j] = miss.w[j];
-                        c_acc[lane * NW + j] = 0;
+                        c_miss[j * LSTR + lane] = miss.w[j];
+                        c_acc[j * LSTR + lane] = 0;
                     }
                     __builtin_amdgcn_wave_barrier();
-                    pull_item<NW>(d.y, d.w & PULL_CNT, Fc, a.g.rci, a.g.own, c_miss, c_acc, &my_scan);
+                    pull_item<NW>(ar, Fc, c_miss, c_acc, &my_scan);
 #pragma unroll
-                    for (int j = 0; j < NW; j++) acc.w[j] = c_acc[lane * NW + j];
+                    for (int j = 0; j < NW; j++) acc.w[j] = c_acc[j * LSTR + lane] & miss.w[j];
                     __builtin_amdgcn_wave_barrier();
                     bool isnew = false;
                     int32_t dw = 0;
@@ -1016,7 +1078,7 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
                             const Mask<NW> nb = acc;
                             isnew = discover<NW>(Fn, a.mark, w, nb, stamp, &acc);
                         }
-                        if (isnew || acc.any()) dw = deg[w];
+                        if (isnew || acc.any()) dw = dv;
                         if (rec_lvl) record_levels<NW>(acc, w, a.w.lvl, W, D + 1);
                     }
                     tally<NW>(acc, dw, ty);
@@ -1118,25 +1180,38 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
             if (tid == 0 && s_blk[0]) fadd_rlx(&stats[ST_BYTES], s_blk[0] * (int64_t)(4 + 8 * NW));
         }
         // ----------------------------------------------------- batch results
-        // The exact lanes' results go into their request's top k (Alg. 1).
-        // Only the k best of a request's results in this batch can be among
-        // its k best overall, so wave 0 of workgroup 0 ranks them per
-        // request (by farness, then id, then lane), and one thread inserts
-        // the ranks below k best first: an entry that no entry before it
-        // follows is placed after one comparison.  In all-ties mode every
-        // exact result goes in, in lane order, so the tie buffer sees what
-        // the top k refuses.  (The pull's per-wave LDS scratch is free here.)
-        if (blockIdx.x == 0 && tid < 64) {
+        // The exact lanes' results go into their request's top k (Alg. 1),
+        // those not already behind the x of the batch's start.  Only the k
+        // best of a request's results in this batch can be among its k best
+        // overall, so workgroup 0 ranks them per request (by farness, then id,
+        // then lane; one pair of lanes per thread and pass).  One request with
+        // k <= MAXW: the ranked results and the top k are two sorted lists,
+        // and every entry finds its place in the merged one by a binary
+        // search in the other.  (One thread inserting them one by one, a chain
+        // of loads each, took 52 us for a first batch.)  Packs and larger k:
+        // one thread inserts, best first, so that an entry no entry before it
+        // follows is placed after one comparison.  All-ties mode: every
+        // result, in lane order, so the tie buffer sees what the top k
+        // refuses.  (The expansion's LDS scratch is free here.)
+        if (blockIdx.x == 0) {
             int32_t* r_rank = &s_cpre[0][0];
-            int32_t* r_id = &s_cbeg[0][0];
+            int32_t* r_id = r_rank + MAXW;
+            int32_t* r_ord = &s_cbeg[0][0];
+            int32_t* o_id = r_ord + MAXW;
+            int32_t* r_on = &s_stage[0][0];   // takes part in the ranking
             int64_t* r_num = (int64_t*)&s_cmiss[0][0];
-            int64_t* r_den = (int64_t*)&s_cacc[0][0];
-            int64_t ex = 0, cu = 0, md = 0;
-            for (int l = lane; l < nsel; l += 64) {
-                md = s_maxD[l] > md ? s_maxD[l] : md;
+            int64_t* r_den = r_num + MAXW;
+            int64_t* o_S = (int64_t*)&s_cacc[0][0];
+            int64_t* o_R = o_S + MAXW;
+            if (tid < 4) s_blk[tid] = 0;
+            __syncthreads();
+            if (tid < nsel) {
+                const int l = tid;
                 r_rank[l] = -1;
+                r_on[l] = 0;
+                atomicMax((unsigned long long*)&s_blk[2], (unsigned long long)s_maxD[l]);
                 if (s_st[l] == 2) {
-                    ex++;
+                    atomicAdd((unsigned long long*)&s_blk[0], 1ull);
                     r_id[l] = s_v[l] - s_off[l];
                     if (a.bv.harm) {
                         r_num[l] = harm_enc(s_H[l]);
@@ -1145,69 +1220,137 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
                         r_num[l] = s_SD[l];
                         r_den[l] = s_nD[l] <= 1 ? 0 : sq64(s_nD[l] - 1);
                     }
+                    if (!a.no_cut && !lex_after(r_num[l], r_den[l], r_id[l], s_xn[l], s_xd[l], s_xi[l])) {
+                        const DevTopk& tk = a.npreq ? a.preq[s_req[l]].tk : a.tk;
+                        const bool ties = ld_rlx(&tk.st->ties) != 0;
+                        r_rank[l] = ties ? -2 : 0;
+                        r_on[l] = !ties;
+                        atomicAdd((unsigned long long*)&s_blk[3], 1ull);
+                    }
                 } else if (s_st[l] == 3) {
-                    cu++;
+                    atomicAdd((unsigned long long*)&s_blk[1], 1ull);
                 }
             }
-            ex = wave_sum_i64(ex);
-            cu = wave_sum_i64(cu);
-            md = wave_max_i64(md);
-            __builtin_amdgcn_wave_barrier();
-            if (ex > 0 && !a.no_cut) {
-                for (int l = lane; l < nsel; l += 64) {
-                    if (s_st[l] != 2) continue;
-                    const DevTopk& tk = a.npreq ? a.preq[s_req[l]].tk : a.tk;
-                    if (ld_rlx(&tk.st->ties)) {
-                        r_rank[l] = -2;
-                        continue;
-                    }
-                    int32_t rk = 0;
-                    for (int q = 0; q < nsel; q++) {
-                        if (q == l || s_st[q] != 2 || s_req[q] != s_req[l]) continue;
-                        if (lex_after(r_num[l], r_den[l], r_id[l], r_num[q], r_den[q], r_id[q]) ||
-                            (q < l && !lex_after(r_num[q], r_den[q], r_id[q], r_num[l], r_den[l], r_id[l])))
-                            rk++;
-                    }
-                    r_rank[l] = rk < ld_rlx(&tk.st->k) ? rk : -1;
+            __syncthreads();
+            if (s_blk[3] > 0) {
+                for (int i = tid; i < nsel * nsel; i += BB) {
+                    const int l = i / nsel, q = i - l * nsel;
+                    if (q == l || !r_on[l] || !r_on[q] || s_req[q] != s_req[l]) continue;
+                    if (lex_after(r_num[l], r_den[l], r_id[l], r_num[q], r_den[q], r_id[q]) ||
+                        (q < l && !lex_after(r_num[q], r_den[q], r_id[q], r_num[l], r_den[l], r_id[l])))
+                        atomicAdd(&r_rank[l], 1);
                 }
-                __builtin_amdgcn_wave_barrier();
-                // insertion order: by rank, then lane (each request's own
-                // entries arrive in rank order)
-                int32_t* r_ord = &s_stage[0][0];
-                int32_t nins = 0;
-                for (int l = lane; l < nsel; l += 64) {
-                    if (r_rank[l] < 0) continue;
-                    int32_t g = 0;
-                    for (int q = 0; q < nsel; q++)
-                        g += r_rank[q] >= 0 && (r_rank[q] < r_rank[l] || (r_rank[q] == r_rank[l] && q < l));
-                    r_ord[g] = l;
-                    nins++;
-                }
-                nins = wave_sum_i32(nins);
-                __builtin_amdgcn_wave_barrier();
-                if (lane == 0) {
-                    for (int32_t g = 0; g < nins; g++) {
-                        const int l = r_ord[g];
-                        const DevTopk& tk = a.npreq ? a.preq[s_req[l]].tk : a.tk;
-                        topk_insert(tk.st, tk.ring, tk.S, tk.R, tk.I, r_num[l], a.bv.harm ? 2 : s_nD[l], r_id[l]);
+                __syncthreads();
+                const int32_t k0 = a.npreq ? 0 : ld_rlx(&a.tk.st->k);
+                const bool merge = !a.npreq && k0 <= MAXW && ld_rlx(&a.tk.st->ties) == 0;
+                if (merge) {
+                    const int32_t cnt0 = ld_rlx(&a.tk.st->cnt);
+                    const int32_t m = s_blk[3] < k0 ? (int32_t)s_blk[3] : k0;
+                    if (tid < nsel && r_on[tid] && r_rank[tid] < k0) r_ord[r_rank[tid]] = tid;
+                    if (tid < cnt0) {
+                        o_S[tid] = ld_rlx(&a.tk.S[tid]);
+                        o_R[tid] = ld_rlx(&a.tk.R[tid]);
+                        o_id[tid] = ld_rlx(&a.tk.I[tid]);
                     }
-                    // all-ties mode: every exact result, in lane order
-                    for (int l = 0; l < nsel; l++) {
-                        if (r_rank[l] != -2) continue;
+                    __syncthreads();
+                    // places: of a new entry its rank and the old entries it
+                    // follows, of an old one its place and the new ones it follows
+                    auto old_den = [&](int i) { return o_R[i] <= 1 ? (int64_t)0 : sq64(o_R[i] - 1); };
+                    auto follows = [&](int l, int i) {   // new entry of lane l, old entry i
+                        return lex_after(r_num[l], r_den[l], r_id[l], o_S[i], old_den(i), o_id[i]);
+                    };
+                    int32_t at = k0, id = 0;
+                    int64_t S = 0, R = 0;
+                    if (tid < m) {
+                        const int l = r_ord[tid];
+                        int32_t lo = 0, hi = cnt0;
+                        while (lo < hi) {
+                            const int32_t mid = (lo + hi) >> 1;
+                            if (follows(l, mid)) lo = mid + 1; else hi = mid;
+                        }
+                        at = tid + lo;
+                        S = r_num[l];
+                        R = a.bv.harm ? 2 : s_nD[l];
+                        id = r_id[l];
+                    }
+                    if (at < k0) {
+                        st_rlx(&a.tk.S[at], S);
+                        st_rlx(&a.tk.R[at], R);
+                        st_rlx(&a.tk.I[at], id);
+                        if (at == k0 - 1) { s_x0[0] = S; s_x0[1] = R; s_x0[2] = id; }
+                    }
+                    at = k0;
+                    if (tid < cnt0) {
+                        int32_t lo = 0, hi = m;
+                        while (lo < hi) {
+                            const int32_t mid = (lo + hi) >> 1;
+                            if (!follows(r_ord[mid], tid)) lo = mid + 1; else hi = mid;
+                        }
+                        at = tid + lo;
+                    }
+                    if (at < k0) {
+                        st_rlx(&a.tk.S[at], o_S[tid]);
+                        st_rlx(&a.tk.R[at], o_R[tid]);
+                        st_rlx(&a.tk.I[at], o_id[tid]);
+                        if (at == k0 - 1) { s_x0[0] = o_S[tid]; s_x0[1] = o_R[tid]; s_x0[2] = o_id[tid]; }
+                    }
+                    __syncthreads();
+                    if (tid == 0) {
+                        TopkState* st = a.tk.st;
+                        const int32_t cnt = cnt0 + m < k0 ? cnt0 + m : k0;
+                        st_rlx(&st->cnt, cnt);
+                        fadd_rlx(&st->n_inserts, (int64_t)m);
+                        if (cnt == k0) {
+                            const int64_t q = ld_rlx(&st->seq) + 1;
+                            XRec* rc = a.tk.ring + (q % TKC_XRING);
+                            st_rlx(&rc->S, s_x0[0]);
+                            st_rlx(&rc->r, s_x0[1]);
+                            st_rlx(&rc->id, s_x0[2]);
+                            st_rel(&st->seq, q);
+                        }
+                    }
+                } else if (tid < 64) {
+                    // insertion order: by rank, then lane (each request's own
+                    // entries arrive in rank order)
+                    int32_t nins = 0;
+                    for (int l = lane; l < nsel; l += 64) {
                         const DevTopk& tk = a.npreq ? a.preq[s_req[l]].tk : a.tk;
-                        topk_insert(tk.st, tk.ring, tk.S, tk.R, tk.I, r_num[l], a.bv.harm ? 2 : s_nD[l], r_id[l]);
+                        if (r_on[l] && r_rank[l] >= ld_rlx(&tk.st->k)) r_rank[l] = -1;
+                    }
+                    __builtin_amdgcn_wave_barrier();
+                    for (int l = lane; l < nsel; l += 64) {
+                        if (r_rank[l] < 0) continue;
+                        int32_t g = 0;
+                        for (int q = 0; q < nsel; q++)
+                            g += r_rank[q] >= 0 && (r_rank[q] < r_rank[l] || (r_rank[q] == r_rank[l] && q < l));
+                        r_ord[g] = l;
+                        nins++;
+                    }
+                    nins = wave_sum_i32(nins);
+                    __builtin_amdgcn_wave_barrier();
+                    if (lane == 0) {
+                        for (int32_t g = 0; g < nins; g++) {
+                            const int l = r_ord[g];
+                            const DevTopk& tk = a.npreq ? a.preq[s_req[l]].tk : a.tk;
+                            topk_insert(tk.st, tk.ring, tk.S, tk.R, tk.I, r_num[l], a.bv.harm ? 2 : s_nD[l], r_id[l]);
+                        }
+                        for (int l = 0; l < nsel; l++) {
+                            if (r_rank[l] != -2) continue;
+                            const DevTopk& tk = a.npreq ? a.preq[s_req[l]].tk : a.tk;
+                            topk_insert(tk.st, tk.ring, tk.S, tk.R, tk.I, r_num[l], a.bv.harm ? 2 : s_nD[l], r_id[l]);
+                        }
                     }
                 }
             }
-            if (lane == 0) {
+            if (tid == 0) {
                 // the until_x decision, taken once so every workgroup makes it alike
                 if (a.until_x) ctr[C_XDONE] = ld_acq(&a.tk.st->seq) >= 0 ? 1 : 0;
                 fadd_rlx(&stats[ST_STARTED], (int64_t)nsel);
-                fadd_rlx(&stats[ST_EXACT], ex);
-                fadd_rlx(&stats[ST_CUT], cu);
+                fadd_rlx(&stats[ST_EXACT], s_blk[0]);
+                fadd_rlx(&stats[ST_CUT], s_blk[1]);
                 fadd_rlx(&stats[ST_MVIS], mvis);
                 fadd_rlx(&stats[ST_BYTES], bytes);
-                __hip_atomic_fetch_max(&stats[ST_MAXLEVEL], md, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_fetch_max(&stats[ST_MAXLEVEL], s_blk[2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
         }
         if (a.no_cut && blockIdx.x == 0 && tid < nsel) {
