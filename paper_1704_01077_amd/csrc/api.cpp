@@ -590,7 +590,7 @@ WsShape tkc_shape_for(const EngineTuning& t, tkc_graph* g, int32_t k, bool lb) {
 }
 
 WsShape tkc_shape_ring(WsShape sh, tkc_graph* g) {
-    if (sh.lb) sh.ring = tkc_ring_blocks(g->view());
+    sh.ring = tkc_ring_blocks(g->view());
     return sh;
 }
 
@@ -958,9 +958,9 @@ int tkc_run_query(tkc_ctx* c, tkc_graph* g, int32_t k, int32_t variant, int32_t 
     {
         WsShape sh = tkc_shape_for(c->tune, g, k, lb);
         sh.ties = ties;
-        // complete searches of a low-degree graph: the ring engine, unless its
-        // buffers do not fit
-        const WsShape rs = lb && !harm && mode != TKC_PLAIN && c->ring_ok ? tkc_shape_ring(sh, g) : sh;
+        // low-degree undirected graphs: the ring engine, unless its buffers do
+        // not fit
+        const WsShape rs = !harm && mode != TKC_PLAIN && c->ring_ok ? tkc_shape_ring(sh, g) : sh;
         rc = tkc_ws_reserve(c, ws, rs);
         ring = rc == TKC_OK ? rs.ring : 0;
         if (rc == TKC_ENOMEM && rs.ring) rc = tkc_ws_reserve(c, ws, sh);
@@ -1005,7 +1005,7 @@ int tkc_run_query(tkc_ctx* c, tkc_graph* g, int32_t k, int32_t variant, int32_t 
     double ms_eng[3] = {0, 0, 0};
     int32_t nl_eng[3] = {0, 0, 0};
     int grid = 0;
-    // the per-workgroup engine has no level-based path
+    // the hybrid's per-workgroup engine has no level-based path
     if (lb && mode == TKC_HYBRID) mode = TKC_BATCHED;
     if (mode == TKC_PLAIN) {
         EngineTimer tm(c, &ms_eng[0], &nl_eng[0]);
@@ -1014,7 +1014,7 @@ int tkc_run_query(tkc_ctx* c, tkc_graph* g, int32_t k, int32_t variant, int32_t 
             return tkc_fail(TKC_EDEVICE, "plain engine launch failed: %s", hipGetErrorString(hipGetLastError()));
         if ((rc = tm.done(readback))) return rc;
         rb_ready = true;
-    } else if (mode == TKC_BATCHED) {
+    } else if (mode == TKC_BATCHED || ring) {
         trace_reset(c);
         // launches of slice_batches batches each when that is set (the
         // cursor, stop flag, top k and bounds live in device memory between

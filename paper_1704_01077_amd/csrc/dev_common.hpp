@@ -273,6 +273,11 @@ TKC_DEV uint64_t wave_transpose64(uint64_t x) {
 #undef TKC_TSTAGE
     return (uint64_t)lo | ((uint64_t)hi << 32);
 }
+TKC_DEV int64_t shfl64(int64_t v, int src) {
+    const int32_t lo = __shfl((int32_t)(v & 0xffffffff), src, 64);
+    const int32_t hi = __shfl((int32_t)(v >> 32), src, 64);
+    return ((int64_t)hi << 32) | (uint32_t)lo;
+}
 // exclusive prefix of a 0/1 predicate within the wave, plus the wave total
 TKC_DEV int wave_rank(bool pred, int* total) {
     uint64_t m = __ballot(pred);
@@ -441,6 +446,89 @@ TKC_DEV void topk_insert(TopkState* st, XRec* ring, int64_t* tS, int64_t* tR, in
         __builtin_amdgcn_s_sleep(2);
     topk_insert_locked(st, ring, tS, tR, tI, S, r, id);
     topk_unlock(st);
+}
+
+// topk_insert_locked by the 64 lanes of a wave (the same arguments in all):
+// entries are compared and moved 64 at a time, where one thread walks them in
+// a chain of coherent loads (100 entries: 100 us and more under the lock)
+TKC_DEV void topk_insert_wave_locked(TopkState* st, XRec* ring, int64_t* tS, int64_t* tR, int32_t* tI,
+                                     int64_t S, int64_t r, int32_t id) {
+    const int lane = lane_id();
+    const int32_t k = ld_rlx(&st->k), cnt = ld_rlx(&st->cnt), ties = ld_rlx(&st->ties);
+    const int64_t den = r <= 1 ? 0 : sq64(r - 1);
+    int32_t p = 0;   // entries that precede (S, r, id)
+    for (int32_t b = 0; b < cnt; b += 64) {
+        const int32_t i = b + lane;
+        bool prec = false;
+        if (i < cnt) {
+            const int64_t eS = ld_rlx(&tS[i]), eR = ld_rlx(&tR[i]);
+            const int32_t eI = ld_rlx(&tI[i]);
+            prec = !lex_after(eS, eR <= 1 ? 0 : sq64(eR - 1), eI, S, den, id);
+        }
+        p += __popcll(__ballot(prec));
+    }
+    if (ties && lane == 0) {
+        if (p >= k) tie_keep(st, S, r, id);
+        else if (cnt == k) tie_keep(st, ld_rlx(&tS[k - 1]), ld_rlx(&tR[k - 1]), ld_rlx(&tI[k - 1]));
+    }
+    __builtin_amdgcn_wave_barrier();
+    if (p < k) {
+        const int32_t last = cnt < k ? cnt : k - 1;   // [p, last) moves up by one
+        int64_t kS = S, kR = r;                       // what ends at place `last`
+        int32_t kI = id;
+        for (int32_t top = last; top > p;) {
+            const int32_t lo = top - 64 > p ? top - 64 : p;
+            const int32_t i = lo + lane;
+            int64_t eS = 0, eR = 0;
+            int32_t eI = 0;
+            if (i < top) {
+                eS = ld_rlx(&tS[i]);
+                eR = ld_rlx(&tR[i]);
+                eI = ld_rlx(&tI[i]);
+            }
+            if (top == last) {
+                const int src = last - 1 - lo;
+                kS = shfl64(eS, src);
+                kR = shfl64(eR, src);
+                kI = __shfl(eI, src, 64);
+            }
+            if (i < top) {
+                st_rlx(&tS[i + 1], eS);
+                st_rlx(&tR[i + 1], eR);
+                st_rlx(&tI[i + 1], eI);
+            }
+            top = lo;
+        }
+        if (lane == 0) {
+            st_rlx(&tS[p], S);
+            st_rlx(&tR[p], r);
+            st_rlx(&tI[p], id);
+            if (cnt < k) st_rlx(&st->cnt, cnt + 1);
+            if (last == k - 1) {   // the top k is full
+                const int64_t q = ld_rlx(&st->seq) + 1;
+                XRec* rc = ring + (q % TKC_XRING);
+                st_rlx(&rc->S, kS);
+                st_rlx(&rc->r, kR);
+                st_rlx(&rc->id, ties ? (int64_t)0x7fffffff : (int64_t)kI);
+                st_rel(&st->seq, q);
+            }
+        }
+    }
+    if (lane == 0) fadd_rlx(&st->n_inserts, (int64_t)1);
+    __builtin_amdgcn_wave_barrier();
+}
+// with the lock, called by the 64 lanes of a wave
+TKC_DEV void topk_insert_wave(TopkState* st, XRec* ring, int64_t* tS, int64_t* tR, int32_t* tI,
+                              int64_t S, int64_t r, int32_t id) {
+    int32_t got = 0;
+    while (!got) {
+        if (lane_id() == 0) got = topk_try_lock(st) ? 1 : 0;
+        got = __shfl(got, 0, 64);
+        if (!got) __builtin_amdgcn_s_sleep(2);
+    }
+    topk_insert_wave_locked(st, ring, tS, tR, tI, S, r, id);
+    if (lane_id() == 0) topk_unlock(st);
+    __builtin_amdgcn_wave_barrier();
 }
 
 // ----------------------------------------------------- BFSCut bound (Sect. 6)

@@ -267,8 +267,9 @@ int tkc_launch_swarm(const DevGraph& g, DevReach rc, OrderView ov, BoundsView bv
                      hipStream_t s);
 int tkc_swarm_max_blocks(int block);
 
-// k_ring.hip: complete searches with level-based updates, one per workgroup,
-// visited set in LDS (undirected graphs of low degree).
+// k_ring.hip: one search per workgroup, visited set in LDS (undirected graphs
+// of low degree): cut ones (lb_mode 0), complete ones with level-based updates
+// (1), or both (2).
 struct RingWork {
     int32_t* queue;      // nblocks * RING_QSTRIDE(n), 16-byte aligned
     int32_t* levoff;     // nblocks * lcap: first queue position of each level

@@ -193,7 +193,7 @@ bool tkc_prep_cached(tkc_ctx* c, tkc_graph* g, bool nb, int32_t* rounds);
 // build that cache from c's workspace after a query computed it
 int tkc_prep_store(tkc_ctx* c, tkc_graph* g, bool nb, int32_t rounds);
 WsShape tkc_shape_for(const EngineTuning& t, tkc_graph* g, int32_t k, bool lb);
-// the same with the ring engine's buffers where it applies to g (lb queries)
+// the same with the ring engine's buffers where it applies to g
 WsShape tkc_shape_ring(WsShape sh, tkc_graph* g);
 // the knobs a TKC_MODE_AUTO query on g runs with, given the context's own
 EngineTuning tkc_effective_tuning(const EngineTuning& ctx_tune, tkc_graph* g);

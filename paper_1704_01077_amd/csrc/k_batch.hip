@@ -86,11 +86,6 @@ struct BatchArgs {
     int32_t npreq;
 };
 
-TKC_DEV int64_t shfl64b(int64_t v, int src) {
-    int32_t lo = __shfl((int32_t)(v & 0xffffffff), src, 64);
-    int32_t hi = __shfl((int32_t)(v >> 32), src, 64);
-    return ((int64_t)hi << 32) | (uint32_t)lo;
-}
 TKC_DEV uint64_t below_mask() {
     int l = lane_id();
     return l == 0 ? 0ull : (~0ull >> (64 - l));
@@ -190,7 +185,7 @@ TKC_DEV void list_append(bool isnew, int32_t w, int32_t dw, const NextLists& L, 
                 b = fadd_rlx(&L.tails[1], (int64_t)st.nh);
                 c0 = fadd_rlx(L.ctail, (int64_t)nck);
             }
-            stage_put_heavy(st, L, shfl64b(b, 0), shfl64b(c0, 0));
+            stage_put_heavy(st, L, shfl64(b, 0), shfl64(c0, 0));
             __builtin_amdgcn_wave_barrier();
             st.nh = 0;
         }
@@ -202,7 +197,7 @@ TKC_DEV void list_append(bool isnew, int32_t w, int32_t dw, const NextLists& L, 
         if (st.n + c > STAGE) {
             int64_t b = 0;
             if (lane_id() == 0) b = fadd_rlx(&L.tails[0], (int64_t)st.n);
-            stage_put(st, L.light, shfl64b(b, 0));
+            stage_put(st, L.light, shfl64(b, 0));
             __builtin_amdgcn_wave_barrier();
             st.n = 0;
         }
@@ -1189,8 +1184,7 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
         // and every entry finds its place in the merged one by a binary
         // search in the other.  (One thread inserting them one by one, a chain
         // of loads each, took 52 us for a first batch.)  Packs and larger k:
-        // one thread inserts, best first, so that an entry no entry before it
-        // follows is placed after one comparison.  All-ties mode: every
+        // one wave inserts, best first.  All-ties mode: every
         // result, in lane order, so the tie buffer sees what the top k
         // refuses.  (The expansion's LDS scratch is free here.)
         if (blockIdx.x == 0) {
@@ -1328,17 +1322,15 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
                     }
                     nins = wave_sum_i32(nins);
                     __builtin_amdgcn_wave_barrier();
-                    if (lane == 0) {
-                        for (int32_t g = 0; g < nins; g++) {
-                            const int l = r_ord[g];
-                            const DevTopk& tk = a.npreq ? a.preq[s_req[l]].tk : a.tk;
-                            topk_insert(tk.st, tk.ring, tk.S, tk.R, tk.I, r_num[l], a.bv.harm ? 2 : s_nD[l], r_id[l]);
-                        }
-                        for (int l = 0; l < nsel; l++) {
-                            if (r_rank[l] != -2) continue;
-                            const DevTopk& tk = a.npreq ? a.preq[s_req[l]].tk : a.tk;
-                            topk_insert(tk.st, tk.ring, tk.S, tk.R, tk.I, r_num[l], a.bv.harm ? 2 : s_nD[l], r_id[l]);
-                        }
+                    for (int32_t g = 0; g < nins; g++) {
+                        const int l = r_ord[g];
+                        const DevTopk& tk = a.npreq ? a.preq[s_req[l]].tk : a.tk;
+                        topk_insert_wave(tk.st, tk.ring, tk.S, tk.R, tk.I, r_num[l], a.bv.harm ? 2 : s_nD[l], r_id[l]);
+                    }
+                    for (int l = 0; l < nsel; l++) {
+                        if (r_rank[l] != -2) continue;
+                        const DevTopk& tk = a.npreq ? a.preq[s_req[l]].tk : a.tk;
+                        topk_insert_wave(tk.st, tk.ring, tk.S, tk.R, tk.I, r_num[l], a.bv.harm ? 2 : s_nD[l], r_id[l]);
                     }
                 }
             }

@@ -38,11 +38,6 @@ struct PlainArgs {
     uint32_t* bar;
 };
 
-TKC_DEV int64_t shfl64(int64_t v, int src) {
-    int32_t lo = __shfl((int32_t)(v & 0xffffffff), src, 64);
-    int32_t hi = __shfl((int32_t)(v >> 32), src, 64);
-    return ((int64_t)hi << 32) | (uint32_t)lo;
-}
 TKC_DEV uint64_t lanes_below() {
     int l = lane_id();
     return l == 0 ? 0ull : (~0ull >> (64 - l));

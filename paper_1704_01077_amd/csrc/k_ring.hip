@@ -1,6 +1,6 @@
-// Ring engine: complete searches for the level-based updates (Sect. 7) on
-// graphs of low degree and high diameter (street networks), one search per
-// workgroup with its visited set in LDS.
+// Ring engine: searches on undirected graphs of low degree (street networks:
+// high diameter), one per workgroup with its visited set in LDS; complete
+// ones for the level-based updates (Sect. 7), cut ones for BFSCut (Sect. 6).
 //
 // Such a search is a thin ring that moves out over hundreds of levels.  The
 // batched engine pays a grid barrier and several trips to memory for every
@@ -83,10 +83,9 @@ __global__ void k_ring_end(int32_t n, const int64_t* __restrict__ omega, const i
 // Marks the targets w (negative: none) of one pass in the LDS bitmap, each
 // new one by exactly one thread, and appends those to the queue at out[...]
 // and to the LDS copy of the next level (as far as that reaches), in the
-// order of one LDS counter.  DEG: also sums the new vertices' degrees.
-template <bool DEG>
-TKC_DEV void ring_visit(const int32_t (&w)[4], const int32_t* __restrict__ deg, uint32_t* bits, int32_t spare,
-                        int32_t* out, int32_t* front, int32_t* tail, uint64_t below, int64_t& my_deg) {
+// order of one LDS counter.
+TKC_DEV void ring_visit(const int32_t (&w)[4], uint32_t* bits, int32_t spare, int32_t* out, int32_t* front,
+                        int32_t* tail, uint64_t below) {
     // the four words are read together (no target: the spare word, which is
     // read but never marked: lanes that mark one word take turns)
     uint32_t word[4];
@@ -123,7 +122,6 @@ TKC_DEV void ring_visit(const int32_t (&w)[4], const int32_t* __restrict__ deg, 
             const int32_t i = at + __popcll(m[j] & below);
             out[i] = w[j];
             front[i < RING_FRONT ? i : RING_FRONT] = w[j];   // the slot behind takes the rest
-            if (DEG) my_deg += deg[w[j]];
         }
         at += __popcll(m[j]);
     }
@@ -135,10 +133,9 @@ TKC_DEV void ring_visit(const int32_t (&w)[4], const int32_t* __restrict__ deg, 
 // queue.  (Two or four vertices per thread and pass, or four threads per
 // vertex, measured the same: the waves of a compute unit hide each other's
 // latency.)
-template <int T, bool DEG>
+template <int T>
 TKC_DEV void ring_expand(const RingArgs& a, uint32_t* bits, const int32_t* cur, int32_t items, int32_t base,
-                         int32_t* out, int32_t* front, int32_t* tail, uint64_t below, int64_t& my_deg,
-                         int64_t& arcs) {
+                         int32_t* out, int32_t* front, int32_t* tail, uint64_t below, int64_t& arcs) {
     const int32_t i = base + (int32_t)threadIdx.x;
     const int32_t u = i < items ? cur[i] : -1;
     int4 r{-1, -1, -1, -1};
@@ -151,12 +148,12 @@ TKC_DEV void ring_expand(const RingArgs& a, uint32_t* bits, const int32_t* cur, 
         w[3] = -1;
     }
     arcs += (w[0] >= 0) + (w[1] >= 0) + (w[2] >= 0) + (w[3] >= 0) + (e - b);
-    ring_visit<DEG>(w, a.g.deg, bits, a.words, out, front, tail, below, my_deg);
+    ring_visit(w, bits, a.words, out, front, tail, below);
     while (__any(b < e)) {
 #pragma unroll
         for (int j = 0; j < 4; j++) w[j] = b + j < e ? a.g.ci[b + j] : -1;
         b += 4;
-        ring_visit<DEG>(w, a.g.deg, bits, a.words, out, front, tail, below, my_deg);
+        ring_visit(w, bits, a.words, out, front, tail, below);
     }
 }
 
@@ -173,7 +170,8 @@ __global__ void __launch_bounds__(T) k_ring(RingArgs a) {
     __shared__ int32_t s_off[RING_LEVELS];
     __shared__ int64_t s_w64[T / 64];
     __shared__ int64_t s_x[3];
-    __shared__ int64_t s_deg[3];
+    __shared__ int64_t s_lim[2];
+    __shared__ int32_t s_limid[2];
     __shared__ int64_t s_pS[RING_PEND], s_pR[RING_PEND], s_thr;
     __shared__ int32_t s_pI[RING_PEND];
     __shared__ int32_t s_pos, s_dec, s_cur;
@@ -201,40 +199,68 @@ __global__ void __launch_bounds__(T) k_ring(RingArgs a) {
         if (lex_after(num, om <= 1 ? 0 : sq64(om - 1), TKC_OID(a.g, v), x.num, x.den, x.id)) return 2;
         return om <= 1 ? 3 : 0;
     };
-    // Results wait in LDS until the top k's lock is free (thread 0): hundreds
+    // Results wait in LDS until the top k's lock is free (first wave, which
+    // also places them: one lane moving a list of 100 entries made 32 requests
+    // on small street networks take 30 ms of 276): hundreds
     // of searches end at about the same time, and a workgroup that spun for
     // its turn would hold its compute unit and slow the lock's owner.  What
     // the top k would refuse by now leaves first (in all-ties mode x carries
     // the largest id, so that cannot tie with the k-th).
     int32_t npend = 0;
-    auto offer = [&](bool wait) {
+    auto offer = [&](bool wait) {   // called by the first wave's 64 lanes
         while (npend > 0) {
             const XVal x = read_x_poll(a.tk.st, a.tk.ring);
-            int32_t m = 0;
-            for (int32_t i = 0; i < npend; i++) {
-                if (lex_after(s_pS[i], s_pR[i] <= 1 ? 0 : sq64(s_pR[i] - 1), s_pI[i], x.num, x.den, x.id)) continue;
-                s_pS[m] = s_pS[i];
-                s_pR[m] = s_pR[i];
-                s_pI[m++] = s_pI[i];
+            const int64_t pS = s_pS[lane & (RING_PEND - 1)], pR = s_pR[lane & (RING_PEND - 1)];
+            const int32_t pI = s_pI[lane & (RING_PEND - 1)];
+            const bool stay = lane < npend && !lex_after(pS, pR <= 1 ? 0 : sq64(pR - 1), pI, x.num, x.den, x.id);
+            uint64_t m = __ballot(stay);
+            if (m) {
+                int32_t got = 0;
+                if (lane == 0) got = topk_try_lock(a.tk.st) ? 1 : 0;
+                if (__shfl(got, 0, 64)) {
+                    for (; m; m &= m - 1) {
+                        const int l = __ffsll((long long)m) - 1;
+                        topk_insert_wave_locked(a.tk.st, a.tk.ring, a.tk.S, a.tk.R, a.tk.I, shfl64(pS, l),
+                                                shfl64(pR, l), __shfl(pI, l, 64));
+                    }
+                    if (lane == 0) topk_unlock(a.tk.st);
+                } else {
+                    __builtin_amdgcn_wave_barrier();
+                    if (stay) {
+                        const int32_t i = __popcll(m & below);
+                        s_pS[i] = pS;
+                        s_pR[i] = pR;
+                        s_pI[i] = pI;
+                    }
+                    __builtin_amdgcn_wave_barrier();
+                }
             }
-            npend = m;
-            if (m == 0) return;
-            if (topk_try_lock(a.tk.st)) {
-                for (int32_t i = 0; i < m; i++)
-                    topk_insert_locked(a.tk.st, a.tk.ring, a.tk.S, a.tk.R, a.tk.I, s_pS[i], s_pR[i], s_pI[i]);
-                topk_unlock(a.tk.st);
-                npend = 0;
-                return;
-            }
+            npend = __popcll(m);
             if (!wait) return;
-            __builtin_amdgcn_s_sleep(64);
+            if (npend) __builtin_amdgcn_s_sleep(64);
         }
     };
     auto pend = [&](int64_t S, int64_t r, int32_t id) {
-        s_pS[npend] = S;
-        s_pR[npend] = r;
-        s_pI[npend++] = id;
+        if (lane == 0) {
+            s_pS[npend] = S;
+            s_pR[npend] = r;
+            s_pI[npend] = id;
+        }
+        __builtin_amdgcn_wave_barrier();
+        npend++;
         offer(npend == RING_PEND);
+    };
+    // the numerator over bden up to which a value does not pass x (exact when
+    // x has that denominator: *id then breaks a tie, else none is cut on one)
+    auto x_limit = [&](const XVal& x, int64_t bden, int32_t* id) -> int64_t {
+        *id = 0x7fffffff;
+        if (x.den == 0) return INT64_MAX - HEAVY_DEG;
+        if (x.den == bden) {
+            *id = x.id;
+            return x.num;
+        }
+        const double t = (double)x.num * ((double)bden / (double)x.den) * (1.0 + 1e-9) + 2.0;
+        return t < 9e18 ? (int64_t)t : INT64_MAX - HEAVY_DEG;
     };
 
     for (;;) {
@@ -243,9 +269,9 @@ __global__ void __launch_bounds__(T) k_ring(RingArgs a) {
         // past the skipped ones and the first that is not (compare-and-swap,
         // so no workgroup holds positions it is not working on; when another
         // was faster, the judged window serves for the next try)
+        if (wv == 0) offer(false);
         if (tid == 0) {
             int32_t p = 0, d = 4;   // 4: no more work for this workgroup
-            offer(false);
             if (ld_rlx(a.w.stop) == 0 && (a.limit == 0 || ld_rlx(a.w.started) < a.limit)) {
                 p = fadd_rlx(a.w.cursor, 1);
                 if (p < count) {
@@ -312,13 +338,14 @@ __global__ void __launch_bounds__(T) k_ring(RingArgs a) {
             if (tid == 0) {
                 st_started++;
                 st_exact++;
-                pend(0, 1, TKC_OID(a.g, v));
             }
+            if (wv == 0) pend(0, 1, TKC_OID(a.g, v));
             __syncthreads();
             continue;
         }
         // ---- the search
-        const int64_t av = a.rc.alpha[v], omv = a.rc.omega[v];
+        const int64_t rv = a.rc.omega[v], bden = sq64(rv - 1);   // undirected: r(v) is known
+        const int32_t vid = TKC_OID(a.g, v);
         if (tid == 0) {
             if (a.limit) fadd_rlx(a.w.started, 1);
             s_bits[v >> 5] |= 1u << (v & 31);
@@ -329,58 +356,48 @@ __global__ void __launch_bounds__(T) k_ring(RingArgs a) {
             s_tail[0] = 0;
             s_tail[1] = 0;
             s_tail[2] = 0;
-            s_deg[0] = 0;
-            s_deg[1] = 0;
-            s_deg[2] = 0;
         }
         __syncthreads();
         // level D holds q[ls, le); level D + 1 is appended at q[le ...) through
         // the counter of parity D % 3, which is cleared one level ahead
         int32_t D = 0, ls = 0, le = 1;
-        int64_t SD = 0, U = deg[v];
+        int64_t SD = 0;
         bool cut = false;
-        const bool shallow_cuts = a.lb_mode == 2;
         for (;;) {
             const int c3 = D % 3;
-            if (shallow_cuts && D <= CUTLB_DEPTH) {
-                if (tid == 0) {
-                    const XVal x = read_x_poll(a.tk.st, a.tk.ring);
-                    int64_t bn, bd;
-                    cut_bound(SD, le, U, D, av, omv, &bn, &bd);
-                    s_dec = lex_after(bn, bd, TKC_OID(a.g, v), x.num, x.den, x.id) ? 1 : 0;
-                }
-                __syncthreads();
-                if (s_dec) { cut = true; break; }
+            // BFSCut with the levels up to D known exactly: every other vertex
+            // is at least D + 1 away (at least what Lemma 6.1 gives at level
+            // D - 1, whose bound on the size of level D is now its size).  x
+            // is polled by the last wave at every fourth level, into the slot
+            // that is not read until the next poll
+            const bool cuts = a.lb_mode == 0 || (a.lb_mode == 2 && D <= CUTLB_DEPTH);
+            if (cuts && D > 0) {
+                const int sl = ((D - 1) >> 2) & 1;
+                const int64_t bound = SD + (int64_t)(D + 1) * (rv - le);
+                if (bound > s_lim[sl] || (bound == s_lim[sl] && vid > s_limid[sl])) { cut = true; break; }
+            }
+            if (cuts && (D & 3) == 0 && tid == T - 64) {
+                int32_t id;
+                s_lim[(D >> 2) & 1] = x_limit(read_x_poll(a.tk.st, a.tk.ring), bden, &id);
+                s_limid[(D >> 2) & 1] = id;
             }
             if (tid == 0) {
                 const int nx = D % 3 == 2 ? 0 : c3 + 1;
                 s_tail[nx] = 0;
-                s_deg[nx] = 0;
                 if (D + 1 < a.w.lcap) off[D + 1] = le;
                 if (D + 1 < RING_LEVELS) s_off[D + 1] = le;
             }
             const int32_t items = le - ls;
             int32_t* front = s_front[(D + 1) & 1];
-            int64_t my_deg = 0;
-            if (shallow_cuts && D <= CUTLB_DEPTH) {
-                const int32_t* cur = items <= RING_FRONT ? s_front[D & 1] : q + ls;
+            if (items <= RING_FRONT) {
                 for (int32_t b = 0; b < items; b += T)
-                    ring_expand<T, true>(a, s_bits, cur, items, b, q + le, front, &s_tail[c3], below, my_deg,
-                                            st_mvis);
-                my_deg = wave_sum_i64(my_deg);
-                if (lane == 0 && my_deg) atomicAdd((unsigned long long*)&s_deg[c3], (unsigned long long)my_deg);
-            } else if (items <= RING_FRONT) {
-                for (int32_t b = 0; b < items; b += T)
-                    ring_expand<T, false>(a, s_bits, s_front[D & 1], items, b, q + le, front, &s_tail[c3], below,
-                                             my_deg, st_mvis);
+                    ring_expand<T>(a, s_bits, s_front[D & 1], items, b, q + le, front, &s_tail[c3], below, st_mvis);
             } else {
                 for (int32_t b = 0; b < items; b += T)
-                    ring_expand<T, false>(a, s_bits, q + ls, items, b, q + le, front, &s_tail[c3], below, my_deg,
-                                               st_mvis);
+                    ring_expand<T>(a, s_bits, q + ls, items, b, q + le, front, &s_tail[c3], below, st_mvis);
             }
             lds_barrier();
             const int32_t cnt = s_tail[c3];
-            if (shallow_cuts && D <= CUTLB_DEPTH) U = s_deg[c3] - cnt;
             D++;
             SD += (int64_t)D * cnt;
             ls = le;
@@ -399,32 +416,24 @@ __global__ void __launch_bounds__(T) k_ring(RingArgs a) {
             const int64_t md = cut ? D : maxD;
             if (md > st_maxl) st_maxl = md;
             st_bytes += 12 * (int64_t)le;
-            if (cut) {
-                st_cut++;
-            } else {
-                st_exact++;
-                pend(SD, r, TKC_OID(a.g, v));
-                // a bound above thr is above x: no later search need raise it
-                const XVal x = read_x_poll(a.tk.st, a.tk.ring);
-                const int64_t bden = sq64((int64_t)r - 1);
-                int64_t thr = INT64_MAX - HEAVY_DEG;
-                if (x.den == bden) {
-                    thr = x.num;
-                } else if (x.den != 0) {
-                    const double t = (double)x.num * ((double)bden / (double)x.den) * (1.0 + 1e-9) + 2.0;
-                    if (t < 9e18) thr = (int64_t)t;
-                }
-                s_thr = thr;
-            }
+            if (cut) st_cut++;
+            else st_exact++;
+        }
+        if (wv == 0 && !cut) {
+            pend(SD, r, vid);
+            // a bound above the limit is above x: no later search need raise it
+            int32_t id;
+            const int64_t lim = a.lb_mode ? x_limit(read_x_poll(a.tk.st, a.tk.ring), bden, &id) : 0;
+            if (lane == 0) s_thr = lim;
         }
         // the bitmap has done its work: it takes the bits of the vertices whose
         // bound needs no update, all of one pass's tests then stay in LDS
-        const bool update = !cut && maxD >= 1 && D + 1 < a.w.lcap;
+        const bool update = a.lb_mode != 0 && !cut && maxD >= 1 && D + 1 < a.w.lcap;
         for (int32_t i = tid; i < a.words; i += T) s_bits[i] = update ? ld_rlx(&a.w.dec[i]) : 0;
         if (!update) {
             // deeper than the level tables: no update, and the batched engine
             // takes the rest of the order
-            if (!cut && maxD >= 1 && tid == 0) for_rlx(a.w.stop, 2);
+            if (a.lb_mode != 0 && !cut && maxD >= 1 && tid == 0) for_rlx(a.w.stop, 2);
         } else {
             // Lev(l) for l >= 1 (off[D] = r closes the table): Lev(1) from the
             // sums, then prefix sums of the steps
@@ -503,7 +512,7 @@ __global__ void __launch_bounds__(T) k_ring(RingArgs a) {
         }
         __syncthreads();
     }
-    if (tid == 0) offer(true);
+    if (wv == 0) offer(true);
     st_mvis = wave_sum_i64(st_mvis);
     if (lane == 0 && st_mvis) {
         fadd_rlx(&a.stats[ST_MVIS], st_mvis);
@@ -532,6 +541,14 @@ static int ring_lds_limit() {
 // the bitmap and a spare word
 static size_t ring_lds_bytes(int32_t n) { return 4 * (((size_t)n + 31) / 32 + 1); }
 
+// Undirected, so that every r(v) is known; no heavy vertex, since one lane
+// expands a vertex; few arcs, or a level would be wide and few in number and
+// the batched engine's shared reads pay.  Up to that line the ring is ahead at
+// low diameter too: batched -> ring, top 10 by NBCut of sparse random graphs
+// of 3 10^4 vertices, 4 arcs a vertex 3.8 -> 1.3 ms, 7 arcs 11.7 -> 2.0 ms; of
+// 3 10^5, 35 -> 11.7 and 74 -> 26 ms; a small world of 3 10^4, 131 -> 5.6 ms.
+// (A random tree of 3 10^5 needs few searches and each has a wide front: 2.8
+// -> 3.2 ms.)
 int tkc_ring_blocks(const DevGraph& g) {
     if (g.directed || g.nheavy > 0 || g.m > 8 * (int64_t)g.n || g.n < 2) return 0;
     if (ring_lds_bytes(g.n) + RING_STATIC_LDS > (size_t)ring_lds_limit()) return 0;
@@ -555,7 +572,7 @@ int tkc_launch_ring(const DevGraph& g, DevReach rc, OrderView ov, BoundsView bv,
                     int64_t* stats, int lb_mode, int32_t limit, hipStream_t s) {
     if (!w.queue || !w.levoff || !w.levtab || !w.comb || !w.dec || !w.ell || !w.cursor || !w.stop || !w.started || w.nblocks < 1 || w.lcap < 4)
         return -2;
-    if (g.directed || g.nheavy > 0 || bv.harm || lb_mode < 1) return -2;
+    if (g.directed || g.nheavy > 0 || bv.harm) return -2;
     const size_t lds = ring_lds_bytes(g.n);
     if (lds + RING_STATIC_LDS > (size_t)ring_lds_limit()) return -2;
     RingArgs a{};

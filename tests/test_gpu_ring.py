@@ -1,4 +1,4 @@
-"""Ring engine (complete searches, one per workgroup, visited set in LDS)
+"""Ring engine (searches one per workgroup, cut or complete, visited set in LDS)
 against the oracle's exact answer: widths around its words, degrees around
 its four-arc records, levels wider than their LDS copy, disconnected graphs,
 searches deeper than its level tables, ties and renumbered graphs."""
@@ -61,7 +61,7 @@ def answer(name):
     return oracle.closeness_topk(g.n, g.edges, False, g.n)
 
 
-@pytest.mark.parametrize("variant", ["nbbound", "degbound", "nbcutlb", "degcutlb"])
+@pytest.mark.parametrize("variant", ["nbbound", "degbound", "nbcutlb", "degcutlb", "nbcut", "degcut"])
 @pytest.mark.parametrize("name", ["path:2", "path:31", "path:33", "cycle:32", "cycle:257", "grid:9", "grid:60",
                                   "parts:40", "fan:30", "path:3000"])
 def test_ring_topk(ctx, name, variant):
@@ -71,7 +71,7 @@ def test_ring_topk(ctx, name, variant):
         dg = tkc.Graph.from_graphgen(ctx, g, relabel=relabel)
         for k in (1, 10, g.n if g.n <= 300 else 100):
             print("ring", name, variant, k, relabel, flush=True)
-            got = tkc.topk_closeness(dg, k, variant, "batched")
+            got = tkc.topk_closeness(dg, k, variant, "hybrid" if variant == "degcut" else "batched")
             kk = min(k, g.n)
             assert got[4]["main_kernel"] == 2
             for a, b in zip(got[:4], (ids, S, r, f)):
@@ -92,10 +92,11 @@ def test_ring_deeper_than_tables(ctx):
     dg.free()
 
 
-def test_ring_ties(ctx):
+@pytest.mark.parametrize("variant", ["nbbound", "nbcut"])
+def test_ring_ties(ctx, variant):
     g = graph("cycle:257")   # every vertex ties
     dg = tkc.Graph.from_graphgen(ctx, g)
-    got = tkc.topk_closeness_ties(dg, 5, "nbbound", "batched")
+    got = tkc.topk_closeness_ties(dg, 5, variant, "batched")
     assert np.array_equal(got[0], np.arange(257)) and len(set(got[1].tolist())) == 1
     dg.free()
 
