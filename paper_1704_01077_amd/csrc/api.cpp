@@ -1302,6 +1302,7 @@ int32_t tkc_auto_variant(tkc_ctx* c, tkc_graph* g) {
     if (rc == TKC_OK) {
         double lg = std::log2((double)std::max<int32_t>(g->n, 2));
         if (st.max_level > 64 && st.max_level > 4 * lg) v = TKC_NB_BOUND;
+        g->levels = std::max<int32_t>(st.max_level, 1);
     }
     g->auto_variant = v;
     return v;

@@ -79,6 +79,15 @@ struct tkc_server {
     std::vector<size_t> pack_need;             // workspace bytes of a packed call
     int64_t n_served = 0, n_packed = 0, n_pack_calls = 0;
 
+    // The ring engine takes this request alone: a pack's searches go level by
+    // level, with a barrier of all its blocks each, for as long as its deepest
+    // member lasts (13.6 ms a launch with a street network of 1,880 vertices
+    // and 56 levels, whose request alone takes 0.8 to 1.7 ms and the others'
+    // about 0.5 ms).  Such a request pays for a launch of its own, about 0.5
+    // ms, from some 32 levels on; social and web graphs have a dozen.  A graph
+    // whose depth is not known yet does not join a pack.
+    static bool rings(const Request& q, const tkc_graph& g) { return q.ring && (!g.levels || g.levels > 32); }
+
     // fills request rq's answer from a packed call's concatenated results
     static void take(Request& rq, const std::vector<int32_t>& ids, const std::vector<int64_t>& S,
                      const std::vector<int64_t>& R, const std::vector<double>& F, int32_t o, int32_t c) {
@@ -146,6 +155,8 @@ struct tkc_server {
                 std::lock_guard<std::mutex> lk(mu);
                 if (packing && !rq->cancelled) pk = pack_of[rq->graph_id];
             }
+            if (pk >= 0 && rq->ring && !g->levels) tkc_auto_variant(c, g);
+            if (pk >= 0 && rings(*rq, *g)) pk = -1;
             if (pk >= 0) {
                 pv = rq->variant == TKC_AUTO ? tkc_auto_variant(c, g) : rq->variant;
                 if (pv != TKC_NB_CUT && pv != TKC_DEG_CUT) pk = -1;
@@ -163,7 +174,8 @@ struct tkc_server {
                         const int32_t gid = q->graph_id;
                         // an AUTO request joins once its graph's variant is known
                         const int32_t qv = q->variant == TKC_AUTO ? graphs[gid]->auto_variant.load() : q->variant;
-                        if (pack_of[gid] == pk && !used[member_of[gid]] && qv == pv && !q->cancelled) {
+                        if (pack_of[gid] == pk && !used[member_of[gid]] && qv == pv && !q->cancelled &&
+                            !rings(*q, *graphs[gid])) {
                             used[member_of[gid]] = 1;
                             q->state = 1;
                             group.push_back(q);
