@@ -109,7 +109,6 @@ static size_t ws_items(Workspace& ws, const WsShape& sh, std::vector<WsItem>& it
         {(void**)&ws.b_lvl, sh.lb ? 2 * n * W : 8, false},
         {(void**)&ws.b_outS, 8 * n, false}, {(void**)&ws.b_outR, 8 * n, false},
         // per-workgroup engine
-        {(void**)&ws.s_vis, 4 * words * (size_t)sh.swarm_blocks, true},
         {(void**)&ws.s_queue, 4 * (size_t)sh.qcap * (size_t)sh.swarm_blocks, false},
         {(void**)&ws.s_deferred, 4 * n, false},
         // ring engine
@@ -582,10 +581,6 @@ WsShape tkc_shape_for(const EngineTuning& t, tkc_graph* g, int32_t k, bool lb) {
     sh.nchunks = std::max(g->nchunks, g->rnchunks);
     sh.qcap = std::max(64, std::min(t.swarm_qcap, g->n));
     sh.swarm_blocks = std::max(1, tkc_swarm_max_blocks(256));
-    // the private bitmaps of the per-workgroup engine cost blocks * n/8 bytes;
-    // keep them under 2 GiB
-    while (sh.swarm_blocks > 64 && (int64_t)sh.swarm_blocks * ((g->n + 31) / 32) * 4 > (2ll << 30))
-        sh.swarm_blocks /= 2;
     return sh;
 }
 
@@ -1014,7 +1009,7 @@ int tkc_run_query(tkc_ctx* c, tkc_graph* g, int32_t k, int32_t variant, int32_t 
             return tkc_fail(TKC_EDEVICE, "plain engine launch failed: %s", hipGetErrorString(hipGetLastError()));
         if ((rc = tm.done(readback))) return rc;
         rb_ready = true;
-    } else if (mode == TKC_BATCHED || ring) {
+    } else if (mode == TKC_BATCHED || ring || !tkc_swarm_fits(dg)) {
         trace_reset(c);
         // launches of slice_batches batches each when that is set (the
         // cursor, stop flag, top k and bounds live in device memory between
@@ -1091,7 +1086,6 @@ int tkc_run_query(tkc_ctx* c, tkc_graph* g, int32_t k, int32_t variant, int32_t 
         int32_t* small = (int32_t*)ws.small;
         int32_t* pin = (int32_t*)c->pinned;
         SwarmWork sw{};
-        sw.vis = ws.s_vis;
         sw.queue = ws.s_queue;
         sw.deferred = ws.s_deferred;
         sw.ndeferred = small + 4;

@@ -247,9 +247,10 @@ int tkc_launch_batch(const DevGraph& g, DevReach rc, OrderView ov, BoundsView bv
                      int64_t* out_S, int64_t* out_r, const EngineTuning& tune, hipStream_t s,
                      int* grid_out, const PackReq* preq = nullptr, int32_t npreq = 0);
 
-// k_swarm.hip: one search per workgroup for short cut searches.
+// k_swarm.hip: one search per workgroup for short cut searches, on graphs of
+// at most TKC_SWARM_SIZE vertices and edges (visited set in LDS).
+#define TKC_SWARM_SIZE (1 << 18)
 struct SwarmWork {
-    uint32_t* vis;       // nblocks * words_per_block
     int32_t* queue;      // nblocks * qcap
     int32_t* deferred;   // n
     int32_t* ndeferred;  // 1
@@ -266,6 +267,7 @@ int tkc_launch_swarm(const DevGraph& g, DevReach rc, OrderView ov, BoundsView bv
                      SwarmWork w, int64_t* stats, int32_t start_pos, const EngineTuning& tune,
                      hipStream_t s);
 int tkc_swarm_max_blocks(int block);
+bool tkc_swarm_fits(const DevGraph& g);
 
 // k_ring.hip: one search per workgroup, visited set in LDS (undirected graphs
 // of low degree): cut ones (lb_mode 0), complete ones with level-based updates

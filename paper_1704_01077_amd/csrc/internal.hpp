@@ -63,7 +63,6 @@ struct Workspace {
     int64_t *b_ctr, *b_hist, *b_levtab, *b_outS, *b_outR;
     uint16_t* b_lvl;
     // per-workgroup engine
-    uint32_t* s_vis;
     int32_t *s_queue, *s_deferred;
     // ring engine
     int32_t *r_queue, *r_off;

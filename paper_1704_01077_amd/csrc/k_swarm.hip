@@ -2,9 +2,8 @@
 // three levels (Sect. 6), far too little work to fill the GPU one search at
 // a time.  Here every workgroup pulls the next candidate from the order
 // with an atomic cursor and runs that search alone: levels are separated by
-// workgroup barriers only, the visited set is a private bitmap that stays
-// in the XCD's L2, the queue is private, and the current k-th farness x is
-// re-read from the shared top-k at every level boundary.  A search whose
+// workgroup barriers only, the visited set is a bitmap in LDS, the queue is
+// private, and the current k-th farness x is polled at every level boundary.  A search whose
 // queue outgrows its capacity is handed back (deferred) to the batched
 // engine, which is better at large searches.  The stop rule of Alg. 1 is
 // applied when a candidate is taken: once one candidate's key proves that
@@ -16,6 +15,17 @@
 // therefore closes itself: the cursor stops, searches in flight are
 // deferred at their next level boundary, and the host hands the deferred
 // list and the rest of the order to the batched engine.
+//
+// What bounds it: the latency of a level (cursor, row, arc, bitmap, barrier),
+// so the bitmap lives in LDS (in memory, with the polls of x invalidating the
+// L2 at every level, the traversal of a social network of 3 10^4 vertices, top
+// 100, took 1.71 ms and of a web graph of 3 10^4, top 10, 0.37; now 0.72 and
+// 0.28).  A large search wants the whole chip, and a batch shares its reads
+// among 64 of them, hence the line at TKC_SWARM_SIZE; batched -> this engine:
+// social networks of 3 10^4 vertices and 1.8 10^5 edges 2.34 -> 0.72 ms, web
+// graphs of 3 10^4 and 1.8 10^5 0.89 -> 0.54 (top 100); but of 6 10^4 and
+// 4.8 10^5 1.28 -> 2.24, of 1.5 10^5 and 1.3 10^6 1.90 -> 4.27.  Between 2 and
+// 5 10^5 arcs it depends on the graph (0.95 -> 0.43 and 1.02 -> 1.72).
 //
 // stop word bits: 1 = the stop rule fired, 2 = the engine closed itself.
 #include "dev_common.hpp"
@@ -45,7 +55,7 @@ struct SwarmArgs {
     SwarmWork w;
     int64_t* stats;
     int32_t start_pos;
-    int32_t words;
+    int32_t words;        // of the bitmap: the dynamic LDS
     int32_t defer_cap;
 };
 
@@ -74,6 +84,7 @@ TKC_DEV int32_t block_excl_scan(int32_t v, int32_t* out, int32_t* wsum) {
 
 template <int SB>
 __global__ void __launch_bounds__(SB) k_swarm(SwarmArgs a) {
+    extern __shared__ uint32_t s_vis[];
     __shared__ int32_t s_pos;
     __shared__ int32_t s_pre[SB + 1];
     __shared__ int32_t s_beg[SB];
@@ -90,7 +101,6 @@ __global__ void __launch_bounds__(SB) k_swarm(SwarmArgs a) {
     const int32_t* __restrict__ ci = a.g.ci;
     const int32_t* __restrict__ deg = a.g.deg;
     const bool dir = a.g.directed;
-    uint32_t* vis = a.w.vis + (int64_t)blockIdx.x * a.words;
     int32_t* q = a.w.queue + (int64_t)blockIdx.x * a.w.qcap;
     const int32_t qcap = a.w.qcap;
     const int32_t count = a.ov.count;
@@ -104,12 +114,13 @@ __global__ void __launch_bounds__(SB) k_swarm(SwarmArgs a) {
         seed_stopped = a.w.seed[ST_STOP] != 0;
     }
 
+    for (int32_t i = tid; i < a.words; i += SB) s_vis[i] = 0;
     for (;;) {
         if (tid == 0) {
             int32_t p = -1;
             if (!seed_stopped && ld_rlx(a.w.stop) == 0) p = start_pos + fadd_rlx(a.w.cursor, 1);
             s_pos = p;
-            XVal x = read_x(a.tk.st, a.tk.ring);
+            const XVal x = read_x_poll(a.tk.st, a.tk.ring);
             s_x[0] = x.num; s_x[1] = x.den; s_x[2] = x.id;
             s_dec = 0;
             if (p >= 0 && p < count) {
@@ -140,7 +151,7 @@ __global__ void __launch_bounds__(SB) k_swarm(SwarmArgs a) {
         const int64_t av = a.rc.alpha[v], ov = a.rc.omega[v];
         const int64_t dv = deg[v];
         if (tid == 0) {
-            vis[v >> 5] |= 1u << (v & 31);
+            s_vis[v >> 5] |= 1u << (v & 31);
             q[0] = v;
             s_tail = 1;
             s_over = 0;
@@ -154,7 +165,7 @@ __global__ void __launch_bounds__(SB) k_swarm(SwarmArgs a) {
         for (;;) {
             if (nf == 0) { status = 1; break; }
             if (tid == 0) {
-                XVal x = read_x(a.tk.st, a.tk.ring);
+                const XVal x = read_x_poll(a.tk.st, a.tk.ring);
                 s_x[0] = x.num; s_x[1] = x.den; s_x[2] = x.id;
                 s_cnt = 0; s_deg = 0;
                 s_closed = (ld_rlx(a.w.stop) & 2) != 0;
@@ -193,8 +204,8 @@ __global__ void __launch_bounds__(SB) k_swarm(SwarmArgs a) {
                     }
                     int32_t w = ci[s_beg[lo] + (e - s_pre[lo])];
                     uint32_t bit = 1u << (w & 31);
-                    if (!(vis[w >> 5] & bit)) {
-                        uint32_t old = for_wg(&vis[w >> 5], bit);
+                    if (!(s_vis[w >> 5] & bit)) {
+                        const uint32_t old = atomicOr(&s_vis[w >> 5], bit);
                         if (!(old & bit)) {
                             int32_t slot = atomicAdd(&s_tail, 1);
                             if (slot < qcap) q[slot] = w;
@@ -225,13 +236,17 @@ __global__ void __launch_bounds__(SB) k_swarm(SwarmArgs a) {
             le = s_tail;
             __syncthreads();
         }
-        // clear the private bitmap: by the queue, unless it overflowed (then
-        // some marked vertices are not in it)
-        if (status == 3 && s_over) {
-            for (int32_t qw = tid; qw < a.words; qw += SB) vis[qw] = 0;
+        // clear the bitmap: by the queue where that is shorter and did not
+        // overflow (then some marked vertices are not in it)
+        if (s_tail < a.words && s_tail <= qcap) {
+            const int32_t tail = s_tail;
+            for (int32_t i = tid; i < tail; i += SB) s_vis[q[i] >> 5] = 0;
         } else {
-            int32_t tail = s_tail;
-            for (int32_t i = tid; i < tail; i += SB) { int32_t w = q[i]; vis[w >> 5] = 0; }
+            for (int32_t i = tid; i < a.words; i += SB) s_vis[i] = 0;
+        }
+        if (status == 1 && tid < 64) {
+            if (a.bv.harm) topk_insert_wave(a.tk.st, a.tk.ring, a.tk.S, a.tk.R, a.tk.I, harm_enc(H), 2, TKC_OID(a.g, v));
+            else topk_insert_wave(a.tk.st, a.tk.ring, a.tk.S, a.tk.R, a.tk.I, SD, nD, TKC_OID(a.g, v));
         }
         if (tid == 0) {
             st_started++;
@@ -241,8 +256,6 @@ __global__ void __launch_bounds__(SB) k_swarm(SwarmArgs a) {
             if (md > st_maxl) st_maxl = md;
             if (status == 1) {
                 st_exact++;
-                if (a.bv.harm) topk_insert(a.tk.st, a.tk.ring, a.tk.S, a.tk.R, a.tk.I, harm_enc(H), 2, TKC_OID(a.g, v));
-                else topk_insert(a.tk.st, a.tk.ring, a.tk.S, a.tk.R, a.tk.I, SD, nD, TKC_OID(a.g, v));
             } else if (status == 2) {
                 st_cut++;
             } else {
@@ -267,6 +280,10 @@ __global__ void __launch_bounds__(SB) k_swarm(SwarmArgs a) {
         if (st_bytes) fadd_rlx(&s[ST_BYTES], st_bytes);
         __hip_atomic_fetch_max(&s[ST_MAXLEVEL], st_maxl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
+}
+
+bool tkc_swarm_fits(const DevGraph& g) {
+    return g.n + (g.directed ? (int64_t)g.m : (int64_t)g.m / 2) <= TKC_SWARM_SIZE;
 }
 
 int tkc_swarm_max_blocks(int block) {
@@ -295,11 +312,13 @@ int tkc_launch_swarm(const DevGraph& g, DevReach rc, OrderView ov, BoundsView bv
     a.g = g; a.rc = rc; a.ov = ov; a.bv = bv; a.tk = tk; a.w = w;
     a.stats = stats;
     a.start_pos = start_pos;
+    if (!tkc_swarm_fits(g)) return -2;
     a.words = (int32_t)(((int64_t)g.n + 31) / 32);
+    const size_t lds = 4 * (size_t)a.words;
     a.defer_cap = w.defer_cap > 0 ? w.defer_cap : 0x7fffffff;
     if (swarm_sb() == 1024)
-        hipLaunchKernelGGL(k_swarm<1024>, dim3(w.nblocks), dim3(1024), 0, s, a);
+        hipLaunchKernelGGL(k_swarm<1024>, dim3(w.nblocks), dim3(1024), lds, s, a);
     else
-        hipLaunchKernelGGL(k_swarm<256>, dim3(w.nblocks), dim3(256), 0, s, a);
+        hipLaunchKernelGGL(k_swarm<256>, dim3(w.nblocks), dim3(256), lds, s, a);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
