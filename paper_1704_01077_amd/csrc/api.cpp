@@ -352,19 +352,23 @@ extern "C" int tkc_graph_upload(tkc_ctx* c, int32_t n, int64_t m, const int32_t*
     if (!directed && (rrow_ptr || rcol_idx))
         return tkc_fail(TKC_EINVAL, "reverse CSR given for an undirected graph");
     HIPCHK(hipSetDevice(c->device));
-    // host copies: the checks below, the heavy-vertex tables, and (directed)
-    // the host fallback of the reachability bounds
-    std::vector<int32_t> hrp(n + 1), hci(m), hrrp, hrci;
-    const hipMemcpyKind k = (flags & TKC_DEVICE_PTRS) ? hipMemcpyDeviceToHost : hipMemcpyHostToHost;
-    HIPCHK(hipMemcpy(hrp.data(), row_ptr, 4 * (size_t)(n + 1), k));
-    if (m) HIPCHK(hipMemcpy(hci.data(), col_idx, 4 * (size_t)m, k));
-    if (directed) {
-        hrrp.resize(n + 1);
-        hrci.resize(m);
-        HIPCHK(hipMemcpy(hrrp.data(), rrow_ptr, 4 * (size_t)(n + 1), k));
-        if (m) HIPCHK(hipMemcpy(hrci.data(), rcol_idx, 4 * (size_t)m, k));
-    }
-    {
+    // the arrays the device copies are taken from: the caller's, or host copies
+    // that TKC_VALIDATE reads and TKC_RELABEL renumbers
+    const bool dev = (flags & TKC_DEVICE_PTRS) != 0;
+    bool host = (flags & (TKC_VALIDATE | TKC_RELABEL)) != 0;
+    std::vector<int32_t> hrp, hci, hrrp, hrci;
+    if (host) {
+        hrp.resize(n + 1);
+        hci.resize(m);
+        const hipMemcpyKind k = dev ? hipMemcpyDeviceToHost : hipMemcpyHostToHost;
+        HIPCHK(hipMemcpy(hrp.data(), row_ptr, 4 * (size_t)(n + 1), k));
+        if (m) HIPCHK(hipMemcpy(hci.data(), col_idx, 4 * (size_t)m, k));
+        if (directed) {
+            hrrp.resize(n + 1);
+            hrci.resize(m);
+            HIPCHK(hipMemcpy(hrrp.data(), rrow_ptr, 4 * (size_t)(n + 1), k));
+            if (m) HIPCHK(hipMemcpy(hrci.data(), rcol_idx, 4 * (size_t)m, k));
+        }
         int rc = check_csr_bounds(n, m, hrp.data(), hci.data(), "out-arcs");
         if (!rc && directed) rc = check_csr_bounds(n, m, hrrp.data(), hrci.data(), "in-arcs");
         if (rc) return rc;
@@ -415,131 +419,116 @@ extern "C" int tkc_graph_upload(tkc_ctx* c, int32_t n, int64_t m, const int32_t*
     g->directed = directed;
     g->relabeled = (flags & TKC_RELABEL) != 0;
     // heavy vertices and their arc chunks (ascending ids: deterministic), for
-    // the out-arcs and (directed) the in-arcs
-    std::vector<int32_t> hv, hcb(1, 0), cb, ce, cv, rcb, rce, rcv;
-    for (int32_t u = 0; u < n; u++) {
-        int32_t d = hrp[u + 1] - hrp[u];
-        if (d <= HEAVY_DEG) continue;
-        hv.push_back(u);
-        for (int32_t b = hrp[u]; b < hrp[u + 1]; b += CHUNK_ARCS) {
-            cb.push_back(b);
-            ce.push_back(std::min(b + CHUNK_ARCS, hrp[u + 1]));
-            cv.push_back(u);
-        }
-        hcb.push_back((int32_t)cb.size());
-    }
-    if (directed) {
-        for (int32_t u = 0; u < n; u++) {
-            if (hrrp[u + 1] - hrrp[u] <= HEAVY_DEG) continue;
-            for (int32_t b = hrrp[u]; b < hrrp[u + 1]; b += CHUNK_ARCS) {
-                rcb.push_back(b);
-                rce.push_back(std::min(b + CHUNK_ARCS, hrrp[u + 1]));
-                rcv.push_back(u);
-            }
-        }
-    }
-    // pull items over the in-arcs
-    std::vector<int4> items;
-    {
-        const int32_t* irp = directed ? hrrp.data() : hrp.data();
-        int4 cur{0, 0, 0, 0};
-        auto close = [&] {
-            if (cur.z) items.push_back(cur);
-            cur.z = cur.w = 0;
-        };
-        for (int32_t u = 0; u < n; u++) {
-            const int32_t d = irp[u + 1] - irp[u];
-            if (d > PULL_ARCS) {
-                close();
-                for (int32_t b = irp[u]; b < irp[u + 1]; b += PULL_ARCS)
-                    items.push_back(int4{u, b, 1, std::min(PULL_ARCS, irp[u + 1] - b) | PULL_SPLIT |
-                                                      (b == irp[u] ? PULL_FIRST : 0)});
-                continue;
-            }
-            if (cur.z == 64 || cur.w + d > PULL_ARCS) close();
-            if (cur.z == 0) {
-                cur.x = u;
-                cur.y = irp[u];
-            }
-            cur.z++;
-            cur.w += d;
-        }
-        close();
-    }
-    g->nitems = (int32_t)items.size();
-    g->nheavy = (int32_t)hv.size();
-    g->nchunks = (int32_t)cb.size();
-    g->rnchunks = directed ? (int32_t)rcb.size() : g->nchunks;
-    size_t bytes = 4 * (size_t)(n + 1) + 4 * (size_t)(m ? m : 1) + 4 * (size_t)n + 4 * (hv.size() + 1) +
-                   4 * hcb.size() + 12 * (cb.size() + 1) + 12 * (rcb.size() + 1) +
-                   16 * items.size() + ((size_t)m + 64) + 16 * 256;
-    if (directed) bytes += 4 * (size_t)(n + 1) + 4 * (size_t)(m ? m : 1);
-    if (g->relabeled) bytes += 8 * (size_t)n + 512;
-    if (hipMalloc(&g->dbase, bytes + 1024) != hipSuccess) {
+    // the out-arcs and (directed) the in-arcs, and the pull items over the
+    // in-arcs.  Room for the most that n and m allow: a chunk or heavy vertex
+    // ends a row of more than HEAVY_DEG arcs or holds CHUNK_ARCS; an item holds
+    // 64 vertices, or more than PULL_ARCS arcs with the vertex behind it (every
+    // arc counts twice at most), or a piece of a row, or ends a span
+    const size_t sm = (size_t)m, sn = (size_t)n;
+    const size_t hmax = sm / (HEAVY_DEG + 1) + 1, cmax = sm / CHUNK_ARCS + hmax;
+    const size_t imax = sn / 64 + 4 * (sm / PULL_ARCS + 1) + (size_t)tkc_tab_spans(n);
+    const size_t tabs = (size_t)tkc_tab_spans(n) + 1;
+    size_t bytes = 4 * (sn + 1) + 4 * (sm ? sm : 1) + 4 * sn + 4 * (2 * hmax + 1) + 24 * cmax + 16 * imax + sm + 64 +
+                   16 * tabs + 2 * sizeof(CsrCheck) + 20 * 256;
+    if (directed) bytes += 4 * (sn + 1) + 4 * (sm ? sm : 1);
+    if (g->relabeled) bytes += 8 * sn;
+    if (hipMalloc(&g->dbase, bytes) != hipSuccess) {
         hipGetLastError();
         delete g;
         return tkc_fail(TKC_ENOMEM, "graph allocation failed");
     }
     char* p = (char*)g->dbase;
     auto take = [&](size_t b) { char* r = p; p += align_up(b); return r; };
-    g->rp = (int32_t*)take(4 * (size_t)(n + 1));
-    g->ci = (int32_t*)take(4 * (size_t)(m ? m : 1));
-    g->deg = (int32_t*)take(4 * (size_t)n);
-    g->heavy = (int32_t*)take(4 * (hv.size() + 1));
-    g->hcb = (int32_t*)take(4 * hcb.size());
-    g->ch_beg = (int32_t*)take(4 * (cb.size() + 1));
-    g->ch_end = (int32_t*)take(4 * (cb.size() + 1));
-    g->ch_vtx = (int32_t*)take(4 * (cb.size() + 1));
+    g->rp = (int32_t*)take(4 * (sn + 1));
+    g->ci = (int32_t*)take(4 * (sm ? sm : 1));
+    g->deg = (int32_t*)take(4 * sn);
+    g->heavy = (int32_t*)take(4 * hmax);
+    g->hcb = (int32_t*)take(4 * (hmax + 1));
+    g->ch_beg = (int32_t*)take(4 * cmax);
+    g->ch_end = (int32_t*)take(4 * cmax);
+    g->ch_vtx = (int32_t*)take(4 * cmax);
     if (directed) {
-        g->rch_beg = (int32_t*)take(4 * (rcb.size() + 1));
-        g->rch_end = (int32_t*)take(4 * (rcb.size() + 1));
-        g->rch_vtx = (int32_t*)take(4 * (rcb.size() + 1));
+        g->rch_beg = (int32_t*)take(4 * cmax);
+        g->rch_end = (int32_t*)take(4 * cmax);
+        g->rch_vtx = (int32_t*)take(4 * cmax);
     } else {
         g->rch_beg = g->ch_beg;
         g->rch_end = g->ch_end;
         g->rch_vtx = g->ch_vtx;
     }
-    g->items = (int4*)take(16 * items.size());
-    g->own = (uint8_t*)take((size_t)m + 64);
+    g->items = (int4*)take(16 * imax);
+    g->own = (uint8_t*)take(sm + 64);
+    int4* tab = (int4*)take(16 * tabs);
+    CsrCheck* chk = (CsrCheck*)take(2 * sizeof(CsrCheck));
     if (directed) {
-        g->rrp = (int32_t*)take(4 * (size_t)(n + 1));
-        g->rci = (int32_t*)take(4 * (size_t)(m ? m : 1));
+        g->rrp = (int32_t*)take(4 * (sn + 1));
+        g->rci = (int32_t*)take(4 * (sm ? sm : 1));
     } else {
         g->rrp = g->rp;
         g->rci = g->ci;
     }
     if (g->relabeled) {
-        g->d_oid = (int32_t*)take(4 * (size_t)n);
-        g->d_nid = (int32_t*)take(4 * (size_t)n);
+        g->d_oid = (int32_t*)take(4 * sn);
+        g->d_nid = (int32_t*)take(4 * sn);
     }
     hipStream_t s = c->stream;
     int rc = TKC_OK;
     if (g->relabeled &&
-        (hipMemcpyAsync(g->d_oid, oid.data(), 4 * (size_t)n, hipMemcpyHostToDevice, s) != hipSuccess ||
-         hipMemcpyAsync(g->d_nid, nid.data(), 4 * (size_t)n, hipMemcpyHostToDevice, s) != hipSuccess))
+        (hipMemcpyAsync(g->d_oid, oid.data(), 4 * sn, hipMemcpyHostToDevice, s) != hipSuccess ||
+         hipMemcpyAsync(g->d_nid, nid.data(), 4 * sn, hipMemcpyHostToDevice, s) != hipSuccess))
         rc = tkc_fail(TKC_EDEVICE, "vertex map copy failed");
     if (g->relabeled) g->h_nid = nid;
-    if (hipMemcpyAsync(g->rp, hrp.data(), 4 * (size_t)(n + 1), hipMemcpyHostToDevice, s) != hipSuccess ||
-        (m && hipMemcpyAsync(g->ci, hci.data(), 4 * (size_t)m, hipMemcpyHostToDevice, s) != hipSuccess))
+    if (host) {
+        row_ptr = hrp.data();
+        col_idx = hci.data();
+        rrow_ptr = hrrp.data();
+        rcol_idx = hrci.data();
+    } else if (dev) {
+        // the caller's arrays may be work of the default stream
+        hipEvent_t ready = nullptr;
+        hipError_t e = hipEventCreateWithFlags(&ready, hipEventDisableTiming);
+        if (e == hipSuccess) e = hipEventRecord(ready, nullptr);
+        if (e == hipSuccess) e = hipStreamWaitEvent(s, ready, 0);
+        if (ready) hipEventDestroy(ready);
+        if (e != hipSuccess) rc = tkc_fail(TKC_EDEVICE, "stream order failed: %s", hipGetErrorString(e));
+    }
+    const hipMemcpyKind kind = dev && !host ? hipMemcpyDefault : hipMemcpyHostToDevice;
+    CsrCheck hchk[2] = {{0, INT32_MAX}, {0, INT32_MAX}};
+    if (!rc && (hipMemcpyAsync(g->rp, row_ptr, 4 * (sn + 1), kind, s) != hipSuccess ||
+                (m && hipMemcpyAsync(g->ci, col_idx, 4 * sm, kind, s) != hipSuccess)))
         rc = tkc_fail(TKC_EDEVICE, "graph copy failed");
-    if (!rc && directed &&
-        (hipMemcpyAsync(g->rrp, hrrp.data(), 4 * (size_t)(n + 1), hipMemcpyHostToDevice, s) != hipSuccess ||
-         (m && hipMemcpyAsync(g->rci, hrci.data(), 4 * (size_t)m, hipMemcpyHostToDevice, s) != hipSuccess)))
+    if (!rc && directed && (hipMemcpyAsync(g->rrp, rrow_ptr, 4 * (sn + 1), kind, s) != hipSuccess ||
+                            (m && hipMemcpyAsync(g->rci, rcol_idx, 4 * sm, kind, s) != hipSuccess)))
         rc = tkc_fail(TKC_EDEVICE, "reverse graph copy failed");
-    if (!rc && ((hv.size() && hipMemcpyAsync(g->heavy, hv.data(), 4 * hv.size(), hipMemcpyHostToDevice, s)) ||
-                hipMemcpyAsync(g->hcb, hcb.data(), 4 * hcb.size(), hipMemcpyHostToDevice, s) ||
-                (cb.size() && (hipMemcpyAsync(g->ch_beg, cb.data(), 4 * cb.size(), hipMemcpyHostToDevice, s) ||
-                               hipMemcpyAsync(g->ch_end, ce.data(), 4 * ce.size(), hipMemcpyHostToDevice, s) ||
-                               hipMemcpyAsync(g->ch_vtx, cv.data(), 4 * cv.size(), hipMemcpyHostToDevice, s))) ||
-                (rcb.size() && (hipMemcpyAsync(g->rch_beg, rcb.data(), 4 * rcb.size(), hipMemcpyHostToDevice, s) ||
-                                hipMemcpyAsync(g->rch_end, rce.data(), 4 * rce.size(), hipMemcpyHostToDevice, s) ||
-                                hipMemcpyAsync(g->rch_vtx, rcv.data(), 4 * rcv.size(), hipMemcpyHostToDevice, s))) ||
-                hipMemcpyAsync(g->items, items.data(), 16 * items.size(), hipMemcpyHostToDevice, s)))
-        rc = tkc_fail(TKC_EDEVICE, "heavy-vertex table copy failed");
+    int4 tot{0, 0, 0, 0};
     if (!rc) {
-        DevGraph dg = g->view();
-        if (tkc_launch_degrees(dg, s) || tkc_launch_own(dg, g->own, s) || hipStreamSynchronize(s) != hipSuccess)
-            rc = tkc_fail(TKC_EDEVICE, "degree kernel failed");
+        const DevGraph dg = g->view();
+        if (hipMemcpyAsync(chk, hchk, sizeof(hchk), hipMemcpyHostToDevice, s) != hipSuccess ||
+            tkc_launch_csr_check(n, m, g->rp, g->ci, chk, s) ||
+            (directed && tkc_launch_csr_check(n, m, g->rrp, g->rci, chk + 1, s)) || tkc_launch_tab_count(dg, tab, s) ||
+            hipMemcpyAsync(hchk, chk, sizeof(hchk), hipMemcpyDeviceToHost, s) != hipSuccess ||
+            hipMemcpyAsync(&tot, tab + tabs - 1, sizeof(tot), hipMemcpyDeviceToHost, s) != hipSuccess ||
+            hipStreamSynchronize(s) != hipSuccess)
+            rc = tkc_fail(TKC_EDEVICE, "graph check failed: %s", hipGetErrorString(hipGetLastError()));
+    }
+    for (int i = 0; i < 2 && !rc; i++) {
+        const char* what = i ? "in-arcs" : "out-arcs";
+        if (hchk[i].bad & CSR_BAD_FIRST) rc = tkc_fail(TKC_EINVAL, "%s: row_ptr[0] must be 0", what);
+        else if (hchk[i].bad & CSR_BAD_LAST) rc = tkc_fail(TKC_EINVAL, "%s: row_ptr[n] != m_arcs", what);
+        else if (hchk[i].bad & CSR_BAD_ORDER) rc = tkc_fail(TKC_EINVAL, "%s: row_ptr not monotone at %d", what, hchk[i].first);
+        else if (hchk[i].bad & CSR_BAD_ID) rc = tkc_fail(TKC_EINVAL, "%s: vertex id out of range", what);
+    }
+    if (!rc) {
+        g->nitems = tot.x;
+        g->nheavy = tot.y;
+        g->nchunks = tot.z;
+        g->rnchunks = directed ? tot.w : tot.z;
+        const DevGraph dg = g->view();
+        const TabOut to{g->items,  g->heavy,   g->hcb,     g->ch_beg, g->ch_end,
+                        g->ch_vtx, g->rch_beg, g->rch_end, g->rch_vtx};
+        if (tkc_launch_tab_fill(dg, tab, to, s) || tkc_launch_degrees(dg, s) || tkc_launch_own(dg, g->own, s) ||
+            hipStreamSynchronize(s) != hipSuccess)
+            rc = tkc_fail(TKC_EDEVICE, "graph table kernel failed");
     }
     if (rc) {
         hipStreamSynchronize(s);

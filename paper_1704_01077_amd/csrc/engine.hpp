@@ -119,6 +119,26 @@ int tkc_occupancy(const void* fn, int block);
 // k_prep.hip
 int tkc_launch_degrees(const DevGraph& g, hipStream_t s);
 // g.own from g.items (g.rrp gives the rows)
+// the checks every upload runs (memory safety of the kernels): row_ptr starts
+// at 0, never decreases and ends at m; every vertex id is in [0, n)
+#define CSR_BAD_FIRST 1
+#define CSR_BAD_LAST 2
+#define CSR_BAD_ORDER 4
+#define CSR_BAD_ID 8
+struct CsrCheck {
+    int32_t bad;     // the bits above, cleared by the caller
+    int32_t first;   // least u whose row ends before it starts (caller: INT32_MAX)
+};
+int tkc_launch_csr_check(int32_t n, int64_t m, const int32_t* rp, const int32_t* ci, CsrCheck* err, hipStream_t s);
+// tables of an upload: tab holds tkc_tab_spans(n) + 1 entries, the last the
+// totals (items, heavy vertices, their chunks, chunks of the in-arcs)
+struct TabOut {
+    int4* items;
+    int32_t *heavy, *hcb, *ch_beg, *ch_end, *ch_vtx, *rch_beg, *rch_end, *rch_vtx;
+};
+int64_t tkc_tab_spans(int32_t n);
+int tkc_launch_tab_count(const DevGraph& g, int4* tab, hipStream_t s);
+int tkc_launch_tab_fill(const DevGraph& g, int4* tab, const TabOut& o, hipStream_t s);
 int tkc_launch_own(const DevGraph& g, uint8_t* own, hipStream_t s);
 // size holds n+2 int64; in_giant n bytes; sample_host is unused (the
 // dominant component is found on the device)
