@@ -93,7 +93,7 @@ static size_t ws_items(Workspace& ws, const WsShape& sh, std::vector<WsItem>& it
         {(void**)&ws.ring, sizeof(XRec) * TKC_XRING, false},
         {(void**)&ws.tieS, sh.ties ? 8 * n : 8, false}, {(void**)&ws.tieR, sh.ties ? 8 * n : 8, false},
         {(void**)&ws.tieI, sh.ties ? 4 * n : 4, false},
-        {(void**)&ws.bar, 4 * tkc_bar_words(4096), true},
+        {(void**)&ws.bar, 4 * tkc_bar_words(), true},
         // plain engine
         {(void**)&ws.p_vis, 4 * words, true}, {(void**)&ws.p_fb, 12 * words, true},
         {(void**)&ws.p_ql, 4 * n, false}, {(void**)&ws.p_qh, 4 * n, false},

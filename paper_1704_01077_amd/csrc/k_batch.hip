@@ -537,6 +537,7 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
     const int32_t count = order_mode ? a.ov.count : a.list_count;
 
     // replicated per-lane control state
+    __shared__ BarState s_bar;
     __shared__ int32_t s_v[MAXW];
     // per lane: the x its cuts compare with (its request's, read at the
     // start of the batch), the union offset of its graph, its request
@@ -580,6 +581,7 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
         s_pk_pos[tid] = 0;
         s_pk_stop[tid] = 0;
     }
+    if (tid == 0) s_bar.mine = 0;
     __syncthreads();
     if (blockIdx.x == 0)
         for (int i = tid; i < C_NSEL; i += BB) a.w.ctr[i] = 0;
@@ -631,7 +633,7 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
                 if (stop) stats[ST_STOP] = 1;
             }
         }
-        grid_barrier(a.bar, gridDim.x);
+        grid_barrier(a.bar, gridDim.x, &s_bar);
         const int32_t nsel = (int32_t)ld_rlx(&ctr[C_NSEL]);
         pos = (int32_t)ld_rlx(&ctr[C_POS]);
         const bool stop_now = ld_rlx(&ctr[C_STOP]) != 0;
@@ -1101,7 +1103,7 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
                 if (s_blk[1]) fadd_rlx(&ctr[C_DDONE(p)], s_blk[1]);
             }
             PHASE(4);
-            grid_barrier(a.bar, gridDim.x);
+            grid_barrier(a.bar, gridDim.x, &s_bar);
             PHASE(5);
             if (boss && tslot >= 0) a.w.trace[8 + 16 * tslot + 8] = (int64_t)wall_clock64();
             if (trb) {
@@ -1371,7 +1373,7 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
                     }
                     a.w.levtab[lv * W + l] = __double_as_longlong(x - 0.5);
                 }
-                grid_barrier(a.bar, gridDim.x);
+                grid_barrier(a.bar, gridDim.x, &s_bar);
                 // every vertex takes the least bound over the lanes that
                 // reached it, its out-neighbours at exactly 1
                 for (int64_t w = gtid; w < n; w += nthreads) {
@@ -1416,7 +1418,7 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
                         lev[i * W + l] = lev[(i - 1) * W + l] + (dir ? 0 : low) - (r - pre);
                     }
                 }
-                grid_barrier(a.bar, gridDim.x);
+                grid_barrier(a.bar, gridDim.x, &s_bar);
                 for (int64_t w = gtid; w < n; w += nthreads) {
                     int64_t best = -1;
                     int64_t bden = 0;
@@ -1447,7 +1449,7 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
         // only that (and the until_x decision) needs a barrier first; the
         // next batch's selection barrier orders the clear before its level 0
         // (and the kernel's end before the host reads anything)
-        if (a.lb_mode || a.until_x) grid_barrier(a.bar, gridDim.x);
+        if (a.lb_mode || a.until_x) grid_barrier(a.bar, gridDim.x, &s_bar);
         {
             int64_t tot = (int64_t)n * NW;
             for (int64_t q = gtid; q < tot; q += nthreads) {
@@ -1467,8 +1469,8 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
 }
 
 // workgroups of a launch: about one pull item per wave, at least 8, at most
-// the whole GPU (a grid barrier costs 1.8 us for 16 workgroups, 3.4 for 64,
-// 6.2 for 256)
+// the whole GPU (a grid barrier costs 1.9 us for 16 workgroups, 2.4 for 64,
+// 4.0 for 256)
 static int batch_grid(int full, const DevGraph& g) {
     int64_t want = ((int64_t)g.nitems + BB / 64 - 1) / (BB / 64);
     if (want < 8) want = 8;

@@ -140,6 +140,9 @@ __global__ void __launch_bounds__(PB) k_plain(PlainArgs a) {
     const int32_t count = a.list ? a.list_count : a.ov.count;
     int64_t* stats = a.stats;
 
+    __shared__ BarState s_bar;
+    if (threadIdx.x == 0) s_bar.mine = 0;
+    __syncthreads();
     int32_t pos;
     int64_t searches = 0;   // replicated: every workgroup takes the same path
     for (pos = 0; pos < count; pos++) {
@@ -166,7 +169,7 @@ __global__ void __launch_bounds__(PB) k_plain(PlainArgs a) {
                 if (a.bv.harm) topk_insert(a.tk.st, a.tk.ring, a.tk.S, a.tk.R, a.tk.I, harm_enc(0.0), 2, TKC_OID(a.g, v));
                 else topk_insert(a.tk.st, a.tk.ring, a.tk.S, a.tk.R, a.tk.I, 0, 1, TKC_OID(a.g, v));
             }
-            grid_barrier(a.bar, gridDim.x);
+            grid_barrier(a.bar, gridDim.x, &s_bar);
             continue;
         }
         if (a.max_searches > 0 && searches >= a.max_searches) {
@@ -187,7 +190,7 @@ __global__ void __launch_bounds__(PB) k_plain(PlainArgs a) {
             }
             if (a.lb_mode) { a.w.lvl[v] = 0; a.w.levcnt[0] = 1; }
         }
-        grid_barrier(a.bar, gridDim.x);
+        grid_barrier(a.bar, gridDim.x, &s_bar);
 
         int64_t D = 0, nD = 1, SD = 0;
         double H = 0.0;   // harmonic centrality so far (levels 1..D)
@@ -214,7 +217,7 @@ __global__ void __launch_bounds__(PB) k_plain(PlainArgs a) {
             if (want_bu && !bu) {
                 // frontier bitmap of level D from the queue segments
                 for (int64_t q = gtid; q < 3 * words; q += nthreads) a.w.fb[q] = 0;
-                grid_barrier(a.bar, gridDim.x);
+                grid_barrier(a.bar, gridDim.x, &s_bar);
                 uint32_t* fcur = a.w.fb + (D % 3) * words;
                 for (int64_t i = gtid; i < en[0] - st[0]; i += nthreads) {
                     int32_t u = a.w.ql[st[0] + i];
@@ -224,7 +227,7 @@ __global__ void __launch_bounds__(PB) k_plain(PlainArgs a) {
                     int32_t u = a.w.qh[st[1] + i];
                     for_rlx(&fcur[u >> 5], 1u << (u & 31));
                 }
-                grid_barrier(a.bar, gridDim.x);
+                grid_barrier(a.bar, gridDim.x, &s_bar);
                 used_bu = true;
             }
             bu = want_bu;
@@ -337,7 +340,7 @@ __global__ void __launch_bounds__(PB) k_plain(PlainArgs a) {
                 fadd_rlx(&ctr[p * CS + 0], my_cnt);
                 fadd_rlx(&ctr[p * CS + 1], my_deg);
             }
-            grid_barrier(a.bar, gridDim.x);
+            grid_barrier(a.bar, gridDim.x, &s_bar);
             const int64_t cnt = ld_rlx(&ctr[p * CS + 0]);
             const int64_t dsum = ld_rlx(&ctr[p * CS + 1]);
             int64_t tails[3];
@@ -371,7 +374,7 @@ __global__ void __launch_bounds__(PB) k_plain(PlainArgs a) {
                 }
                 a.w.levtab[lv] = __double_as_longlong(xs - 0.5);
             }
-            grid_barrier(a.bar, gridDim.x);
+            grid_barrier(a.bar, gridDim.x, &s_bar);
             const int32_t sc = dir ? a.rc.scc[v] : 0;
             for (int64_t i = gtid; i < en[0] + en[1]; i += nthreads) {
                 int32_t w = i < en[0] ? a.w.ql[i] : a.w.qh[i - en[0]];
@@ -387,7 +390,7 @@ __global__ void __launch_bounds__(PB) k_plain(PlainArgs a) {
                 a.w.levcnt[D] = 0;
                 lev_table(a.w.levcnt, maxD, nD, dir, a.w.levtab);
             }
-            grid_barrier(a.bar, gridDim.x);
+            grid_barrier(a.bar, gridDim.x, &s_bar);
             const int64_t den = sq64(nD - 1);
             const int32_t sc = dir ? a.rc.scc[v] : 0;
             for (int64_t i = gtid; i < en[0] + en[1]; i += nthreads) {
@@ -420,7 +423,7 @@ __global__ void __launch_bounds__(PB) k_plain(PlainArgs a) {
                 stats[ST_CUT]++;
             }
         }
-        grid_barrier(a.bar, gridDim.x);
+        grid_barrier(a.bar, gridDim.x, &s_bar);
     }
     if (boss) stats[ST_CURSOR] = pos;
 }

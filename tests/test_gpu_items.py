@@ -86,3 +86,22 @@ def test_items(ctx, name, width, force):
     finally:
         ctx.tune(**keep)
         dg.free()
+
+
+@pytest.mark.parametrize("groups", [8, 23, 24, 25, 31, 64, 255, 256, 257])
+def test_grid_barrier_widths(ctx, groups):
+    """512 vertices of a tree to a workgroup: launches around the width from
+    which a grid barrier goes by XCD, narrow and wide ones in turn."""
+    gs = []
+    for k in (groups, 8, 40):
+        n = 512 * k
+        g = graphgen.make("tree", n, graphgen.tree(n, k), False)
+        src = np.arange(0, n, n // 150 + 1, dtype=np.int32)
+        gs.append((tkc.Graph.from_graphgen(ctx, g), src, oracle.sums(n, g.edges, False, sources=src)))
+    for turn in range(3):
+        for dg, src, (S, r) in gs:
+            print("barrier", groups, turn, dg.n, flush=True)
+            S2, r2 = dg.sums(src)
+            assert np.array_equal(S2, S) and np.array_equal(r2, r)
+    for dg, _, _ in gs:
+        dg.free()
