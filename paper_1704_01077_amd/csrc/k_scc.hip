@@ -219,63 +219,106 @@ __global__ void __launch_bounds__(SB) k_scc_pivot(int32_t n, const int32_t* scc,
     if (threadIdx.x == 0 && key) atomicMax(best, key);
 }
 
-// the same level as a pull: an unassigned vertex not yet found looks for a
-// predecessor found at level nl - 1 (its own thread, first hit ends it);
-// used when the frontier is a large part of the graph
-__global__ void k_scc_pull(int32_t n, const int32_t* prp, const int32_t* pci, const int32_t* scc, uint32_t* mark,
-                           uint32_t bit, int32_t* lev, int32_t nl) {
-    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
-        if (scc[v] >= 0 || (mark[v] & bit)) continue;
-        for (int32_t e = prp[v]; e < prp[v + 1]; e++) {
-            if (__hip_atomic_load(&lev[pci[e]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == nl - 1) {
-                mark[v] |= bit;
-                __hip_atomic_store(&lev[v], nl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                break;
+// The pivot's forward (dir 0, bit 1) and backward (dir 1, bit 2) searches, side
+// by side in blockIdx.y, one launch per level.  Only who is reached matters,
+// so a level's vertices are appended in any order, as pieces of at most
+// FB_PIECE arcs; a small frontier pushes, one wave per piece, a large one makes
+// every unassigned vertex look for a found predecessor (in this launch's marks
+// too: whoever is marked is also in the next frontier, so nothing is missed
+// when a mark is not seen yet).  Frontier sizes stay on the device: the host
+// launches FB_GROUP levels at a time, empty ones end at once.  With the list
+// of each level sorted and its size read back, a level took 11 launches and a
+// host wait, and the search of a web graph of 1.3 10^5 vertices 1.0 ms.
+#define FB_PIECE 256
+#define FB_GROUP 8
+struct FbState {
+    int32_t cnt[3];     // pieces of the frontier of level l at [l % 3]
+    int32_t start[3];   // ... and where they start in the queue
+    unsigned long long sum[3];   // its vertices << 32 + their arcs
+    int32_t pad[4];
+};
+__global__ void k_fb_seed(const int32_t* rp, const int32_t* rrp, uint32_t* mark, int32_t pivot, FbState* st, int2* q,
+                          int64_t qcap) {
+    const int dir = blockIdx.x;
+    const int32_t* arp = dir ? rrp : rp;
+    const int32_t b = arp[pivot], d = arp[pivot + 1] - b, np = (d + FB_PIECE - 1) / FB_PIECE;
+    for (int32_t i = threadIdx.x; i < np; i += blockDim.x) q[dir * qcap + i] = int2{pivot, b + i * FB_PIECE};
+    if (threadIdx.x == 0) {
+        FbState s0{};
+        s0.cnt[0] = np;
+        s0.sum[0] = (1ull << 32) + (unsigned long long)d;
+        st[dir] = s0;
+        if (dir == 0) mark[pivot] = 3u;
+    }
+}
+__global__ void __launch_bounds__(SB) k_fb_level(int32_t n, int64_t m, const int32_t* __restrict__ rp,
+                                                 const int32_t* __restrict__ ci, const int32_t* __restrict__ rrp,
+                                                 const int32_t* __restrict__ rci, const int32_t* __restrict__ scc,
+                                                 uint32_t* mark, FbState* st, int2* q, int64_t qcap, int32_t nl) {
+    const int dir = blockIdx.y;
+    const int32_t *arp = dir ? rrp : rp, *aci = dir ? rci : ci;
+    const uint32_t bit = dir ? 2u : 1u;
+    st += dir;
+    q += dir * qcap;
+    const int p = (nl - 1) % 3, c = nl % 3, z = (nl + 1) % 3;
+    const int32_t fcnt = st->cnt[p], out = st->start[p] + fcnt;
+    const unsigned long long sum = st->sum[p];
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        st->start[c] = out;
+        st->cnt[z] = 0;
+        st->sum[z] = 0;
+    }
+    if (fcnt == 0) return;
+    const int lane = lane_id();
+    // the whole wave: lanes with `found` append their vertex w
+    auto append = [&](bool found, int32_t w) {
+        const uint64_t fm = __ballot(found);
+        if (!fm) return;
+        const int32_t b = found ? arp[w] : 0, d = found ? arp[w + 1] - b : 0, np = (d + FB_PIECE - 1) / FB_PIECE;
+        int32_t x = np, a = d;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int32_t y = __shfl_up(x, o, 64), t = __shfl_up(a, o, 64);
+            if (lane >= o) {
+                x += y;
+                a += t;
             }
         }
-    }
-}
-// out-degrees (in the search's direction) of the frontier entries, zero
-// past its end: an exclusive scan of these spreads its arcs evenly
-__global__ void k_front_deg(int32_t n, const int32_t* fr, const int32_t* fcnt_dev, const int32_t* arp, int32_t* deg) {
-    const int32_t fcnt = *fcnt_dev;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        deg[i] = i < fcnt ? arp[fr[i] + 1] - arp[fr[i]] : 0;
-}
-// one level of a push over the frontier's arcs, one thread per arc: arc j
-// belongs to the last entry whose prefix pre[] is <= j
-__global__ void k_scc_push(const int32_t* fr, const int32_t* pre, int32_t fcnt, int64_t farcs, const int32_t* arp,
-                           const int32_t* aci, const int32_t* scc, uint32_t* mark, uint32_t bit, int32_t* lev,
-                           int32_t nl) {
-    for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < farcs;
-         j += (int64_t)gridDim.x * blockDim.x) {
-        int32_t lo = 0, hi = fcnt - 1;
-        while (lo < hi) {
-            const int32_t mid = (lo + hi + 1) >> 1;
-            if (pre[mid] <= j) lo = mid;
-            else hi = mid - 1;
+        int32_t at = 0;
+        if (lane == 63) {
+            at = atomicAdd(&st->cnt[c], x);
+            atomicAdd(&st->sum[c], ((unsigned long long)__popcll(fm) << 32) + (unsigned long long)(uint32_t)a);
         }
-        const int32_t u = fr[lo];
-        const int32_t w = aci[arp[u] + (int32_t)(j - pre[lo])];
-        if (scc[w] < 0 && !(mark[w] & bit) && !(atomicOr(&mark[w], bit) & bit)) lev[w] = nl;
+        at = out + __shfl(at, 63, 64) + x - np;
+        for (int32_t i = 0; i < np; i++) q[at + i] = int2{w, b + i * FB_PIECE};
+    };
+    const int64_t gt = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, nt = (int64_t)gridDim.x * blockDim.x;
+    // a frontier holding a large share of the vertices or arcs pulls
+    if ((int64_t)(sum >> 32) * 16 > n || (int64_t)(sum & 0xffffffffull) * 8 > m) {
+        const int32_t *prp = dir ? rp : rrp, *pci = dir ? ci : rci;
+        for (int64_t v0 = gt - lane; v0 < n; v0 += nt) {
+            const int64_t v = v0 + lane;
+            bool found = false;
+            if (v < n && scc[v] < 0 && !(mark[v] & bit)) {
+                for (int32_t e = prp[v]; e < prp[v + 1]; e++)
+                    if (mark[pci[e]] & bit) {
+                        found = true;
+                        break;
+                    }
+                if (found) atomicOr(&mark[v], bit);
+            }
+            append(found, (int32_t)v);
+        }
+        return;
     }
-}
-// the vertices of level nl, in id order: flags, then (after a scan) scatter
-__global__ void k_lev_flag(int32_t n, const int32_t* lev, int32_t nl, int32_t* flag) {
-    const int32_t v = blockIdx.x * blockDim.x + threadIdx.x;
-    if (v < n) flag[v] = lev[v] == nl;
-}
-__global__ void k_lev_scatter(int32_t n, const int32_t* lev, int32_t nl, const int32_t* pos, int32_t* out) {
-    const int32_t v = blockIdx.x * blockDim.x + threadIdx.x;
-    if (v < n && lev[v] == nl) out[pos[v]] = v;
-}
-__global__ void k_scc_seed(int32_t* list, uint32_t* mark, int32_t* lev, int32_t pivot, uint32_t bit,
-                           int32_t* fcnt_dev) {
-    if (threadIdx.x == 0) {
-        list[0] = pivot;
-        mark[pivot] |= bit;
-        lev[pivot] = 0;
-        *fcnt_dev = 1;
+    for (int64_t i = gt / 64; i < fcnt; i += nt / 64) {
+        const int2 pc = q[st->start[p] + i];
+        const int32_t end = arp[pc.x + 1] - pc.y < FB_PIECE ? arp[pc.x + 1] : pc.y + FB_PIECE;
+        for (int32_t e0 = pc.y; e0 < end; e0 += 64) {
+            const int32_t e = e0 + lane, w = e < end ? aci[e] : 0;
+            const bool found = e < end && scc[w] < 0 && !(mark[w] & bit) && !(atomicOr(&mark[w], bit) & bit);
+            append(found, w);
+        }
     }
 }
 __global__ void k_scc_assign_fb(int32_t n, int32_t* scc, uint32_t* mark, int32_t pivot) {
@@ -1010,44 +1053,24 @@ int tkc_device_alpha_omega(const DevGraph& g, int64_t* alpha, int64_t* omega, in
         DEV_OK(hipStreamSynchronize(s));
         if (*(unsigned long long*)pin != 0) {
             pivot = (int32_t)(0xffffffffull - (*(unsigned long long*)pin & 0xffffffffull));
-            int32_t* lev = color;   // free until the colouring
-            for (int dir = 0; dir < 2 && !seq; dir++) {
-                const uint32_t bit = dir == 0 ? 1u : 2u;
-                const int32_t* arp = dir == 0 ? g.rp : g.rrp;
-                const int32_t* aci = dir == 0 ? g.ci : g.rci;
-                DEV_OK(hipMemsetAsync(lev, 0xff, 4 * (size_t)n, s));
-                hipLaunchKernelGGL(k_scc_seed, dim3(1), dim3(64), 0, s, list, mark, lev, pivot, bit, small);
-                // frontier size (small[0]), its arcs (small[2]) and their
-                // prefix by entry (next[]), read back once per level
-                auto frontier = [&]() -> int {
-                    hipLaunchKernelGGL(k_front_deg, dim3(rblk(n)), dim3(SB), 0, s, n, list, small, arp, next);
-                    if (scan(next, n, bsum, small + 2, s)) return -1;
-                    if (hipMemcpyAsync(pin, small, 16, hipMemcpyDeviceToHost, s) != hipSuccess) return -1;
-                    if (hipStreamSynchronize(s) != hipSuccess) return -1;
-                    return 0;
-                };
-                STEP_OK(frontier());
-                int32_t fcnt = pin[0];
-                int64_t farcs = pin[2];
-                for (int32_t nl = 1; fcnt > 0; nl++) {
-                    if (nl > FB_LEVELS) {
-                        seq = true;
-                        break;
-                    }
-                    // a frontier holding a large share of the arcs: pull
-                    // over the predecessors instead (direction optimising)
-                    if ((int64_t)fcnt * 16 > n || farcs * 8 > m)
-                        hipLaunchKernelGGL(k_scc_pull, dim3(nblk(n)), dim3(SB), 0, s, n, dir == 0 ? g.rrp : g.rp,
-                                           dir == 0 ? g.rci : g.ci, scc, mark, bit, lev, nl);
-                    else if (farcs > 0)
-                        hipLaunchKernelGGL(k_scc_push, dim3(std::min(nblk(farcs), 8192)), dim3(SB), 0, s, list, next,
-                                           fcnt, farcs, arp, aci, scc, mark, bit, lev, nl);
-                    hipLaunchKernelGGL(k_lev_flag, dim3(gb), dim3(SB), 0, s, n, lev, nl, cid);
-                    STEP_OK(scan(cid, n, bsum, small, s));
-                    hipLaunchKernelGGL(k_lev_scatter, dim3(gb), dim3(SB), 0, s, n, lev, nl, cid, list);
-                    STEP_OK(frontier());
-                    fcnt = pin[0];
-                    farcs = pin[2];
+            // both queues in the space of arrays that later steps fill
+            FbState* st = (FbState*)(small + 128);
+            int2* q = (int2*)ca;
+            const int64_t qcap = (int64_t)n + m / FB_PIECE + 8;
+            if ((char*)bsum - (char*)q < (int64_t)(16 * qcap)) { fail(-3); goto done; }
+            hipLaunchKernelGGL(k_fb_seed, dim3(2), dim3(SB), 0, s, g.rp, g.rrp, mark, pivot, st, q, qcap);
+            const FbState* hs = (const FbState*)pin;
+            const dim3 grid(std::min(nblk(n), 512), 2);
+            for (int32_t nl = 1;;) {
+                for (int i = 0; i < FB_GROUP; i++, nl++)
+                    hipLaunchKernelGGL(k_fb_level, grid, dim3(SB), 0, s, n, m, g.rp, g.ci, g.rrp, g.rci, scc, mark, st,
+                                       q, qcap, nl);
+                DEV_OK(hipMemcpyAsync(pin, st, 2 * sizeof(FbState), hipMemcpyDeviceToHost, s));
+                DEV_OK(hipStreamSynchronize(s));
+                if (hs[0].cnt[(nl - 1) % 3] == 0 && hs[1].cnt[(nl - 1) % 3] == 0) break;
+                if (nl > FB_LEVELS) {
+                    seq = true;
+                    break;
                 }
             }
             phase("fw-bw", seq, pivot);
