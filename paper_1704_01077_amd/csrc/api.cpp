@@ -967,9 +967,9 @@ int tkc_run_query(tkc_ctx* c, tkc_graph* g, int32_t k, int32_t variant, int32_t 
     }
     DevTopk tk = topk_view(ws);
     const TieBuf tb{ws.tieS, ws.tieR, ws.tieI, n};
-    if (tkc_launch_topk_init(tk, k, s, ties ? &tb : nullptr)) return tkc_fail(TKC_EDEVICE, "top-k init failed");
-    HIPCHK(hipMemsetAsync(ws.stats, 0, 8 * 4 * ST_COUNT, s));
-    HIPCHK(hipMemsetAsync(ws.p_vis, 0, 4 * (((size_t)n + 31) / 32), s));
+    if (tkc_launch_topk_init(tk, k, s, ties ? &tb : nullptr, ws.stats, 4 * ST_COUNT, (int32_t*)ws.small + 4))
+        return tkc_fail(TKC_EDEVICE, "top-k init failed");
+    if (mode == TKC_PLAIN) HIPCHK(hipMemsetAsync(ws.p_vis, 0, 4 * (((size_t)n + 31) / 32), s));
     HIPCHK(hipEventRecord(c->evq[2], s));
 
     DevGraph dg = g->view();
@@ -1023,7 +1023,6 @@ int tkc_run_query(tkc_ctx* c, tkc_graph* g, int32_t k, int32_t variant, int32_t 
             rw.nblocks = ring;
             // a slice runs two searches per workgroup
             const int32_t limit = slice ? 2 * ring : 0;
-            HIPCHK(hipMemsetAsync(small + 4, 0, 2 * sizeof(int32_t), s));
             if (tkc_launch_ring_begin(dg, rcv, bv, rw, s)) return tkc_fail(TKC_EDEVICE, "bound kernel failed");
             do {
                 HIPCHK(hipMemsetAsync(small + 6, 0, sizeof(int32_t), s));
@@ -1095,14 +1094,12 @@ int tkc_run_query(tkc_ctx* c, tkc_graph* g, int32_t k, int32_t variant, int32_t 
                                  false, nullptr, nullptr, seed, s, &grid))
                 return tkc_fail(TKC_EDEVICE, "batched seed launch failed: %s", hipGetErrorString(hipGetLastError()));
             HIPCHK(hipEventRecord(c->evm, s));
-            HIPCHK(hipMemsetAsync(small + 4, 0, 3 * sizeof(int32_t), s));
             if (tkc_launch_swarm(dg, rcv, ov, bv, tk, sw, st_swarm, 0, c->tune, s))
                 return tkc_fail(TKC_EDEVICE, "per-workgroup engine launch failed");
-            // the seed's counters, the swarm's exit state, and the results in
-            // case nothing follows
+            // the swarm's exit state, the counters, and the results in case
+            // nothing follows
             if ((rc = tm.done([&] {
                      HIPCHK(hipMemcpyAsync(pin, small + 4, 3 * sizeof(int32_t), hipMemcpyDeviceToHost, s));
-                     if (int r = queue_stats(c, st_batch)) return r;
                      return readback();
                  })))
                 return rc;

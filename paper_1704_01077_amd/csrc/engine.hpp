@@ -176,21 +176,15 @@ int tkc_device_alpha_omega(const DevGraph& g, int64_t* alpha, int64_t* omega, in
                            size_t* need = nullptr);
 
 // k_sort.hip: stable ascending sort of (key, val) pairs; the result ends in
-// keys/vals.  tmp_* hold n items, hist holds sort_hist_words(n) int32.
-int64_t tkc_sort_hist_words(int32_t n);
-int tkc_sort_pairs(uint32_t* keys, int32_t* vals, uint32_t* tmp_keys, int32_t* tmp_vals,
-                   int32_t n, int32_t* hist, uint32_t* mask_dev, uint32_t* mask_host,
-                   hipStream_t s);
-// the same with 8-bit digits (the processing order): hist holds
-// tkc_sort8_hist_words(n) int32
+// keys/vals.  tmp_* hold n items, hist holds tkc_sort8_hist_words(n) int32.
 int64_t tkc_sort8_hist_words(int32_t n);
-// known_mask: the OR and AND of the keys already in host memory (from
-// tkc_sort_mask and a host wait), else null: the sort finds them itself
+// known_mask: the OR of the keys and of their complements already in host
+// memory (from tkc_sort_mask and a host wait), else null: the sort finds them
 int tkc_sort_pairs8(uint32_t* keys, int32_t* vals, uint32_t* tmp_keys, int32_t* tmp_vals,
                     int32_t n, int32_t* hist, uint32_t* mask_dev, uint32_t* mask_host,
                     hipStream_t s, const uint32_t* known_mask = nullptr);
-// queue the OR and AND of n keys into mask_dev[0..1] and their copy to the
-// pinned mask_host[0..1] (no wait)
+// queue the OR of n keys and of their complements into mask_dev[0..1] and their
+// copy to the pinned mask_host[0..1] (no wait; nothing where n needs no mask)
 int tkc_sort_mask(const uint32_t* keys, int32_t n, uint32_t* mask_dev, uint32_t* mask_host, hipStream_t s);
 
 // k_topk.hip
@@ -201,7 +195,9 @@ struct TieBuf {
     int32_t* I;
     int32_t cap;
 };
-int tkc_launch_topk_init(DevTopk t, int32_t k, hipStream_t s, const TieBuf* tb = nullptr);
+// (and clears `words` counters and the hybrid's three state words, if given)
+int tkc_launch_topk_init(DevTopk t, int32_t k, hipStream_t s, const TieBuf* tb = nullptr, int64_t* counters = nullptr,
+                         int32_t words = 0, int32_t* state3 = nullptr);
 
 // k_plain.hip: one source at a time on the whole GPU (cooperative kernel).
 struct PlainWork {

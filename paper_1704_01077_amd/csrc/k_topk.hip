@@ -3,7 +3,9 @@
 #include "engine.hpp"
 
 __global__ void k_topk_init(TopkState* st, int32_t k, int32_t ties, int32_t tcap, int64_t* tieS, int64_t* tieR,
-                            int32_t* tieI) {
+                            int32_t* tieI, int64_t* counters, int32_t words, int32_t* state3) {
+    for (int32_t i = threadIdx.x; i < words; i += blockDim.x) counters[i] = 0;
+    if (state3 && threadIdx.x < 3) state3[threadIdx.x] = 0;
     if (threadIdx.x == 0 && blockIdx.x == 0) {
         st->lock = 0;
         st->cnt = 0;
@@ -19,9 +21,10 @@ __global__ void k_topk_init(TopkState* st, int32_t k, int32_t ties, int32_t tcap
     }
 }
 
-int tkc_launch_topk_init(DevTopk t, int32_t k, hipStream_t s, const TieBuf* tb) {
+int tkc_launch_topk_init(DevTopk t, int32_t k, hipStream_t s, const TieBuf* tb, int64_t* counters, int32_t words,
+                         int32_t* state3) {
     hipLaunchKernelGGL(k_topk_init, dim3(1), dim3(64), 0, s, t.st, k, tb ? 1 : 0, tb ? tb->cap : 0,
-                       tb ? tb->S : nullptr, tb ? tb->R : nullptr, tb ? tb->I : nullptr);
+                       tb ? tb->S : nullptr, tb ? tb->R : nullptr, tb ? tb->I : nullptr, counters, words, state3);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
