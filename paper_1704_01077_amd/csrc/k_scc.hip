@@ -907,7 +907,6 @@ int tkc_device_alpha_omega(const DevGraph& g, int64_t* alpha, int64_t* omega, in
     const int gb = nblk(n);
     const int64_t mx = m > n ? m : n;
     const int64_t words_scan = mx / (SCAN_T * SCAN_I) + 2;
-    const int64_t hist_words = tkc_sort8_hist_words((int32_t)mx);
     Scratch sc;
     // scratch: vertex arrays, component arrays, arc arrays, scan and sort
     // state; the same sequence of takes sizes it (base null) and lays it out
@@ -944,7 +943,6 @@ int tkc_device_alpha_omega(const DevGraph& g, int64_t* alpha, int64_t* omega, in
     int32_t* hdst = nullptr;
     int32_t *ccnt = nullptr, *cfirst = nullptr;   // heavy-vertex chunks
     int32_t* bsum = nullptr;
-    int32_t* hist = nullptr;
     int32_t* small = nullptr;
     auto layout = [&](char* base) -> size_t {
         sc.p = base;
@@ -984,7 +982,6 @@ int tkc_device_alpha_omega(const DevGraph& g, int64_t* alpha, int64_t* omega, in
         ccnt = sc.take<int32_t>((int64_t)g.nchunks + 1);
         cfirst = sc.take<int32_t>((int64_t)g.nchunks + 1);
         bsum = sc.take<int32_t>(words_scan);
-        hist = sc.take<int32_t>(hist_words);
         small = sc.take<int32_t>(256);
         return (size_t)(sc.p - base);
     };
@@ -1180,11 +1177,13 @@ int tkc_device_alpha_omega(const DevGraph& g, int64_t* alpha, int64_t* omega, in
             if (g.nheavy)
                 hipLaunchKernelGGL(k_dag_chunk_pairs, dim3(wblk(g.nchunks)), dim3(SB), 0, s, g.nchunks, g.ch_beg,
                                    g.ch_end, g.ch_vtx, g.ci, comp, cnt, ccnt, cfirst, key, val);
-            // by target, then (stable) by source
-            STEP_OK(tkc_sort_pairs8(key, val, tkey, tval, E, hist, smask, pin_mask, s));
+            // by target, then (stable) by source.  A sort's digit counts (n / 8 +
+            // 528 words, none up to 4,096 items) take an array of at least as
+            // many items that is free meanwhile
+            STEP_OK(tkc_sort_pairs8(key, val, tkey, tval, E, flag, smask, pin_mask, s));
             DEV_OK(hipMemcpyAsync(tkey, val, 4 * (size_t)E, hipMemcpyDeviceToDevice, s));
             DEV_OK(hipMemcpyAsync(tval, key, 4 * (size_t)E, hipMemcpyDeviceToDevice, s));
-            STEP_OK(tkc_sort_pairs8(tkey, tval, key, val, E, hist, smask, pin_mask, s));
+            STEP_OK(tkc_sort_pairs8(tkey, tval, key, val, E, flag, smask, pin_mask, s));
             hipLaunchKernelGGL(k_dag_uniq, dim3(nblk(E)), dim3(SB), 0, s, (int64_t)E, tkey, tval, flag);
             DEV_OK(hipMemcpyAsync(pos, flag, 4 * (size_t)E, hipMemcpyDeviceToDevice, s));
             STEP_OK(scan(pos, E, bsum, small + 5, s));
@@ -1238,14 +1237,14 @@ int tkc_device_alpha_omega(const DevGraph& g, int64_t* alpha, int64_t* omega, in
             uint32_t* ck = (uint32_t*)in_rem;   // vertex arrays free from here on
             int32_t* byh = out_rem;
             hipLaunchKernelGGL(k_comp_hkey, dim3(nblk(nc)), dim3(SB), 0, s, nc, hgt, hmax, ck, byh);
-            STEP_OK(tkc_sort_pairs8(ck, byh, (uint32_t*)list, next, nc, hist, smask, pin_mask, s));
+            STEP_OK(tkc_sort_pairs8(ck, byh, (uint32_t*)list, next, nc, color, smask, pin_mask, s));
             hipLaunchKernelGGL(k_topo_of, dim3(nblk(nc)), dim3(SB), 0, s, nc, byh, topo);
             DEV_OK(hipMemsetAsync(cstart, 0xff, 4 * ((size_t)hmax + 2), s));
             DEV_OK(hipMemsetAsync(astart, 0xff, 4 * ((size_t)hmax + 2), s));
             hipLaunchKernelGGL(k_bucket_starts, dim3(nblk(nc)), dim3(SB), 0, s, nc, ck, cstart);
             if (U > 0) {
                 hipLaunchKernelGGL(k_arc_hkey, dim3(nblk(U)), dim3(SB), 0, s, U, asrc, hgt, hmax, tkey, tval);
-                STEP_OK(tkc_sort_pairs8(tkey, tval, key, val, U, hist, smask, pin_mask, s));
+                STEP_OK(tkc_sort_pairs8(tkey, tval, key, val, U, flag, smask, pin_mask, s));
                 hipLaunchKernelGGL(k_arc_gather, dim3(nblk(U)), dim3(SB), 0, s, U, tval, asrc, adst, hsrc, hdst);
                 hipLaunchKernelGGL(k_bucket_starts, dim3(nblk(U)), dim3(SB), 0, s, U, tkey, astart);
             }
