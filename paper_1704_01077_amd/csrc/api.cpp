@@ -86,6 +86,7 @@ static size_t ws_items(Workspace& ws, const WsShape& sh, std::vector<WsItem>& it
         {(void**)&ws.nbflags, n, false}, {(void**)&ws.small, 8192, false},
         // NB: heavy chunks' partial sums, or the tail rounds' list (n / 64 int32)
         {(void**)&ws.nbpart, std::max(8 * (size_t)sh.nchunks, 4 * (n / 64)) + 8, false},
+        {(void**)&ws.nbhcnt, 4 * (size_t)sh.nchunks + 8, true},
         // read back together: keep stats .. tI adjacent and in this order
         {(void**)&ws.stats, 8 * 4 * ST_COUNT, false}, {(void**)&ws.tstate, 4096, false},
         {(void**)&ws.tS, 8 * (size_t)sh.kcap, false}, {(void**)&ws.tR, 8 * (size_t)sh.kcap, false},
@@ -207,7 +208,7 @@ extern "C" int tkc_ctx_create(int device, void* hip_stream, tkc_ctx** out) {
     bool ok = hipEventCreate(&c->ev0) == hipSuccess && hipEventCreate(&c->ev1) == hipSuccess &&
               hipEventCreate(&c->evm) == hipSuccess;
     for (auto& e : c->evq) ok = ok && hipEventCreate(&e) == hipSuccess;
-    ok = ok && hipHostMalloc((void**)&c->pinned, 4096, hipHostMallocDefault) == hipSuccess;
+    ok = ok && hipHostMalloc((void**)&c->pinned, 8192, hipHostMallocDefault) == hipSuccess;
     if (!ok) {
         hipGetLastError();
         tkc_ctx_destroy(c);
@@ -641,7 +642,7 @@ int tkc_step_bounds(tkc_ctx* c, tkc_graph* g, Workspace& ws, bool nb, int32_t* r
             return tkc_sort_mask(ws.key, n, (uint32_t*)ws.mask, mask_pin, s);
         };
         int r = tkc_launch_nb(dg, ws.alpha, ws.omega, ws.gbuf, ws.nbsum, ws.nbvis, ws.nbflags, ws.lnum, ws.lden,
-                              ws.nbpart, nfin_dev, (int32_t*)c->pinned, s, harm ? ws.nbhub : nullptr, &fin, &keyed);
+                              ws.nbpart, ws.nbhcnt, nfin_dev, (int32_t*)c->pinned + 1024, s, harm ? ws.nbhub : nullptr, &fin, &keyed);
         if (r < 0) return tkc_fail(TKC_EDEVICE, "NB bound kernels failed");
         if (rounds) *rounds = r;
         if (!keyed) {

@@ -145,7 +145,8 @@ int tkc_launch_own(const DevGraph& g, uint8_t* own, hipStream_t s);
 int tkc_launch_cc(const DevGraph& g, int32_t* parent, int64_t* size, int64_t* alpha, int64_t* omega,
                   uint8_t* in_giant, int32_t* sample_host, hipStream_t s);
 // gbuf holds 3n int64 and then 2n int32; partial holds nchunks uint64 and
-// at least n/64 int32; nfin_dev the finish counters (1,057 int32).  Returns
+// at least n/64 int32; hcnt nchunks int32, zero before and after; nfin_dev the
+// finish counters (1,057 int32), nfin_host 4 KiB of pinned memory.  Returns
 // the number of rounds, -1 on error.  hub (n doubles, may be null): also
 // the walk-count upper bound on the harmonic centrality
 // fin (may be null): the caller's work on the final bounds (order keys and
@@ -153,7 +154,7 @@ int tkc_launch_cc(const DevGraph& g, int32_t* parent, int64_t* size, int64_t* al
 // host wait covers both; *fin_done says whether the rounds ended at such a
 // check (else the bounds changed after fin ran, and the caller runs it again)
 int tkc_launch_nb(const DevGraph& g, const int64_t* alpha, const int64_t* omega, int64_t* gbuf, int64_t* sum,
-                  int64_t* vis, uint8_t* flags, int64_t* num, int64_t* den, uint64_t* partial,
+                  int64_t* vis, uint8_t* flags, int64_t* num, int64_t* den, uint64_t* partial, int32_t* hcnt,
                   int32_t* nfin_dev, int32_t* nfin_host, hipStream_t s, double* hub = nullptr,
                   const std::function<int()>* fin = nullptr, bool* fin_done = nullptr);
 // harmonic centrality bounds and order keys: from hub (walk counts) when

@@ -42,7 +42,8 @@ struct Workspace {
     int64_t* csize;
     int64_t *gbuf, *nbsum, *nbvis;
     double* nbhub;
-    uint64_t* nbpart;
+    uint64_t* nbpart;    int32_t* nbhcnt;
+
     uint8_t* nbflags;
     void* small;
     void* tstate;
@@ -85,7 +86,7 @@ struct tkc_ctx {
     // between two launches timed as one span (the seed batch and the swarm)
     hipEvent_t evm = nullptr;
     bool ring_ok = true;      // a query may take the ring engine's buffers (servers: they fit the budget)
-    void* pinned = nullptr;   // 4 KiB of pinned host memory for small readbacks
+    void* pinned = nullptr;   // 8 KiB of pinned host memory for small readbacks (the upper half: NB's finish counts)
 };
 
 struct tkc_graph {

@@ -366,12 +366,13 @@ struct NBState {
 // Finish counts: one add per workgroup, into NB_NCTR counters 128 B apart.
 // Adds to one address are done one after another at the cache; with one
 // add per wave on a single counter, a round in which most waves finish a
-// vertex queued ~16K adds there and took twice as long.  k_nb_total sums
-// the counters for the host check.
+// vertex queued ~16K adds there and took twice as long.  The host sums the
+// counters it copied.
 #define NB_NCTR 32
 #define NB_CTR_WORDS 32
 #define NB_TOTAL_WORD (NB_NCTR * NB_CTR_WORDS)
 #define NB_TAILCNT_WORD (NB_TOTAL_WORD + 32)
+#define NB_WORDS (NB_TAILCNT_WORD + 1)
 // every thread of the block calls it; lds holds one int per wave
 TKC_DEV void nb_count(bool fin, int32_t* nfin, int32_t* lds) {
     int tot;
@@ -384,18 +385,6 @@ TKC_DEV void nb_count(bool fin, int32_t* nfin, int32_t* lds) {
         if (t) fadd_rlx(nfin + (blockIdx.x % NB_NCTR) * NB_CTR_WORDS, t);
     }
 }
-// one wave: the counters' sum into nfin[NB_TOTAL_WORD]; it also clears the
-// tail list's count, which a collect after the check starts from
-__global__ void k_nb_total(int32_t* nfin) {
-    int32_t v = lane_id() < NB_NCTR ? nfin[lane_id() * NB_CTR_WORDS] : 0;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    if (lane_id() == 0) {
-        nfin[NB_TOTAL_WORD] = v;
-        nfin[NB_TAILCNT_WORD] = 0;
-    }
-}
-
 // Harmonic centrality from the same counts: level k takes min(gamma_k,
 // omega - placed) vertices (placed = the visited count, s included), the
 // closest placement the counts allow, and adds that many times 1/k.  Called
@@ -495,7 +484,8 @@ TKC_DEV void nb_finish_vertex(int32_t s, uint64_t acc, int64_t k, int32_t d, con
 template <bool DIRECTED, int LPV, typename G>
 __global__ void k_nb_round(int32_t n, const int32_t* __restrict__ rp, const int32_t* __restrict__ ci,
                            const int32_t* __restrict__ deg, const int32_t* __restrict__ ch_beg,
-                           const int32_t* __restrict__ ch_end, int32_t nchunks, int32_t nlight_blocks,
+                           const int32_t* __restrict__ ch_end, const int32_t* __restrict__ ch_vtx, int32_t* hcnt,
+                           int32_t nchunks, int32_t nlight_blocks,
                            int64_t k, const G* __restrict__ g1, const int64_t* __restrict__ g1x,
                            const int64_t* __restrict__ g2,
                            int64_t* __restrict__ gk, const int64_t* __restrict__ alpha,
@@ -579,44 +569,51 @@ __global__ void k_nb_round(int32_t n, const int32_t* __restrict__ rp, const int3
         __shared__ int32_t lds[16];
         nb_count(fin, nfin, lds);   // the branch is uniform over the workgroup
     } else {
-        // arcs of heavy vertices: one wave per chunk, saturating partial sum
-        int32_t c = ((blockIdx.x - nlight_blocks) * blockDim.x + threadIdx.x) >> 6;
-        if (c >= nchunks) return;   // wave-uniform
-        // (the exact 64-bit counts: a 512-arc chunk meets a capped count
-        // far more often than a light row)
-        uint64_t acc = 0;
-        for (int32_t e = ch_beg[c] + lane_id(); e < ch_end[c]; e += 64) {
-            acc += (uint64_t)g1x[ci[e]];
-            if (acc > (uint64_t)NB_INF) acc = NB_INF;
-        }
+        // arcs of heavy vertices: one wave per chunk, saturating partial sum;
+        // the wave that completes a vertex (a counter at its first chunk)
+        // adds its chunks' sums and finishes it.  The sums are stored and read
+        // past the caches and each store has ended before its wave counts, so
+        // no fence is needed.  (With a launch of its own for the finishing a
+        // round took one launch more: 275 -> 265 us a query on 2,000 vertices.)
+        const int32_t c = ((blockIdx.x - nlight_blocks) * blockDim.x + threadIdx.x) >> 6;
+        bool fin = false;
+        if (c < nchunks) {   // wave-uniform
+            // (the exact 64-bit counts: a 512-arc chunk meets a capped count
+            // far more often than a light row)
+            uint64_t acc = 0;
+            for (int32_t e = ch_beg[c] + lane_id(); e < ch_end[c]; e += 64) {
+                acc += (uint64_t)g1x[ci[e]];
+                if (acc > (uint64_t)NB_INF) acc = NB_INF;
+            }
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            acc += __shfl_xor(acc, o, 64);
-            if (acc > (uint64_t)NB_INF) acc = NB_INF;
+            for (int o = 32; o > 0; o >>= 1) {
+                acc += __shfl_xor(acc, o, 64);
+                if (acc > (uint64_t)NB_INF) acc = NB_INF;
+            }
+            if (lane_id() == 0) {
+                const int32_t s = ch_vtx[c], d = deg[s];
+                const int32_t first = c - (ch_beg[c] - rp[s]) / CHUNK_ARCS, nc = (d + CHUNK_ARCS - 1) / CHUNK_ARCS;
+                bool last = nc == 1;
+                if (!last) {
+                    st_rlx(&partial[c], acc);
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+                    __builtin_amdgcn_s_waitcnt(0x0F70);
+                    last = fadd_rlx(&hcnt[first], 1) == nc - 1;
+                    if (last) {
+                        st_rlx(&hcnt[first], 0);
+                        acc = 0;
+                        for (int32_t q = first; q < first + nc; q++) {
+                            acc += ld_rlx(&partial[q]);
+                            if (acc > (uint64_t)NB_INF) acc = NB_INF;
+                        }
+                    }
+                }
+                if (last) nb_finish_vertex<DIRECTED>(s, acc, k, d, g2, gk, alpha, omega, st, adv != 0, &fin);
+            }
         }
-        if (lane_id() == 0) partial[c] = acc;
+        __shared__ int32_t lds[16];
+        nb_count(fin, nfin, lds);
     }
-}
-// heavy vertices: sum their chunks' partials and finish (one thread each)
-template <bool DIRECTED>
-__global__ void k_nb_heavy(int32_t nheavy, const int32_t* __restrict__ heavy, const int32_t* __restrict__ hcb,
-                           const uint64_t* __restrict__ partial, const int32_t* __restrict__ deg, int64_t k,
-                           const int64_t* __restrict__ g2, int64_t* __restrict__ gk,
-                           const int64_t* __restrict__ alpha, const int64_t* __restrict__ omega, NBState st,
-                           int32_t* nfin, int32_t adv) {
-    int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    bool fin = false;
-    if (i < nheavy) {
-        uint64_t acc = 0;
-        for (int32_t c = hcb[i]; c < hcb[i + 1]; c++) {
-            acc += partial[c];
-            if (acc > (uint64_t)NB_INF) acc = NB_INF;
-        }
-        int32_t s = heavy[i];
-        nb_finish_vertex<DIRECTED>(s, acc, k, deg[s], g2, gk, alpha, omega, st, adv != 0, &fin);
-    }
-    __shared__ int32_t lds[16];
-    nb_count(fin, nfin, lds);
 }
 
 // The open (unfinished) vertices, in no particular order: the tail round
@@ -855,20 +852,20 @@ static void launch_nb_round(int lpv, dim3 grid, hipStream_t s, A... args) {
 // NB bound: returns the number of rounds, -1 on error.  gbuf holds 3*n int64
 // and then 2*n int32;
 // partial holds the heavy chunks' partial sums and also at least
-// n / NB_TAIL_DIV int32; nfin_dev holds NB_TAILCNT_WORD + 1 int32 (the
-// finish counters, their total, the tail list's count).
+// n / NB_TAIL_DIV int32; hcnt counts each heavy vertex's finished chunks at its
+// first one; nfin_dev holds NB_WORDS int32 (the finish counters, the tail
+// list's count).
 int tkc_launch_nb(const DevGraph& g, const int64_t* alpha, const int64_t* omega, int64_t* gbuf, int64_t* sum,
-                  int64_t* vis, uint8_t* flags, int64_t* num, int64_t* den, uint64_t* partial,
+                  int64_t* vis, uint8_t* flags, int64_t* num, int64_t* den, uint64_t* partial, int32_t* hcnt,
                   int32_t* nfin_dev, int32_t* nfin_host, hipStream_t s, double* hub,
                   const std::function<int()>* fin, bool* fin_done) {
     int32_t n = g.n;
     if (fin_done) *fin_done = false;
     int nl = nblk(n, 256);
     int nc = nblk((int64_t)g.nchunks * 64, 256);
-    int nhb = nblk(g.nheavy, 256);
     NBState st{sum, vis, flags, num, den, hub, nullptr};
     int64_t* buf[3] = {gbuf, gbuf + n, gbuf + 2 * (int64_t)n};
-    hipMemsetAsync(nfin_dev, 0, sizeof(int32_t) * NB_TOTAL_WORD, s);
+    hipMemsetAsync(nfin_dev, 0, sizeof(int32_t) * NB_WORDS, s);
     // gamma_0 -> buf[0], gamma_1 -> buf[1]
     hipLaunchKernelGGL(k_nb_init, dim3(nl), dim3(256), 0, s, n, g.deg, alpha, omega, buf[0], buf[1],
                        st, nfin_dev);
@@ -892,29 +889,21 @@ int tkc_launch_nb(const DevGraph& g, const int64_t* alpha, const int64_t* omega,
             rs.c32 = c32[lv & 1];
             const int32_t* g1c = lv == 2 ? g.deg : c32[(lv - 1) & 1];
             if (g.directed)
-                launch_nb_round<true, int32_t>(lpv, dim3(nlr + nc), s, n, g.rp, g.ci, g.deg, g.ch_beg, g.ch_end,
+                launch_nb_round<true, int32_t>(lpv, dim3(nlr + nc), s, n, g.rp, g.ci, g.deg, g.ch_beg, g.ch_end, g.ch_vtx, hcnt,
                                                g.nchunks, nlr, lv, g1c, (const int64_t*)g1, (const int64_t*)g2, gk,
                                                alpha, omega, rs, partial, nfin_dev, adv);
             else
-                launch_nb_round<false, int32_t>(lpv, dim3(nlr + nc), s, n, g.rp, g.ci, g.deg, g.ch_beg, g.ch_end,
+                launch_nb_round<false, int32_t>(lpv, dim3(nlr + nc), s, n, g.rp, g.ci, g.deg, g.ch_beg, g.ch_end, g.ch_vtx, hcnt,
                                                 g.nchunks, nlr, lv, g1c, (const int64_t*)g1, (const int64_t*)g2, gk,
                                                 alpha, omega, rs, partial, nfin_dev, adv);
         } else if (g.directed) {
-            launch_nb_round<true, int64_t>(lpv, dim3(nlr + nc), s, n, g.rp, g.ci, g.deg, g.ch_beg, g.ch_end,
+            launch_nb_round<true, int64_t>(lpv, dim3(nlr + nc), s, n, g.rp, g.ci, g.deg, g.ch_beg, g.ch_end, g.ch_vtx, hcnt,
                                            g.nchunks, nlr, lv, (const int64_t*)g1, (const int64_t*)g1,
                                            (const int64_t*)g2, gk, alpha, omega, rs, partial, nfin_dev, adv);
         } else {
-            launch_nb_round<false, int64_t>(lpv, dim3(nlr + nc), s, n, g.rp, g.ci, g.deg, g.ch_beg, g.ch_end,
+            launch_nb_round<false, int64_t>(lpv, dim3(nlr + nc), s, n, g.rp, g.ci, g.deg, g.ch_beg, g.ch_end, g.ch_vtx, hcnt,
                                             g.nchunks, nlr, lv, (const int64_t*)g1, (const int64_t*)g1,
                                             (const int64_t*)g2, gk, alpha, omega, rs, partial, nfin_dev, adv);
-        }
-        if (g.nheavy) {
-            if (g.directed)
-                hipLaunchKernelGGL(k_nb_heavy<true>, dim3(nhb), dim3(256), 0, s, g.nheavy, g.heavy, g.hcb, partial,
-                                   g.deg, lv, (const int64_t*)g2, gk, alpha, omega, rs, nfin_dev, adv);
-            else
-                hipLaunchKernelGGL(k_nb_heavy<false>, dim3(nhb), dim3(256), 0, s, g.nheavy, g.heavy, g.hcb,
-                                   partial, g.deg, lv, (const int64_t*)g2, gk, alpha, omega, rs, nfin_dev, adv);
         }
     };
     // the finish count after the rounds queued so far; with `ahead`, round k
@@ -928,9 +917,8 @@ int tkc_launch_nb(const DevGraph& g, const int64_t* alpha, const int64_t* omega,
         ~EventGuard() { hipEventDestroy(e); }
     } ev_guard{ev_copy};
     auto check = [&](bool ahead) -> bool {
-        hipLaunchKernelGGL(k_nb_total, dim3(1), dim3(64), 0, s, nfin_dev);
         if (hipGetLastError() != hipSuccess) return false;
-        if (hipMemcpyAsync(nfin_host, nfin_dev + NB_TOTAL_WORD, sizeof(int32_t), hipMemcpyDeviceToHost, s) !=
+        if (hipMemcpyAsync(nfin_host, nfin_dev, sizeof(int32_t) * NB_TOTAL_WORD, hipMemcpyDeviceToHost, s) !=
             hipSuccess)
             return false;
         if (ahead) {
@@ -941,7 +929,8 @@ int tkc_launch_nb(const DevGraph& g, const int64_t* alpha, const int64_t* omega,
         } else if (hipStreamSynchronize(s) != hipSuccess) {
             return false;
         }
-        done = *nfin_host;
+        done = 0;
+        for (int i = 0; i < NB_NCTR; i++) done += nfin_host[i * NB_CTR_WORDS];
         return true;
     };
     // tail rounds: once at most n / NB_TAIL_DIV vertices are open, a round
@@ -954,12 +943,13 @@ int tkc_launch_nb(const DevGraph& g, const int64_t* alpha, const int64_t* omega,
     int32_t* tail_list = (int32_t*)partial;
     int32_t* tail_cnt = nfin_dev + NB_TAILCNT_WORD;
     bool checked = false;
+    int tails = 0;   // tail rounds so far
     int ahead = 0;   // rounds of the current pair already queued by a check
     while (k <= kmax) {
         const int32_t open = n - done;   // may count some that a queued round finished
         if (checked && open <= tail_at) {
             ahead = 0;
-            // tail_cnt was cleared by the check's k_nb_total
+            if (tails++ && hipMemsetAsync(tail_cnt, 0, sizeof(int32_t), s) != hipSuccess) return -1;
             hipLaunchKernelGGL(k_nb_collect, dim3(nblk(n, 1024)), dim3(1024), 0, s, n, (const uint8_t*)flags,
                                tail_cap, tail_list, tail_cnt);
             const int nt = nblk((int64_t)open * 64, 256);
