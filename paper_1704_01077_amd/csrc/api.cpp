@@ -992,7 +992,24 @@ int tkc_run_query(tkc_ctx* c, tkc_graph* g, int32_t k, int32_t variant, int32_t 
     int grid = 0;
     // the hybrid's per-workgroup engine has no level-based path
     if (lb && mode == TKC_HYBRID) mode = TKC_BATCHED;
-    if (mode == TKC_PLAIN) {
+    // one search at a time on a small graph: one workgroup of the per-workgroup
+    // engine (its queue holds every vertex, so it defers nothing)
+    if (mode == TKC_PLAIN && !lb && max_searches <= 0 && ws.shape.qcap >= n && tkc_plain_small(dg)) {
+        EngineTimer tm(c, &ms_eng[0], &nl_eng[0]);
+        int32_t* small = (int32_t*)ws.small;
+        SwarmWork sw{};
+        sw.queue = ws.s_queue;
+        sw.deferred = ws.s_deferred;
+        sw.ndeferred = small + 4;
+        sw.cursor = small + 5;
+        sw.stop = small + 6;
+        sw.nblocks = 1;
+        sw.qcap = ws.shape.qcap;
+        if (tkc_launch_swarm(dg, rcv, ov, bv, tk, sw, st_plain, 0, c->tune, s))
+            return tkc_fail(TKC_EDEVICE, "plain engine launch failed: %s", hipGetErrorString(hipGetLastError()));
+        if ((rc = tm.done(readback))) return rc;
+        rb_ready = true;
+    } else if (mode == TKC_PLAIN) {
         EngineTimer tm(c, &ms_eng[0], &nl_eng[0]);
         if (tkc_launch_plain(dg, rcv, ov, bv, tk, plain_view(ws), st_plain, nullptr, 0, lbl, c->tune, s, &grid,
                              max_searches))

@@ -285,6 +285,7 @@ int tkc_launch_swarm(const DevGraph& g, DevReach rc, OrderView ov, BoundsView bv
                      hipStream_t s);
 int tkc_swarm_max_blocks(int block);
 bool tkc_swarm_fits(const DevGraph& g);
+bool tkc_plain_small(const DevGraph& g);
 
 // k_ring.hip: one search per workgroup, visited set in LDS (undirected graphs
 // of low degree): cut ones (lb_mode 0), complete ones with level-based updates

@@ -286,6 +286,15 @@ bool tkc_swarm_fits(const DevGraph& g) {
     return g.n + (g.directed ? (int64_t)g.m : (int64_t)g.m / 2) <= TKC_SWARM_SIZE;
 }
 
+// Plain mode on a small graph: this engine with one workgroup takes the same
+// searches in the same order (same counters), and a level costs it a few
+// workgroup barriers where the grid of the plain engine pays three grid
+// barriers.  Whole queries, top 10: social networks of 2,000 vertices and 2 10^4
+// edges 8.5 -> 2.0 ms, web graphs of 4,000 and 4 10^4 arcs 39.6 -> 7.3, of 8,000
+// and 8 10^4 43 -> 13; the line lies where the whole chip begins to pay for
+// complete searches (16,000 and 1.6 10^5, top 1: 1.16 -> 1.79).
+bool tkc_plain_small(const DevGraph& g) { return g.n + (int64_t)g.m <= (1 << 17); }
+
 int tkc_swarm_max_blocks(int block) {
     (void)block;
     const int cus = tkc_cu_count();

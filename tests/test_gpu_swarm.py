@@ -1,6 +1,6 @@
 """Per-workgroup engine (visited set in LDS) against the oracle: widths around
 its bitmap's words, searches that overflow their queue, and graphs on both
-sides of the size up to which it is used."""
+sides of the size up to which it is used, alone (plain mode) and many at once."""
 import functools
 
 import numpy as np
@@ -52,13 +52,15 @@ def test_swarm_words(ctx, n, qcap):
         dg = tkc.Graph.from_graphgen(ctx, g)
         for k in (1, 7, min(n, 300)):
             for variant in ("nbcut", "degcut"):
-                print("swarm", n, qcap, k, variant, flush=True)
-                got = tkc.topk_closeness(dg, k, variant, "hybrid")
-                for a, b in zip(got[:4], want):
-                    assert np.array_equal(a, b[:k])
-            hv, hh = tkc.topk_harmonic(dg, k, "nbcut", "hybrid")[:2]
+                for mode in ("hybrid", "plain"):
+                    print("swarm", n, qcap, k, variant, mode, flush=True)
+                    got = tkc.topk_closeness(dg, k, variant, mode)
+                    for a, b in zip(got[:4], want):
+                        assert np.array_equal(a, b[:k])
             ids = oracle.harmonic_topk(h, k)
-            assert np.array_equal(hv, ids) and np.array_equal(hh, h[ids])
+            for mode in ("hybrid", "plain"):
+                hv, hh = tkc.topk_harmonic(dg, k, "nbcut", mode)[:2]
+                assert np.array_equal(hv, ids) and np.array_equal(hh, h[ids])
         dg.free()
     finally:
         ctx.tune(**keep)
@@ -77,4 +79,22 @@ def test_swarm_size_line(ctx, directed):
         for x, y in zip(a[:4], b[:4]):
             assert np.array_equal(x, y)
         assert b[4]["mode_used"] == 2
+        dg.free()
+
+
+def test_swarm_plain_line(ctx):
+    """Plain mode on both sides of 2^17 vertices and arcs: the same searches
+    (their counters too) and the same answer as with a search cap, which only
+    the plain engine has."""
+    for arcs in (110000, 140000):
+        g = graph(9000, arcs, True)
+        assert (g.n + len(g.edges) <= 1 << 17) == (arcs == 110000)
+        dg = tkc.Graph.from_graphgen(ctx, g)
+        a = tkc.topk_closeness(dg, 5, "nbcut", "plain")
+        done, b, st = tkc.topk_closeness_budget(dg, 5, "nbcut", 10**6)
+        assert done
+        for x, y in zip(a[:4], b):
+            assert np.array_equal(x, y)
+        for key in ("bfs_started", "bfs_exact", "bfs_cut", "skipped", "m_vis", "max_level", "mode_used"):
+            assert a[4][key] == st[key], key
         dg.free()
