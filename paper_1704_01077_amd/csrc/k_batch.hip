@@ -731,7 +731,7 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
         bool bu = false;
         int64_t tslot = -1;
         int64_t mvis = 0, bytes = 0;
-        int64_t my_scan = 0;   // in-arcs this thread scanned in pull steps (traffic count)
+        int64_t my_scan = 0;   // words of in-arcs this thread scanned in pull steps (traffic count)
         for (;;) {
             // ------------------------------------ per-lane control (replicated)
             if (tid < MAXW) {
@@ -1174,7 +1174,7 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
             __syncthreads();
             if (lane == 0 && t) atomicAdd((unsigned long long*)&s_blk[0], (unsigned long long)t);
             __syncthreads();
-            if (tid == 0 && s_blk[0]) fadd_rlx(&stats[ST_BYTES], s_blk[0] * (int64_t)(4 + 8 * NW));
+            if (tid == 0 && s_blk[0]) fadd_rlx(&stats[ST_BYTES], s_blk[0] * (int64_t)(4 + 8 * NW) / NW);
         }
         // ----------------------------------------------------- batch results
         // The exact lanes' results go into their request's top k (Alg. 1),
