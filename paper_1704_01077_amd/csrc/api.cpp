@@ -995,7 +995,7 @@ int tkc_run_query(tkc_ctx* c, tkc_graph* g, int32_t k, int32_t variant, int32_t 
     // one search at a time on a small graph: one workgroup of the per-workgroup
     // engine (its queue holds every vertex, so it defers nothing)
     if (mode == TKC_PLAIN && !lb && max_searches <= 0 && ws.shape.qcap >= n && tkc_plain_small(dg)) {
-        EngineTimer tm(c, &ms_eng[0], &nl_eng[0]);
+        EngineTimer tm(c, &ms_eng[2], &nl_eng[2]);
         int32_t* small = (int32_t*)ws.small;
         SwarmWork sw{};
         sw.queue = ws.s_queue;
@@ -1005,7 +1005,7 @@ int tkc_run_query(tkc_ctx* c, tkc_graph* g, int32_t k, int32_t variant, int32_t 
         sw.stop = small + 6;
         sw.nblocks = 1;
         sw.qcap = ws.shape.qcap;
-        if (tkc_launch_swarm(dg, rcv, ov, bv, tk, sw, st_plain, 0, c->tune, s))
+        if (tkc_launch_swarm(dg, rcv, ov, bv, tk, sw, st_swarm, 0, c->tune, s))
             return tkc_fail(TKC_EDEVICE, "plain engine launch failed: %s", hipGetErrorString(hipGetLastError()));
         if ((rc = tm.done(readback))) return rc;
         rb_ready = true;
