@@ -176,7 +176,7 @@ __global__ void __launch_bounds__(RS8_THREADS) k_rs8_scatter(const uint32_t* __r
 // All of a small sort in one workgroup: every wave holds 256 consecutive items
 // in registers, ranks them digit by digit as the scatter above does, and the
 // workgroup trades them through LDS.  Seven launches and a host wait for the
-// keys' mask, about 60 us, become one of 10 us.
+// keys' mask, about 60 us, become one of 18 us at 2,000 keys.
 #define RSS_MAX 4096
 __global__ void __launch_bounds__(1024) k_rs_small(uint32_t* keys, int32_t* vals, int32_t n) {
     __shared__ uint32_t s_k[RSS_MAX];
