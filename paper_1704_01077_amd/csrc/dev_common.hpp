@@ -475,6 +475,15 @@ TKC_DEV void tie_keep(TopkState* st, int64_t S, int64_t r, int32_t id) {
     }
     st_rlx(&st->tcnt, t + 1);
 }
+// The list, the x ring and the state are only read and written past the caches
+// (agent-scope loads and stores), so holding the lock needs no cache
+// maintenance: an agent-scope acquire here would invalidate the XCD's L2 under
+// every search on it, a release write it back.  The calling wave waits for its
+// own stores before the next step can be seen.
+TKC_DEV void topk_stores_done() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
+}
 // Insert an exact result; the caller is one thread.  topk arrays hold the
 // min(k, inserted) best (S, r, id) in exact order.  Spins on st->lock.  In
 // all-ties mode every entry that leaves the top k, or is refused by it, is
@@ -513,20 +522,25 @@ TKC_DEV void topk_insert_locked(TopkState* st, XRec* ring, int64_t* tS, int64_t*
             st_rlx(&rc->S, ld_rlx(&tS[k - 1]));
             st_rlx(&rc->r, ld_rlx(&tR[k - 1]));
             st_rlx(&rc->id, st->ties ? (int64_t)0x7fffffff : (int64_t)ld_rlx(&tI[k - 1]));
-            st_rel(&st->seq, s);
+            topk_stores_done();
+            st_rlx(&st->seq, s);
         }
     }
     fadd_rlx(&st->n_inserts, (int64_t)1);
 }
 TKC_DEV bool topk_try_lock(TopkState* st) {
-    return ld_rlx(&st->lock) == 0 &&
-           __hip_atomic_exchange(&st->lock, 1, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) == 0;
+    const bool got = ld_rlx(&st->lock) == 0 &&
+                     __hip_atomic_exchange(&st->lock, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    return got;
 }
-TKC_DEV void topk_unlock(TopkState* st) { __hip_atomic_store(&st->lock, 0, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT); }
+TKC_DEV void topk_unlock(TopkState* st) {
+    topk_stores_done();
+    st_rlx(&st->lock, 0);
+}
 TKC_DEV void topk_insert(TopkState* st, XRec* ring, int64_t* tS, int64_t* tR, int32_t* tI,
                          int64_t S, int64_t r, int32_t id) {
-    while (__hip_atomic_exchange(&st->lock, 1, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) != 0)
-        __builtin_amdgcn_s_sleep(2);
+    while (!topk_try_lock(st)) __builtin_amdgcn_s_sleep(2);
     topk_insert_locked(st, ring, tS, tR, tI, S, r, id);
     topk_unlock(st);
 }
@@ -593,7 +607,8 @@ TKC_DEV void topk_insert_wave_locked(TopkState* st, XRec* ring, int64_t* tS, int
                 st_rlx(&rc->S, kS);
                 st_rlx(&rc->r, kR);
                 st_rlx(&rc->id, ties ? (int64_t)0x7fffffff : (int64_t)kI);
-                st_rel(&st->seq, q);
+                topk_stores_done();
+                st_rlx(&st->seq, q);
             }
         }
     }
