@@ -703,12 +703,6 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
             if (tid < MAXW) s_un[tid] = pre;
         }
         if (blockIdx.x == 0) {
-            if (tid < nsel) {
-                const int32_t v = s_v[tid];
-                // (a source list may name one vertex twice)
-                for_rlx(&vis[(int64_t)v * NW + (tid >> 6)], (uint64_t)1 << (tid & 63));
-                if (a.lb_mode) { a.w.lvl[(int64_t)v * W + tid] = 0; a.w.hist[tid] = 1; }
-            }
             // the next batch's counters: every workgroup has passed the barrier
             // behind the batch that used them last
             int64_t* nctr = a.w.ctr + ((batches + 1) & 1) * C_TOTAL;
@@ -838,6 +832,16 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
             }
             PHASE(0);
             if (D == 0) {
+                // The sources' own bits and levels, which nobody reads before
+                // this level's barrier.  Not earlier: a batch whose searches are
+                // all cut before level 0 passes no barrier between here and
+                // the clear at its end, and a bit set meanwhile could outlive it
+                if (blockIdx.x == 0 && tid < nsel) {
+                    const int32_t v = s_v[tid];
+                    // (a source list may name one vertex twice)
+                    for_rlx(&vis[(int64_t)v * NW + (tid >> 6)], (uint64_t)1 << (tid & 63));
+                    if (a.lb_mode) { a.w.lvl[(int64_t)v * W + tid] = 0; a.w.hist[tid] = 1; }
+                }
                 // a source's neighbours are all new to its search: one arc per
                 // lane, no visited or frontier word to read
                 for (int64_t un = gwave; un < units; un += nwaves) {
@@ -1444,8 +1448,9 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
                 }
             }
         }
-        // Clear the batch's words for the next batch.  Nothing reads them
-        // after the last level's barrier except the level-based update, so
+        // Clear the batch's words for the next batch.  Nothing reads or sets
+        // them after the last level's barrier except the level-based update (and
+        // a batch that ran no level has set none), so
         // only that (and the until_x decision) needs a barrier first; the
         // next batch's selection barrier orders the clear before its level 0
         // (and the kernel's end before the host reads anything)
