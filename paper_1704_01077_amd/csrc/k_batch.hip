@@ -842,8 +842,9 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
                     for_rlx(&vis[(int64_t)v * NW + (tid >> 6)], (uint64_t)1 << (tid & 63));
                     if (a.lb_mode) { a.w.lvl[(int64_t)v * W + tid] = 0; a.w.hist[tid] = 1; }
                 }
-                // a source's neighbours are all new to its search: one arc per
-                // lane, no visited or frontier word to read
+                // a source's neighbours are all new to its search (but for the
+                // source itself, in a graph uploaded unchecked with a loop): one
+                // arc per lane, no visited or frontier word to read
                 for (int64_t un = gwave; un < units; un += nwaves) {
                     int32_t l = 0, hi = nsel;   // the last source whose units start up to un
                     while (hi - l > 1) {
@@ -858,8 +859,8 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
                     Mask<NW> fr;
 #pragma unroll
                     for (int j = 0; j < NW; j++) fr.w[j] = 0;
-                    if (e < rp[u + 1]) {
-                        w = ci[e];
+                    if (e < rp[u + 1]) w = ci[e];
+                    if (e < rp[u + 1] && w != u) {
                         Mask<NW> nb;
 #pragma unroll
                         for (int j = 0; j < NW; j++) nb.w[j] = j == (l >> 6) ? (uint64_t)1 << (l & 63) : 0;
