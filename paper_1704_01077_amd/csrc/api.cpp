@@ -112,12 +112,6 @@ static size_t ws_items(Workspace& ws, const WsShape& sh, std::vector<WsItem>& it
         // per-workgroup engine
         {(void**)&ws.s_queue, 4 * (size_t)sh.qcap * (size_t)sh.swarm_blocks, false},
         {(void**)&ws.s_deferred, 4 * n, false},
-        // ring engine
-        {(void**)&ws.r_queue, sh.ring ? 4 * (size_t)RING_QSTRIDE(n) * (size_t)sh.ring : 8, false},
-        {(void**)&ws.r_off, sh.ring ? 4 * ring_lcap(sh.n) * (size_t)sh.ring : 8, false},
-        {(void**)&ws.r_lev, sh.ring ? 8 * ring_lcap(sh.n) * (size_t)sh.ring : 8, false},
-        {(void**)&ws.r_comb, sh.ring ? 8 * n : 8, false}, {(void**)&ws.r_dec, sh.ring ? 4 * words : 8, false},
-        {(void**)&ws.r_ell, sh.ring ? 16 * n : 8, false},
     };
     size_t total = 0;
     for (auto& it : items) total += align_up(it.bytes);
@@ -128,6 +122,66 @@ size_t tkc_ws_bytes(const WsShape& sh) {
     Workspace tmp;
     std::vector<WsItem> items;
     return ws_items(tmp, sh, items);
+}
+
+static size_t ring_items(Workspace& ws, int32_t n, int32_t blocks, std::vector<WsItem>& items) {
+    const size_t nn = (size_t)n, nb = (size_t)blocks;
+    items = {
+        {(void**)&ws.r_queue, 4 * (size_t)RING_QSTRIDE(n) * nb, false},
+        {(void**)&ws.r_off, 4 * ring_lcap(n) * nb, false}, {(void**)&ws.r_lev, 8 * ring_lcap(n) * nb, false},
+        {(void**)&ws.r_comb, 8 * nn, false}, {(void**)&ws.r_dec, 4 * ((nn + 31) / 32), false},
+        {(void**)&ws.r_ell, 16 * nn, false},
+    };
+    size_t total = 0;
+    for (auto& it : items) total += align_up(it.bytes);
+    return total;
+}
+
+size_t tkc_ring_bytes(int32_t n, int32_t blocks) {
+    Workspace tmp;
+    std::vector<WsItem> items;
+    return ring_items(tmp, n, blocks, items);
+}
+
+// the ring engine's buffers; TKC_ENOMEM leaves the workspace without any
+static int ring_reserve(tkc_ctx* ctx, Workspace& ws, int32_t n, int32_t blocks) {
+    if (ws.r_base && ws.r_n >= n && ws.r_blocks >= blocks) return TKC_OK;
+    std::vector<WsItem> items;
+    n = std::max(n, ws.r_n);
+    blocks = std::max(blocks, ws.r_blocks);
+    const size_t total = ring_items(ws, n, blocks, items);
+    if (ws.r_base) {
+        HIPCHK(hipStreamSynchronize(ctx->stream));
+        hipFree(ws.r_base);
+    }
+    ws.r_base = nullptr;
+    ws.r_bytes = 0;
+    ws.r_n = ws.r_blocks = 0;
+    void* base = nullptr;
+    if (hipMalloc(&base, total) != hipSuccess) {
+        hipGetLastError();
+        return tkc_fail(TKC_ENOMEM, "device allocation of %zu bytes failed", total);
+    }
+    ws.r_base = (char*)base;
+    ws.r_bytes = total;
+    ws.r_n = n;
+    ws.r_blocks = blocks;
+    size_t off = 0;
+    for (auto& it : items) {
+        *it.p = ws.r_base + off;
+        off += align_up(it.bytes);
+    }
+    return TKC_OK;
+}
+
+void tkc_ws_release(tkc_ctx* ctx, Workspace& ws) {
+    hipStreamSynchronize(ctx->stream);
+    if (ws.base) hipFree(ws.base);
+    if (ws.r_base) hipFree(ws.r_base);
+    ws.base = ws.r_base = nullptr;
+    ws.bytes = ws.r_bytes = 0;
+    ws.shape = WsShape();
+    ws.r_n = ws.r_blocks = 0;
 }
 
 std::mutex& tkc_coop_mutex() {
@@ -221,8 +275,7 @@ extern "C" int tkc_ctx_create(int device, void* hip_stream, tkc_ctx** out) {
 extern "C" int tkc_ctx_destroy(tkc_ctx* c) {
     if (!c) return TKC_OK;
     hipSetDevice(c->device);
-    hipStreamSynchronize(c->stream);
-    if (c->ws.base) hipFree(c->ws.base);
+    tkc_ws_release(c, c->ws);
     if (c->ws.trace) hipFree(c->ws.trace);
     if (c->ws.pin) hipHostFree(c->ws.pin);
     if (c->pinned) hipHostFree(c->pinned);
@@ -571,11 +624,6 @@ WsShape tkc_shape_for(const EngineTuning& t, tkc_graph* g, int32_t k, bool lb) {
     sh.nchunks = std::max(g->nchunks, g->rnchunks);
     sh.qcap = std::max(64, std::min(t.swarm_qcap, g->n));
     sh.swarm_blocks = std::max(1, tkc_swarm_max_blocks(256));
-    return sh;
-}
-
-WsShape tkc_shape_ring(WsShape sh, tkc_graph* g) {
-    sh.ring = tkc_ring_blocks(g->view());
     return sh;
 }
 
@@ -943,14 +991,15 @@ int tkc_run_query(tkc_ctx* c, tkc_graph* g, int32_t k, int32_t variant, int32_t 
     {
         WsShape sh = tkc_shape_for(c->tune, g, k, lb);
         sh.ties = ties;
+        rc = tkc_ws_reserve(c, ws, sh);
+        if (rc) return rc;
         // low-degree undirected graphs: the ring engine, unless its buffers do
         // not fit
-        const WsShape rs = !harm && mode != TKC_PLAIN && c->ring_ok ? tkc_shape_ring(sh, g) : sh;
-        rc = tkc_ws_reserve(c, ws, rs);
-        ring = rc == TKC_OK ? rs.ring : 0;
-        if (rc == TKC_ENOMEM && rs.ring) rc = tkc_ws_reserve(c, ws, sh);
+        if (!harm && mode != TKC_PLAIN && c->ring_ok) ring = tkc_ring_blocks(g->view());
+        if (ring) rc = ring_reserve(c, ws, n, ring);
+        if (rc == TKC_ENOMEM) ring = 0;
+        else if (rc) return rc;
     }
-    if (rc) return rc;
     int32_t rounds = 0;
     HIPCHK(hipEventRecord(c->evq[0], s));
     if (!harm && tkc_prep_cached(c, g, nb, &rounds)) {

@@ -14,18 +14,23 @@ struct WsShape {
     int32_t n = 0, W = 64, nw = 1, kcap = 1, lcap = 0, qcap = 0, swarm_blocks = 0, nchunks = 0;
     bool lb = false;
     bool ties = false;   // all-ties buffers
-    int32_t ring = 0;    // workgroups of the ring engine (0: not used)
     bool covers(const WsShape& o) const {
         return n >= o.n && nw >= o.nw && W >= o.W && kcap >= o.kcap && lcap >= o.lcap && qcap >= o.qcap &&
-               swarm_blocks >= o.swarm_blocks && nchunks >= o.nchunks && (lb || !o.lb) && (ties || !o.ties) &&
-               ring >= o.ring;
+               swarm_blocks >= o.swarm_blocks && nchunks >= o.nchunks && (lb || !o.lb) && (ties || !o.ties);
     }
 };
 
-// Every device buffer one query may touch; one allocation, grown on demand.
+// Every device buffer one query may touch, grown on demand: one allocation,
+// and one of the ring engine's own.  (The ring's buffers go by the largest
+// graph it takes, the others by the largest of all: in one allocation for the
+// shape of the last query, a street network and a larger social network asked
+// in turn made every call allocate and clear anew.)
 struct Workspace {
     char* base = nullptr;
     size_t bytes = 0;
+    char* r_base = nullptr;
+    size_t r_bytes = 0;
+    int32_t r_n = 0, r_blocks = 0;   // vertices and workgroups it was laid out for
     // pinned host copy of the span from `stats` to the end of `tI` (the
     // query's results and counters, read back with one copy)
     char* pin = nullptr;
@@ -42,8 +47,8 @@ struct Workspace {
     int64_t* csize;
     int64_t *gbuf, *nbsum, *nbvis;
     double* nbhub;
-    uint64_t* nbpart;    int32_t* nbhcnt;
-
+    uint64_t* nbpart;
+    int32_t* nbhcnt;
     uint8_t* nbflags;
     void* small;
     void* tstate;
@@ -194,8 +199,10 @@ bool tkc_prep_cached(tkc_ctx* c, tkc_graph* g, bool nb, int32_t* rounds);
 // build that cache from c's workspace after a query computed it
 int tkc_prep_store(tkc_ctx* c, tkc_graph* g, bool nb, int32_t rounds);
 WsShape tkc_shape_for(const EngineTuning& t, tkc_graph* g, int32_t k, bool lb);
-// the same with the ring engine's buffers where it applies to g
-WsShape tkc_shape_ring(WsShape sh, tkc_graph* g);
+// the ring engine's buffers for n vertices and that many workgroups
+size_t tkc_ring_bytes(int32_t n, int32_t blocks);
+// give a workspace's memory back (its pinned part stays)
+void tkc_ws_release(tkc_ctx* ctx, Workspace& ws);
 // the knobs a TKC_MODE_AUTO query on g runs with, given the context's own
 EngineTuning tkc_effective_tuning(const EngineTuning& ctx_tune, tkc_graph* g);
 size_t tkc_ws_bytes(const WsShape& sh);

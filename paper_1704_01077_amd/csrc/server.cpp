@@ -53,7 +53,7 @@ struct Request {
     std::vector<int64_t> S, R;
     std::vector<double> F;
     size_t need = 0;        // workspace bytes this request needs
-    bool ring = false;      // ... with the ring engine's buffers
+    size_t need_ring = 0;   // ... and the ring engine's, if it may take them
 };
 
 }  // namespace
@@ -64,7 +64,7 @@ struct tkc_server {
     int32_t slots_n = 0;
     std::vector<tkc_graph*> graphs;
     std::vector<tkc_ctx*> slot_ctx;
-    std::vector<size_t> slot_bytes;
+    std::vector<size_t> slot_bytes, slot_ring;   // committed: the workspace, the ring engine's buffers
     std::vector<std::thread> workers;
     std::mutex mu;
     std::condition_variable cv_work, cv_done;
@@ -86,7 +86,7 @@ struct tkc_server {
     // about 0.5 ms).  Such a request pays for a launch of its own, about 0.5
     // ms, from some 32 levels on; social and web graphs have a dozen.  A graph
     // whose depth is not known yet does not join a pack.
-    static bool rings(const Request& q, const tkc_graph& g) { return q.ring && (!g.levels || g.levels > 32); }
+    static bool rings(const Request& q, const tkc_graph& g) { return q.need_ring && (!g.levels || g.levels > 32); }
 
     // fills request rq's answer from a packed call's concatenated results
     static void take(Request& rq, const std::vector<int32_t>& ids, const std::vector<int64_t>& S,
@@ -100,7 +100,7 @@ struct tkc_server {
     size_t committed_except(int slot) {
         size_t t = 0;
         for (int i = 0; i < slots_n; i++)
-            if (i != slot) t += slot_bytes[i];
+            if (i != slot) t += slot_bytes[i] + slot_ring[i];
         return t;
     }
 
@@ -116,26 +116,22 @@ struct tkc_server {
                     if (stopping) return;
                     // first queued request whose workspace fits next to the others
                     for (auto it = queue.begin(); it != queue.end(); ++it) {
-                        size_t need = std::max((*it)->need, slot_bytes[slot]);
-                        if (committed_except(slot) + need <= budget) {
+                        const size_t need = std::max((*it)->need, slot_bytes[slot]);
+                        const size_t ring = std::max((*it)->need_ring, slot_ring[slot]);
+                        if (committed_except(slot) + need + ring <= budget) {
                             rq = *it;
                             queue.erase(it);
                             slot_bytes[slot] = need;
+                            slot_ring[slot] = ring;
                             break;
                         }
                     }
                     if (rq) break;
-                    if (!queue.empty() && slot_bytes[slot] > 0) {
+                    if (!queue.empty() && slot_bytes[slot] + slot_ring[slot] > 0) {
                         // nothing fits next to the other slots: give this idle
                         // slot's workspace back so a waiting request can run
-                        if (c->ws.base) {
-                            hipStreamSynchronize(c->stream);
-                            hipFree(c->ws.base);
-                            c->ws.base = nullptr;
-                            c->ws.bytes = 0;
-                            c->ws.shape = WsShape();
-                        }
-                        slot_bytes[slot] = 0;
+                        tkc_ws_release(c, c->ws);
+                        slot_bytes[slot] = slot_ring[slot] = 0;
                         cv_work.notify_all();
                         continue;
                     }
@@ -155,7 +151,7 @@ struct tkc_server {
                 std::lock_guard<std::mutex> lk(mu);
                 if (packing && !rq->cancelled) pk = pack_of[rq->graph_id];
             }
-            if (pk >= 0 && rq->ring && !g->levels) tkc_auto_variant(c, g);
+            if (pk >= 0 && rq->need_ring && !g->levels) tkc_auto_variant(c, g);
             if (pk >= 0 && rings(*rq, *g)) pk = -1;
             if (pk >= 0) {
                 pv = rq->variant == TKC_AUTO ? tkc_auto_variant(c, g) : rq->variant;
@@ -164,7 +160,7 @@ struct tkc_server {
             if (pk >= 0) {
                 std::lock_guard<std::mutex> lk(mu);
                 const size_t need = std::max(slot_bytes[slot], pack_need[pk]);
-                if (committed_except(slot) + need <= budget) {
+                if (committed_except(slot) + need + slot_ring[slot] <= budget) {
                     slot_bytes[slot] = need;
                     group.push_back(rq);
                     std::vector<char> used(packs[pk]->members.size(), 0);
@@ -232,7 +228,7 @@ struct tkc_server {
                 std::lock_guard<std::mutex> lk(mu);
                 skip = rq->cancelled;
             }
-            c->ring_ok = rq->ring;
+            c->ring_ok = rq->need_ring > 0;
             if (!skip)
                 st = tkc_run_query(c, g, k, rq->variant, TKC_MODE_AUTO, rq->ids.data(), rq->S.data(), rq->R.data(),
                                    rq->F.data(), &got, nullptr);
@@ -243,6 +239,7 @@ struct tkc_server {
                 rq->t_done = now_ms();
                 rq->state = 2;
                 slot_bytes[slot] = c->ws.bytes;
+                slot_ring[slot] = c->ws.r_bytes;
                 n_served++;
             }
             cv_done.notify_all();
@@ -273,6 +270,7 @@ extern "C" int tkc_server_create(tkc_ctx* ctx, size_t hbm_budget_bytes, int32_t 
         c->tune.slice_batches = 2;
         s->slot_ctx.push_back(c);
         s->slot_bytes.push_back(0);
+        s->slot_ring.push_back(0);
     }
     for (int i = 0; i < max_inflight; i++) s->workers.emplace_back(&tkc_server::worker, s, i);
     *out = s;
@@ -309,13 +307,11 @@ extern "C" int tkc_server_submit(tkc_server* s, int32_t graph_id, int32_t k, int
     bool lb = tkc_lb_level(variant) != 0 || variant == TKC_AUTO;
     const WsShape sh = tkc_shape_for(tkc_effective_tuning(s->ctx->tune, g), g, std::min(k, g->n), lb);
     rq->need = tkc_ws_bytes(sh);
-    // the ring engine's larger buffers only where they fit beside the other
-    // slots' share of the budget
-    const WsShape rs = tkc_shape_ring(sh, g);
-    if (rs.ring && tkc_ws_bytes(rs) <= s->budget / (size_t)s->slots_n) {
-        rq->need = tkc_ws_bytes(rs);
-        rq->ring = true;
-    }
+    // the ring engine's buffers only where they fit beside the other slots'
+    // share of the budget
+    const int32_t ring = tkc_ring_blocks(g->view());
+    const size_t rb = ring ? tkc_ring_bytes(g->n, ring) : 0;
+    if (rq->need + rb <= s->budget / (size_t)s->slots_n) rq->need_ring = rb;
     if (rq->need > s->budget) return tkc_fail(TKC_EBUSY, "request needs %zu bytes, budget is %zu", rq->need, s->budget);
     s->queue.push_back(rq);
     s->all[rq->ticket] = rq;
