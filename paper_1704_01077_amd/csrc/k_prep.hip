@@ -574,42 +574,53 @@ __global__ void k_nb_round(int32_t n, const int32_t* __restrict__ rp, const int3
         // adds its chunks' sums and finishes it.  The sums are stored and read
         // past the caches and each store has ended before its wave counts, so
         // no fence is needed.  (With a launch of its own for the finishing a
-        // round took one launch more: 275 -> 265 us a query on 2,000 vertices.)
+        // round took one launch more: 275 -> 265 us a query on 2,000 vertices.
+        // All 64 lanes read the sums: with one, a chain of 1,954 loads, the three
+        // rounds on a graph with a hub of 10^6 arcs took 0.98 ms, now 0.29.)
         const int32_t c = ((blockIdx.x - nlight_blocks) * blockDim.x + threadIdx.x) >> 6;
         bool fin = false;
         if (c < nchunks) {   // wave-uniform
+            const int lane = lane_id();
+            // saturating sum over the wave (of values that do not depend on order)
+            auto wave_sum = [](uint64_t x) {
+#pragma unroll
+                for (int o = 32; o > 0; o >>= 1) {
+                    x += __shfl_xor(x, o, 64);
+                    if (x > (uint64_t)NB_INF) x = NB_INF;
+                }
+                return x;
+            };
             // (the exact 64-bit counts: a 512-arc chunk meets a capped count
             // far more often than a light row)
             uint64_t acc = 0;
-            for (int32_t e = ch_beg[c] + lane_id(); e < ch_end[c]; e += 64) {
+            for (int32_t e = ch_beg[c] + lane; e < ch_end[c]; e += 64) {
                 acc += (uint64_t)g1x[ci[e]];
                 if (acc > (uint64_t)NB_INF) acc = NB_INF;
             }
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) {
-                acc += __shfl_xor(acc, o, 64);
-                if (acc > (uint64_t)NB_INF) acc = NB_INF;
-            }
-            if (lane_id() == 0) {
-                const int32_t s = ch_vtx[c], d = deg[s];
-                const int32_t first = c - (ch_beg[c] - rp[s]) / CHUNK_ARCS, nc = (d + CHUNK_ARCS - 1) / CHUNK_ARCS;
-                bool last = nc == 1;
-                if (!last) {
+            acc = wave_sum(acc);
+            const int32_t s = ch_vtx[c], d = deg[s];
+            const int32_t first = c - (ch_beg[c] - rp[s]) / CHUNK_ARCS, nc = (d + CHUNK_ARCS - 1) / CHUNK_ARCS;
+            bool last = nc == 1;
+            if (!last) {
+                int32_t before = 0;
+                if (lane == 0) {
                     st_rlx(&partial[c], acc);
                     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
                     __builtin_amdgcn_s_waitcnt(0x0F70);
-                    last = fadd_rlx(&hcnt[first], 1) == nc - 1;
-                    if (last) {
-                        st_rlx(&hcnt[first], 0);
-                        acc = 0;
-                        for (int32_t q = first; q < first + nc; q++) {
-                            acc += ld_rlx(&partial[q]);
-                            if (acc > (uint64_t)NB_INF) acc = NB_INF;
-                        }
-                    }
+                    before = fadd_rlx(&hcnt[first], 1);
+                    if (before == nc - 1) st_rlx(&hcnt[first], 0);
                 }
-                if (last) nb_finish_vertex<DIRECTED>(s, acc, k, d, g2, gk, alpha, omega, st, adv != 0, &fin);
+                last = __shfl(before, 0, 64) == nc - 1;
+                if (last) {
+                    acc = 0;
+                    for (int32_t q = first + lane; q < first + nc; q += 64) {
+                        acc += ld_rlx(&partial[q]);
+                        if (acc > (uint64_t)NB_INF) acc = NB_INF;
+                    }
+                    acc = wave_sum(acc);
+                }
             }
+            if (last && lane == 0) nb_finish_vertex<DIRECTED>(s, acc, k, d, g2, gk, alpha, omega, st, adv != 0, &fin);
         }
         __shared__ int32_t lds[16];
         nb_count(fin, nfin, lds);
