@@ -1041,6 +1041,44 @@ int tkc_run_query(tkc_ctx* c, tkc_graph* g, int32_t k, int32_t variant, int32_t 
     int grid = 0;
     // the hybrid's per-workgroup engine has no level-based path
     if (lb && mode == TKC_HYBRID) mode = TKC_BATCHED;
+    // the hybrid's seed batch: searches until x is known, and `more` batches
+    auto launch_seed = [&](int32_t more) -> int {
+        EngineTuning seed = c->tune;
+        seed.lanes_cap = seed.seed_lanes;
+        if (tkc_launch_batch(dg, rcv, ov, bv, tk, tkc_batch_view(ws), st_batch, nullptr, 0, 0, -1 - more, false, false,
+                             nullptr, nullptr, seed, s, &grid))
+            return tkc_fail(TKC_EDEVICE, "batched seed launch failed: %s", hipGetErrorString(hipGetLastError()));
+        return TKC_OK;
+    };
+    // it goes on with the per-workgroup engine on small graphs.  On larger ones
+    // whose searches that engine's queue holds, a few batches show how many
+    // arcs and levels a cut search takes, and which engine is the faster one
+    // for the rest.  Where the queue may overflow only a deep graph is worth
+    // the try; its depth is that of the seeds (complete searches, since x is
+    // not known yet) unless AUTO's search or an earlier query has shown it
+    bool swarm = mode == TKC_HYBRID && !ring && tkc_swarm_small(dg);
+    bool seeded = false;
+    int32_t resume = 0;   // position of the order after the seeds, n when they ended the query
+    const bool queued = ws.shape.qcap >= n;
+    if (mode == TKC_HYBRID && !ring && !swarm && tkc_swarm_fits(dg) &&
+        (queued || !g->levels || g->levels > TKC_SWARM_LEVELS)) {
+        trace_reset(c);
+        {
+            EngineTimer tm(c, &ms_eng[1], &nl_eng[1]);
+            if ((rc = launch_seed(queued ? TKC_SWARM_TRY : 0))) return rc;
+            if ((rc = tm.done(readback))) return rc;
+        }
+        trace_dump(c, "seed");
+        const int64_t* hs = pin_at<int64_t>(ws, st_batch);
+        const int64_t levels = std::max<int64_t>(hs[ST_MAXLEVEL], 1);
+        if (!g->levels) g->levels = (int32_t)levels;
+        resume = hs[ST_STOP] ? n : (int32_t)hs[ST_CURSOR];
+        seeded = rb_ready = true;
+        // (a search that was not cut took every arc)
+        const double arcs = (double)hs[ST_MVIS] - (double)hs[ST_EXACT] * (double)g->m;
+        swarm = queued ? tkc_swarm_pays(arcs / (double)std::max<int64_t>(hs[ST_CUT], 1), levels)
+                       : levels > TKC_SWARM_LEVELS;
+    }
     // one search at a time on a small graph: one workgroup of the per-workgroup
     // engine (its queue holds every vertex, so it defers nothing)
     if (mode == TKC_PLAIN && !lb && max_searches <= 0 && ws.shape.qcap >= n && tkc_plain_small(dg)) {
@@ -1065,14 +1103,14 @@ int tkc_run_query(tkc_ctx* c, tkc_graph* g, int32_t k, int32_t variant, int32_t 
             return tkc_fail(TKC_EDEVICE, "plain engine launch failed: %s", hipGetErrorString(hipGetLastError()));
         if ((rc = tm.done(readback))) return rc;
         rb_ready = true;
-    } else if (mode == TKC_BATCHED || ring || !tkc_swarm_fits(dg)) {
+    } else if (!swarm) {
         trace_reset(c);
         // launches of slice_batches batches each when that is set (the
         // cursor, stop flag, top k and bounds live in device memory between
         // them), else one launch
         const int32_t slice = c->tune.slice_batches > 0 ? c->tune.slice_batches : 0;
-        int32_t pos = 0;
-        bool more = true;
+        int32_t pos = resume;
+        bool more = pos < n;
         if (ring) {
             int32_t* small = (int32_t*)ws.small;
             const int32_t* pin = (const int32_t*)c->pinned;
@@ -1152,24 +1190,27 @@ int tkc_run_query(tkc_ctx* c, tkc_graph* g, int32_t k, int32_t variant, int32_t 
         // the seed's cursor and stop flag reach the swarm on the device: no
         // host wait between the two launches
         sw.seed = st_batch;
-        {
+        // the swarm's exit state, the counters, and the results in case
+        // nothing follows
+        auto exit_state = [&]() -> int {
+            HIPCHK(hipMemcpyAsync(pin, small + 4, 3 * sizeof(int32_t), hipMemcpyDeviceToHost, s));
+            return readback();
+        };
+        if (seeded) {
+            if (resume < n) {
+                EngineTimer tm(c, &ms_eng[2], &nl_eng[2]);
+                if (tkc_launch_swarm(dg, rcv, ov, bv, tk, sw, st_swarm, 0, c->tune, s))
+                    return tkc_fail(TKC_EDEVICE, "per-workgroup engine launch failed");
+                if ((rc = tm.done(exit_state))) return rc;
+            }
+        } else {
             const double before = ms_eng[1];
             EngineTimer tm(c, &ms_eng[1], &nl_eng[1]);
-            EngineTuning seed = c->tune;
-            seed.lanes_cap = seed.seed_lanes;
-            if (tkc_launch_batch(dg, rcv, ov, bv, tk, tkc_batch_view(ws), st_batch, nullptr, 0, 0, -1, false,
-                                 false, nullptr, nullptr, seed, s, &grid))
-                return tkc_fail(TKC_EDEVICE, "batched seed launch failed: %s", hipGetErrorString(hipGetLastError()));
+            if ((rc = launch_seed(0))) return rc;
             HIPCHK(hipEventRecord(c->evm, s));
             if (tkc_launch_swarm(dg, rcv, ov, bv, tk, sw, st_swarm, 0, c->tune, s))
                 return tkc_fail(TKC_EDEVICE, "per-workgroup engine launch failed");
-            // the swarm's exit state, the counters, and the results in case
-            // nothing follows
-            if ((rc = tm.done([&] {
-                     HIPCHK(hipMemcpyAsync(pin, small + 4, 3 * sizeof(int32_t), hipMemcpyDeviceToHost, s));
-                     return readback();
-                 })))
-                return rc;
+            if ((rc = tm.done(exit_state))) return rc;
             rb_ready = true;
             // split the timed span at the mark between the launches
             float seed_ms = 0.f;
@@ -1181,7 +1222,7 @@ int tkc_run_query(tkc_ctx* c, tkc_graph* g, int32_t k, int32_t variant, int32_t 
             nl_eng[2]++;
         }
         memcpy(hs, pin_at<int64_t>(ws, st_batch), sizeof(hs));
-        trace_dump(c, "seed");
+        if (!seeded) trace_dump(c, "seed");
         const int32_t cursor = (int32_t)hs[ST_CURSOR];
         const bool stopped = hs[ST_STOP] != 0;
         if (!stopped && cursor < n) {
@@ -1200,11 +1241,11 @@ int tkc_run_query(tkc_ctx* c, tkc_graph* g, int32_t k, int32_t variant, int32_t 
             }
             // every position the cursor handed out was searched, skipped or
             // deferred; without a stop rule firing, the order resumes there
-            const int32_t resume = cursor + std::min(fetched, n - cursor);
-            if (!(sw_stop & 1) && (sw_stop & 2) && resume < n) {
+            const int32_t at = cursor + std::min(fetched, n - cursor);
+            if (!(sw_stop & 1) && (sw_stop & 2) && at < n) {
                 trace_reset(c);
                 EngineTimer tm(c, &ms_eng[1], &nl_eng[1]);
-                if (tkc_launch_batch(dg, rcv, ov, bv, tk, tkc_batch_view(ws), st_batch, nullptr, 0, resume, 0, false,
+                if (tkc_launch_batch(dg, rcv, ov, bv, tk, tkc_batch_view(ws), st_batch, nullptr, 0, at, 0, false,
                                      false, nullptr, nullptr, c->tune, s, &grid))
                     return tkc_fail(TKC_EDEVICE, "batched continuation launch failed");
                 if ((rc = tm.done(readback))) return rc;

@@ -115,6 +115,8 @@ static inline int tkc_grid_for(int cus, int per, int32_t n) {
 // runtime once per device and kernel, then cached); -1 on error
 int tkc_cu_count();
 int tkc_occupancy(const void* fn, int block);
+// the most LDS of a workgroup on the current device, 0 on error
+int tkc_lds_limit();
 
 // k_prep.hip
 int tkc_launch_degrees(const DevGraph& g, hipStream_t s);
@@ -258,15 +260,17 @@ struct PackReq {
 };
 #define TKC_PACK_MAXREQ 64
 
+// max_batches: 0 no limit, -1 - b: until x is finite and b batches more
 int tkc_launch_batch(const DevGraph& g, DevReach rc, OrderView ov, BoundsView bv, DevTopk tk,
                      BatchWork w, int64_t* stats, const int32_t* list, int32_t list_count,
                      int32_t start_pos, int32_t max_batches, int lb_mode, bool no_cut,
                      int64_t* out_S, int64_t* out_r, const EngineTuning& tune, hipStream_t s,
                      int* grid_out, const PackReq* preq = nullptr, int32_t npreq = 0);
 
-// k_swarm.hip: one search per workgroup for short cut searches, on graphs of
-// at most TKC_SWARM_SIZE vertices and edges (visited set in LDS).
-#define TKC_SWARM_SIZE (1 << 18)
+// k_swarm.hip: one search per workgroup (visited set in LDS).
+#define TKC_SWARM_SIZE (1 << 18)   // vertices and edges up to which it follows the seeds at once
+#define TKC_SWARM_LEVELS 48        // depth of a graph that counts as deep
+#define TKC_SWARM_TRY 4            // batches beyond the seeds that show what a search is like
 struct SwarmWork {
     int32_t* queue;      // nblocks * qcap
     int32_t* deferred;   // n
@@ -284,7 +288,10 @@ int tkc_launch_swarm(const DevGraph& g, DevReach rc, OrderView ov, BoundsView bv
                      SwarmWork w, int64_t* stats, int32_t start_pos, const EngineTuning& tune,
                      hipStream_t s);
 int tkc_swarm_max_blocks(int block);
-bool tkc_swarm_fits(const DevGraph& g);
+bool tkc_swarm_small(const DevGraph& g);
+bool tkc_swarm_fits(const DevGraph& g);   // the visited set fits LDS
+// searches of so many arcs and levels are faster one per workgroup than batched
+bool tkc_swarm_pays(double arcs, int64_t levels);
 bool tkc_plain_small(const DevGraph& g);
 
 // k_ring.hip: one search per workgroup, visited set in LDS (undirected graphs

@@ -70,7 +70,8 @@ struct BatchArgs {
     int32_t max_batches;
     int32_t lb_mode;
     int32_t no_cut;        // full searches, results to out_S / out_r only
-    int32_t until_x;       // stop after the batch in which x becomes finite
+    int32_t until_x;       // stop `after` batches behind the one in which x becomes finite
+    int32_t after;
     int32_t W;
     int32_t Wsel;          // lanes filled per batch (<= W)
     int32_t alpha_td;
@@ -576,7 +577,7 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
     __shared__ uint64_t s_cacc[BB / 64][LSTR * NW];
 
     int32_t pos = a.start_pos;
-    int32_t batches = 0;
+    int32_t batches = 0, after = a.after;
     if (tid < TKC_PACK_MAXREQ) {
         s_pk_pos[tid] = 0;
         s_pk_stop[tid] = 0;
@@ -1469,7 +1470,7 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
         }
         batches++;
         if (stop_now) break;
-        if (a.until_x && ld_rlx(&ctr[C_XDONE]) != 0) break;
+        if (a.until_x && ld_rlx(&ctr[C_XDONE]) != 0 && after-- == 0) break;
     }
     if (boss) stats[ST_CURSOR] = pos;
 }
@@ -1516,8 +1517,8 @@ int tkc_launch_batch(const DevGraph& g, DevReach rc, OrderView ov, BoundsView bv
     a.max_batches = max_batches > 0 ? max_batches : 0x7fffffff;
     a.lb_mode = lb_mode;
     a.no_cut = no_cut ? 1 : 0;
-    a.until_x = (max_batches == -1) ? 1 : 0;
-    if (max_batches == -1) a.max_batches = 0x7fffffff;
+    a.until_x = max_batches < 0 ? 1 : 0;
+    a.after = max_batches < 0 ? -1 - max_batches : 0;
     a.W = W;
     a.Wsel = (tune.lanes_cap > 0 && tune.lanes_cap < W) ? tune.lanes_cap : W;
     a.alpha_td = tune.batch_alpha > 0 ? tune.batch_alpha : 14;

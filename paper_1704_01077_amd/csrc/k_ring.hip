@@ -532,12 +532,6 @@ __global__ void __launch_bounds__(T) k_ring(RingArgs a) {
 // the kernels' static LDS: two level copies, the offsets, and under 1 KiB more
 #define RING_STATIC_LDS (4 * (2 * RING_FRONT + RING_LEVELS) + 1024)
 
-static int ring_lds_limit() {
-    int dev = 0, v = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return 0;
-    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess) return 0;
-    return v;
-}
 // the bitmap and a spare word
 static size_t ring_lds_bytes(int32_t n) { return 4 * (((size_t)n + 31) / 32 + 1); }
 
@@ -551,7 +545,7 @@ static size_t ring_lds_bytes(int32_t n) { return 4 * (((size_t)n + 31) / 32 + 1)
 // -> 3.2 ms.)
 int tkc_ring_blocks(const DevGraph& g) {
     if (g.directed || g.nheavy > 0 || g.m > 8 * (int64_t)g.n || g.n < 2) return 0;
-    if (ring_lds_bytes(g.n) + RING_STATIC_LDS > (size_t)ring_lds_limit()) return 0;
+    if (ring_lds_bytes(g.n) + RING_STATIC_LDS > (size_t)tkc_lds_limit()) return 0;
     const int cus = tkc_cu_count();
     return cus > 0 ? cus : 0;
 }
@@ -574,7 +568,7 @@ int tkc_launch_ring(const DevGraph& g, DevReach rc, OrderView ov, BoundsView bv,
         return -2;
     if (g.directed || g.nheavy > 0 || bv.harm) return -2;
     const size_t lds = ring_lds_bytes(g.n);
-    if (lds + RING_STATIC_LDS > (size_t)ring_lds_limit()) return -2;
+    if (lds + RING_STATIC_LDS > (size_t)tkc_lds_limit()) return -2;
     RingArgs a{};
     a.g = g; a.rc = rc; a.ov = ov; a.bv = bv; a.tk = tk; a.w = w;
     a.stats = stats;

@@ -282,8 +282,25 @@ __global__ void __launch_bounds__(SB) k_swarm(SwarmArgs a) {
     }
 }
 
-bool tkc_swarm_fits(const DevGraph& g) {
+bool tkc_swarm_small(const DevGraph& g) {
     return g.n + (g.directed ? (int64_t)g.m : (int64_t)g.m / 2) <= TKC_SWARM_SIZE;
+}
+// the kernel's static LDS: rows and their prefix sums, and under 1 KiB more
+#define SWARM_STATIC_LDS (8 * 1024 + 1024)
+static size_t swarm_lds_bytes(int32_t n) { return 4 * (((size_t)n + 31) / 32); }
+// A level costs a batch a grid barrier, 7 us shared by 64 searches, and this
+// engine some workgroup barriers; an arc costs a batch its share of one read
+// of the frontier's rows, and this engine 1 / 150 ns of the whole chip.
+// Batched -> this engine, us a search, by arcs and levels: random graphs of 4
+// 10^4 vertices (28,000, 6) 1.33 -> 0.40; of 2 10^4 (11,900, 3) 0.85 -> 0.14;
+// of 6 10^4 and 3 10^6 arcs (126,000, 4) 1.41 -> 0.75; small worlds of 6.2 10^4
+// (44,000, 22) 2.86 -> 0.46, (105,000, 95) 9.34 -> 1.32; a king's lattice of one-way
+// streets of 6.25 10^4, 142 levels, 12.9 -> 1.5; but web graphs of 6 10^4 and 3.8
+// 10^6 arcs (812,000, 4) 1.18 -> 3.52, a social network of 2 10^4 and 8 10^5
+// (178,000, 3) 1.09 -> 2.89.
+bool tkc_swarm_pays(double arcs, int64_t levels) { return arcs <= (1 << 17) + 8192.0 * (double)levels; }
+bool tkc_swarm_fits(const DevGraph& g) {
+    return swarm_lds_bytes(g.n) + SWARM_STATIC_LDS <= (size_t)tkc_lds_limit();
 }
 
 // Plain mode on a small graph: this engine with one workgroup takes the same
@@ -322,8 +339,12 @@ int tkc_launch_swarm(const DevGraph& g, DevReach rc, OrderView ov, BoundsView bv
     a.stats = stats;
     a.start_pos = start_pos;
     if (!tkc_swarm_fits(g)) return -2;
-    a.words = (int32_t)(((int64_t)g.n + 31) / 32);
-    const size_t lds = 4 * (size_t)a.words;
+    const size_t lds = swarm_lds_bytes(g.n);
+    a.words = (int32_t)(lds / 4);
+    const void* fn = swarm_sb() == 1024 ? (const void*)k_swarm<1024> : (const void*)k_swarm<256>;
+    if (lds > (32 << 10) &&
+        hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+        hipGetLastError();
     a.defer_cap = w.defer_cap > 0 ? w.defer_cap : 0x7fffffff;
     if (swarm_sb() == 1024)
         hipLaunchKernelGGL(k_swarm<1024>, dim3(w.nblocks), dim3(1024), lds, s, a);

@@ -48,6 +48,12 @@ int tkc_cu_count() {
     cus[dev] = v;
     return v;
 }
+int tkc_lds_limit() {
+    int dev = 0, v = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return 0;
+    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess) return 0;
+    return v;
+}
 int tkc_occupancy(const void* fn, int block) {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0) return -1;
