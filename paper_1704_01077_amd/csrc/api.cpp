@@ -1041,43 +1041,59 @@ int tkc_run_query(tkc_ctx* c, tkc_graph* g, int32_t k, int32_t variant, int32_t 
     int grid = 0;
     // the hybrid's per-workgroup engine has no level-based path
     if (lb && mode == TKC_HYBRID) mode = TKC_BATCHED;
-    // the hybrid's seed batch: searches until x is known, and `more` batches
-    auto launch_seed = [&](int32_t more) -> int {
+    // seeds: batches until x is known, and `more` batches
+    auto launch_seed = [&](int32_t more, int32_t level_cap) -> int {
         EngineTuning seed = c->tune;
         seed.lanes_cap = seed.seed_lanes;
-        if (tkc_launch_batch(dg, rcv, ov, bv, tk, tkc_batch_view(ws), st_batch, nullptr, 0, 0, -1 - more, false, false,
+        seed.level_cap = level_cap;
+        if (tkc_launch_batch(dg, rcv, ov, bv, tk, tkc_batch_view(ws), st_batch, nullptr, 0, 0, -1 - more, lbl, false,
                              nullptr, nullptr, seed, s, &grid))
             return tkc_fail(TKC_EDEVICE, "batched seed launch failed: %s", hipGetErrorString(hipGetLastError()));
         return TKC_OK;
     };
-    // it goes on with the per-workgroup engine on small graphs.  On larger ones
-    // whose searches that engine's queue holds, a few batches show how many
-    // arcs and levels a cut search takes, and which engine is the faster one
-    // for the rest.  Where the queue may overflow only a deep graph is worth
-    // the try; its depth is that of the seeds (complete searches, since x is
-    // not known yet) unless AUTO's search or an earlier query has shown it
+    // Hybrid mode goes on with the per-workgroup engine on small graphs.  On
+    // larger ones whose searches that engine's queue holds, a few batches show
+    // how many arcs and levels a cut search takes, and which engine is the
+    // faster one for the rest.  Where the queue may overflow only a deep graph
+    // is worth the try; its depth is that of the seeds (complete searches,
+    // since x is not known yet) unless AUTO's search or an earlier query has
+    // shown it.  The ring engine lets a batch search first on large graphs
+    // that are not deep; a batch that turns out to be deep gives up.
     bool swarm = mode == TKC_HYBRID && !ring && tkc_swarm_small(dg);
     bool seeded = false;
     int32_t resume = 0;   // position of the order after the seeds, n when they ended the query
     const bool queued = ws.shape.qcap >= n;
-    if (mode == TKC_HYBRID && !ring && !swarm && tkc_swarm_fits(dg) &&
-        (queued || !g->levels || g->levels > TKC_SWARM_LEVELS)) {
+    const bool seed_swarm = mode == TKC_HYBRID && !ring && !swarm && tkc_swarm_fits(dg) &&
+                            (queued || !g->levels || g->levels > TKC_DEEP);
+    const bool seed_ring = ring && tkc_ring_seeds(dg, g->levels);
+    if (seed_swarm || seed_ring) {
         trace_reset(c);
         {
             EngineTimer tm(c, &ms_eng[1], &nl_eng[1]);
-            if ((rc = launch_seed(queued ? TKC_SWARM_TRY : 0))) return rc;
+            if ((rc = launch_seed(seed_ring ? 1 : queued ? TKC_SWARM_TRY : 0, seed_ring && !g->levels ? TKC_DEEP : 0)))
+                return rc;
             if ((rc = tm.done(readback))) return rc;
         }
         trace_dump(c, "seed");
         const int64_t* hs = pin_at<int64_t>(ws, st_batch);
-        const int64_t levels = std::max<int64_t>(hs[ST_MAXLEVEL], 1);
-        if (!g->levels) g->levels = (int32_t)levels;
-        resume = hs[ST_STOP] ? n : (int32_t)hs[ST_CURSOR];
-        seeded = rb_ready = true;
-        // (a search that was not cut took every arc)
-        const double arcs = (double)hs[ST_MVIS] - (double)hs[ST_EXACT] * (double)g->m;
-        swarm = queued ? tkc_swarm_pays(arcs / (double)std::max<int64_t>(hs[ST_CUT], 1), levels)
-                       : levels > TKC_SWARM_LEVELS;
+        if (hs[ST_CAPPED]) {
+            // (the top k may hold vertices that reach nothing: it starts over)
+            if (!g->levels) g->levels = TKC_DEEP + 1;
+            if (tkc_launch_topk_init(tk, k, s, ties ? &tb : nullptr, ws.stats, 4 * ST_COUNT, (int32_t*)ws.small + 4))
+                return tkc_fail(TKC_EDEVICE, "top-k init failed");
+            ms_eng[1] = 0;
+            nl_eng[1] = 0;
+        } else {
+            const int64_t levels = std::max<int64_t>(hs[ST_MAXLEVEL], 1);
+            if (!g->levels) g->levels = (int32_t)levels;
+            resume = hs[ST_STOP] ? n : (int32_t)hs[ST_CURSOR];
+            seeded = rb_ready = true;
+            // (a search that was not cut took every arc)
+            const double arcs = (double)hs[ST_MVIS] - (double)hs[ST_EXACT] * (double)g->m;
+            if (seed_swarm)
+                swarm = queued ? tkc_swarm_pays(arcs / (double)std::max<int64_t>(hs[ST_CUT], 1), levels)
+                               : levels > TKC_DEEP;
+        }
     }
     // one search at a time on a small graph: one workgroup of the per-workgroup
     // engine (its queue holds every vertex, so it defers nothing)
@@ -1111,7 +1127,7 @@ int tkc_run_query(tkc_ctx* c, tkc_graph* g, int32_t k, int32_t variant, int32_t 
         const int32_t slice = c->tune.slice_batches > 0 ? c->tune.slice_batches : 0;
         int32_t pos = resume;
         bool more = pos < n;
-        if (ring) {
+        if (ring && more) {
             int32_t* small = (int32_t*)ws.small;
             const int32_t* pin = (const int32_t*)c->pinned;
             RingWork rw{};
@@ -1128,11 +1144,11 @@ int tkc_run_query(tkc_ctx* c, tkc_graph* g, int32_t k, int32_t variant, int32_t 
             rw.nblocks = ring;
             // a slice runs two searches per workgroup
             const int32_t limit = slice ? 2 * ring : 0;
-            if (tkc_launch_ring_begin(dg, rcv, bv, rw, s)) return tkc_fail(TKC_EDEVICE, "bound kernel failed");
+            if (tkc_launch_ring_begin(dg, rcv, bv, rw, pos, s)) return tkc_fail(TKC_EDEVICE, "bound kernel failed");
             do {
                 HIPCHK(hipMemsetAsync(small + 6, 0, sizeof(int32_t), s));
                 EngineTimer tm(c, &ms_eng[2], &nl_eng[2]);
-                if (tkc_launch_ring(dg, rcv, ov, bv, tk, rw, st_swarm, lbl, limit, s))
+                if (tkc_launch_ring(dg, rcv, ov, bv, tk, rw, st_swarm, lbl, k, limit, s))
                     return tkc_fail(TKC_EDEVICE, "ring engine launch failed: %s", hipGetErrorString(hipGetLastError()));
                 if ((rc = tm.done([&] {
                          HIPCHK(hipMemcpyAsync(c->pinned, small + 4, 2 * sizeof(int32_t), hipMemcpyDeviceToHost, s));
@@ -1206,7 +1222,7 @@ int tkc_run_query(tkc_ctx* c, tkc_graph* g, int32_t k, int32_t variant, int32_t 
         } else {
             const double before = ms_eng[1];
             EngineTimer tm(c, &ms_eng[1], &nl_eng[1]);
-            if ((rc = launch_seed(0))) return rc;
+            if ((rc = launch_seed(0, 0))) return rc;
             HIPCHK(hipEventRecord(c->evm, s));
             if (tkc_launch_swarm(dg, rcv, ov, bv, tk, sw, st_swarm, 0, c->tune, s))
                 return tkc_fail(TKC_EDEVICE, "per-workgroup engine launch failed");

@@ -98,6 +98,8 @@ struct EngineTuning {
     int32_t lanes_cap = 0;       // lanes used per batch in one launch (0: batch_width)
     int32_t blocks_per_cu = 2;   // workgroups per CU of the persistent kernels
     int32_t mode = 1;            // preferred mode (TKC_BATCHED) for TKC_MODE_AUTO
+    int32_t level_cap = 0;       // batched launch: it ends without a result, with ST_CAPPED
+                                 // set, when its first batch goes deeper (0: no cap)
     int32_t slice_batches = 0;   // batched searches per launch (0: all in one); servers
                                  // slice long queries so other requests interleave
 };
@@ -267,9 +269,10 @@ int tkc_launch_batch(const DevGraph& g, DevReach rc, OrderView ov, BoundsView bv
                      int64_t* out_S, int64_t* out_r, const EngineTuning& tune, hipStream_t s,
                      int* grid_out, const PackReq* preq = nullptr, int32_t npreq = 0);
 
+#define TKC_DEEP 48   // levels of a search from which a graph counts as deep
+
 // k_swarm.hip: one search per workgroup (visited set in LDS).
 #define TKC_SWARM_SIZE (1 << 18)   // vertices and edges up to which it follows the seeds at once
-#define TKC_SWARM_LEVELS 48        // depth of a graph that counts as deep
 #define TKC_SWARM_TRY 4            // batches beyond the seeds that show what a search is like
 struct SwarmWork {
     int32_t* queue;      // nblocks * qcap
@@ -317,12 +320,16 @@ struct RingWork {
 // arcs or more than 8 arcs a vertex on average (one workgroup per search
 // then loses to the batched engine's shared reads), bitmaps beyond LDS
 int tkc_ring_blocks(const DevGraph& g);
-// bounds into the engine's form before its first launch, and back after the
-// last when another engine goes on with them
+// a batch searches first on graphs of that size, unless they are deep
+// (levels: their depth, 0 if not known)
+bool tkc_ring_seeds(const DevGraph& g, int32_t levels);
+// bounds into the engine's form before its first launch, which starts at
+// position `from` of the order, and back after the last when another engine
+// goes on with them
 int tkc_launch_ring_begin(const DevGraph& g, const DevReach& rc, const BoundsView& bv, const RingWork& w,
-                          hipStream_t s);
+                          int32_t from, hipStream_t s);
 int tkc_launch_ring_end(const DevGraph& g, const DevReach& rc, const BoundsView& bv, const RingWork& w, hipStream_t s);
-// searches the order from *cursor on; limit > 0: about that many searches,
+// searches the order from *cursor on for the top k; limit > 0: about that many searches,
 // then the launch ends with the cursor where the next one resumes
 int tkc_launch_ring(const DevGraph& g, DevReach rc, OrderView ov, BoundsView bv, DevTopk tk, RingWork w,
-                    int64_t* stats, int lb_mode, int32_t limit, hipStream_t s);
+                    int64_t* stats, int lb_mode, int32_t k, int32_t limit, hipStream_t s);

@@ -72,6 +72,7 @@ struct BatchArgs {
     int32_t no_cut;        // full searches, results to out_S / out_r only
     int32_t until_x;       // stop `after` batches behind the one in which x becomes finite
     int32_t after;
+    int32_t level_cap;     // 0: none; else a first batch that goes deeper ends the launch
     int32_t W;
     int32_t Wsel;          // lanes filled per batch (<= W)
     int32_t alpha_td;
@@ -726,6 +727,7 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
         bool bu = false;
         int64_t tslot = -1;
         int64_t mvis = 0, bytes = 0;
+        bool gave_up = false;
         int64_t my_scan = 0;   // words of in-arcs this thread scanned in pull steps (traffic count)
         for (;;) {
             // ------------------------------------ per-lane control (replicated)
@@ -768,6 +770,10 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
 #pragma unroll
             for (int j = 0; j < NW; j++) { act.w[j] = s_act[j]; any |= act.w[j] != 0; }
             if (!any) break;
+            if (a.level_cap && batches == 0 && D > a.level_cap) {
+                gave_up = true;
+                break;
+            }
             mvis += s_scal[0];
             // direction on the union frontier.  With several lanes a pull
             // rarely stops early (every missing lane must be found), so it
@@ -1195,7 +1201,7 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
         // one wave inserts, best first.  All-ties mode: every
         // result, in lane order, so the tie buffer sees what the top k
         // refuses.  (The expansion's LDS scratch is free here.)
-        if (blockIdx.x == 0) {
+        if (blockIdx.x == 0 && !gave_up) {
             int32_t* r_rank = &s_cpre[0][0];
             int32_t* r_id = r_rank + MAXW;
             int32_t* r_ord = &s_cbeg[0][0];
@@ -1357,7 +1363,7 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
             a.out_S[pos - nsel + tid] = s_SD[tid];
             a.out_r[pos - nsel + tid] = s_nD[tid];
         }
-        if (a.lb_mode) {
+        if (a.lb_mode && !gave_up) {
             // Lev tables per exact lane (thread per lane), then every vertex
             // takes the best level bound over the lanes that reached it
             // every level's counts and levels fit the tables (same value in
@@ -1468,6 +1474,10 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
             if (NW > 1)
                 for (int64_t q = gtid; q < n; q += nthreads) a.mark[q] = 0;
         }
+        if (gave_up) {
+            if (boss) stats[ST_CAPPED] = 1;
+            break;
+        }
         batches++;
         if (stop_now) break;
         if (a.until_x && ld_rlx(&ctr[C_XDONE]) != 0 && after-- == 0) break;
@@ -1519,6 +1529,7 @@ int tkc_launch_batch(const DevGraph& g, DevReach rc, OrderView ov, BoundsView bv
     a.no_cut = no_cut ? 1 : 0;
     a.until_x = max_batches < 0 ? 1 : 0;
     a.after = max_batches < 0 ? -1 - max_batches : 0;
+    a.level_cap = tune.level_cap;
     a.W = W;
     a.Wsel = (tune.lanes_cap > 0 && tune.lanes_cap < W) ? tune.lanes_cap : W;
     a.alpha_td = tune.batch_alpha > 0 ? tune.batch_alpha : 14;

@@ -22,6 +22,8 @@
 // (82 of 110 ms on a grid of 10^6: 7 10^9 vertices expanded, about one 128 B
 // line each, the rate at which random lines reach the chip being 55 G/s).
 // Measured against the batched engine: 20.9 -> 2.0 ms and 690 -> 111 ms.
+#include <algorithm>
+
 #include "dev_common.hpp"
 #include "engine.hpp"
 
@@ -44,6 +46,7 @@ struct RingArgs {
     int32_t words;
     int32_t lb_mode;
     int32_t limit;   // searches of this launch (0: no limit)
+    int32_t gate;    // positions handed out before the top k is full
 };
 
 // The bound of a vertex is num / (r - 1)^2; Lev(l) - deg(w) is compared with
@@ -57,9 +60,10 @@ struct RingArgs {
 __global__ void k_ring_begin(int32_t n, const int64_t* __restrict__ omega, const int32_t* __restrict__ deg,
                              const int64_t* __restrict__ num, const int64_t* __restrict__ den, int64_t* comb,
                              uint32_t* dec, const int32_t* __restrict__ rp, const int32_t* __restrict__ ci,
-                             int4* __restrict__ ell) {
+                             int4* __restrict__ ell, int32_t* cursor, int32_t from) {
     const int32_t v = blockIdx.x * blockDim.x + threadIdx.x;
     if (v >= n) return;
+    if (v == 0) *cursor = from;
     const int32_t b = rp[v], dv = rp[v + 1] - b;
     int4 r{-1, -1, -1, -1};
     if (dv > 0) r.x = ci[b];
@@ -263,24 +267,44 @@ __global__ void __launch_bounds__(T) k_ring(RingArgs a) {
         return t < 9e18 ? (int64_t)t : INT64_MAX - HEAVY_DEG;
     };
 
+    bool open = false;   // no waiting at the gate any more
     for (;;) {
         // ---- the next candidate: one position from the shared cursor; if it
         // is skipped, T positions at a time are judged and the cursor moves
         // past the skipped ones and the first that is not (compare-and-swap,
         // so no workgroup holds positions it is not working on; when another
         // was faster, the judged window serves for the next try)
-        if (wv == 0) offer(false);
-        if (tid == 0) {
-            int32_t p = 0, d = 4;   // 4: no more work for this workgroup
-            if (ld_rlx(a.w.stop) == 0 && (a.limit == 0 || ld_rlx(a.w.started) < a.limit)) {
-                p = fadd_rlx(a.w.cursor, 1);
-                if (p < count) {
+        if (wv == 0) {
+            // Until the top k is full nothing is cut or skipped, and where the
+            // first searches fill it and end the order, others that started
+            // meanwhile were in vain.  Positions from the gate on wait for those
+            // before it, which are at least k, all in work, and never wait
+            // themselves; a workgroup whose searches run deep does not wait (all
+            // take long there, and it costs 2 % to say so to the others).
+            // (Top 100 of trees of 3,000 and 150,000 vertices 1.80 -> 1.30 and 3.46
+            // -> 2.06 ms with 256 searches for 2,000 and 1,000; top 1,000 18.8 ->
+            // 7.1 and 16.8 -> 9.0.)
+            int32_t p = -2, d = 4;   // 4: no more work for this workgroup
+            for (;;) {
+                offer(false);
+                if (p == -2) {
+                    p = -1;
+                    if (lane == 0 && ld_rlx(a.w.stop) == 0 && (a.limit == 0 || ld_rlx(a.w.started) < a.limit))
+                        p = fadd_rlx(a.w.cursor, 1);
+                    p = __builtin_amdgcn_readfirstlane(p);
+                }
+                if (open || p < a.gate || p >= count) break;
+                open = __builtin_amdgcn_readfirstlane(ld_rlx(&a.tk.st->seq) >= 0 ? 1 : 0);
+                if (!open) __builtin_amdgcn_s_sleep(16);
+            }
+            if (lane == 0) {
+                if (p >= 0 && p < count) {
                     d = judge(p, read_x_poll(a.tk.st, a.tk.ring));
                     st_skip += d == 2;
                 }
+                s_pos = p;
+                s_dec = d;
             }
-            s_pos = p;
-            s_dec = d;
         }
         __syncthreads();
         int dec = s_dec;
@@ -411,6 +435,7 @@ __global__ void __launch_bounds__(T) k_ring(RingArgs a) {
         __syncthreads();   // the queue and the offsets are written
         const int32_t r = le;
         const int32_t maxD = D - 1;
+        open |= D > TKC_DEEP;
         if (tid == 0) {
             st_started++;
             const int64_t md = cut ? D : maxD;
@@ -550,10 +575,18 @@ int tkc_ring_blocks(const DevGraph& g) {
     return cus > 0 ? cus : 0;
 }
 
+// A complete search of one workgroup takes 4.7 ms on a tree of 10^6 vertices,
+// 64 of them batched half of that, and they often end the query: top 10 by
+// NBCut and NBBound 7.1 -> 4.2 and 9.1 -> 4.9 ms, of a random graph of 7 10^6
+// arcs, top 1, 17.2 -> 6.4; trees of 3 10^5 2.5 -> 2.0 and 3.0 -> 2.3, of 1.5 10^5
+// 1.7 -> 1.5, but a random graph of as many vertices and 4.5 10^5 arcs 3.3 -> 3.6.
+// On a deep graph a batch pays a grid barrier for every one of its levels.
+bool tkc_ring_seeds(const DevGraph& g, int32_t levels) { return levels <= TKC_DEEP && g.n > (1 << 18); }
+
 int tkc_launch_ring_begin(const DevGraph& g, const DevReach& rc, const BoundsView& bv, const RingWork& w,
-                          hipStream_t s) {
+                          int32_t from, hipStream_t s) {
     hipLaunchKernelGGL(k_ring_begin, dim3((g.n + 255) / 256), dim3(256), 0, s, g.n, rc.omega, (const int32_t*)g.deg,
-                       (const int64_t*)bv.num, (const int64_t*)bv.den, w.comb, w.dec, g.rp, g.ci, w.ell);
+                       (const int64_t*)bv.num, (const int64_t*)bv.den, w.comb, w.dec, g.rp, g.ci, w.ell, w.cursor, from);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 int tkc_launch_ring_end(const DevGraph& g, const DevReach& rc, const BoundsView& bv, const RingWork& w, hipStream_t s) {
@@ -563,7 +596,7 @@ int tkc_launch_ring_end(const DevGraph& g, const DevReach& rc, const BoundsView&
 }
 
 int tkc_launch_ring(const DevGraph& g, DevReach rc, OrderView ov, BoundsView bv, DevTopk tk, RingWork w,
-                    int64_t* stats, int lb_mode, int32_t limit, hipStream_t s) {
+                    int64_t* stats, int lb_mode, int32_t k, int32_t limit, hipStream_t s) {
     if (!w.queue || !w.levoff || !w.levtab || !w.comb || !w.dec || !w.ell || !w.cursor || !w.stop || !w.started || w.nblocks < 1 || w.lcap < 4)
         return -2;
     if (g.directed || g.nheavy > 0 || bv.harm) return -2;
@@ -575,6 +608,7 @@ int tkc_launch_ring(const DevGraph& g, DevReach rc, OrderView ov, BoundsView bv,
     a.words = (int32_t)(lds / 4) - 1;
     a.lb_mode = lb_mode;
     a.limit = limit;
+    a.gate = std::max(k, w.nblocks);
     const void* fn = (const void*)k_ring<RING_T>;
     if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) hipGetLastError();
     hipLaunchKernelGGL(k_ring<RING_T>, dim3(w.nblocks), dim3(RING_T), lds, s, a);
