@@ -1096,8 +1096,20 @@ int tkc_run_query(tkc_ctx* c, tkc_graph* g, int32_t k, int32_t variant, int32_t 
         }
     }
     // one search at a time on a small graph: one workgroup of the per-workgroup
-    // engine (its queue holds every vertex, so it defers nothing)
-    if (mode == TKC_PLAIN && !lb && max_searches <= 0 && ws.shape.qcap >= n && tkc_plain_small(dg)) {
+    // engine (its queue holds every vertex, so it defers nothing), after the k
+    // complete searches that fill the top k where the plain engine is faster
+    // at those
+    const bool plain_small = mode == TKC_PLAIN && !lb && max_searches <= 0 && ws.shape.qcap >= n && tkc_plain_small(dg);
+    if (plain_small && tkc_plain_first(dg)) {
+        EngineTimer tm(c, &ms_eng[0], &nl_eng[0]);
+        if (tkc_launch_plain(dg, rcv, ov, bv, tk, plain_view(ws), st_plain, nullptr, 0, 0, c->tune, s, &grid, k))
+            return tkc_fail(TKC_EDEVICE, "plain engine launch failed: %s", hipGetErrorString(hipGetLastError()));
+        if ((rc = tm.done(readback))) return rc;
+        rb_ready = true;
+        const int64_t* hs = pin_at<int64_t>(ws, st_plain);
+        resume = hs[ST_CAPPED] ? (int32_t)hs[ST_CURSOR] : n;
+    }
+    if (plain_small && resume < n) {
         EngineTimer tm(c, &ms_eng[2], &nl_eng[2]);
         int32_t* small = (int32_t*)ws.small;
         SwarmWork sw{};
@@ -1108,10 +1120,12 @@ int tkc_run_query(tkc_ctx* c, tkc_graph* g, int32_t k, int32_t variant, int32_t 
         sw.stop = small + 6;
         sw.nblocks = 1;
         sw.qcap = ws.shape.qcap;
-        if (tkc_launch_swarm(dg, rcv, ov, bv, tk, sw, st_swarm, 0, c->tune, s))
+        if (tkc_launch_swarm(dg, rcv, ov, bv, tk, sw, st_swarm, resume, c->tune, s))
             return tkc_fail(TKC_EDEVICE, "plain engine launch failed: %s", hipGetErrorString(hipGetLastError()));
         if ((rc = tm.done(readback))) return rc;
         rb_ready = true;
+    } else if (plain_small) {
+        // (its k searches ended the query)
     } else if (mode == TKC_PLAIN) {
         EngineTimer tm(c, &ms_eng[0], &nl_eng[0]);
         if (tkc_launch_plain(dg, rcv, ov, bv, tk, plain_view(ws), st_plain, nullptr, 0, lbl, c->tune, s, &grid,
@@ -1322,7 +1336,7 @@ int tkc_run_query(tkc_ctx* c, tkc_graph* g, int32_t k, int32_t variant, int32_t 
         *stats = st;
         return TKC_OK;
     };
-    if (hstat[0][ST_CAPPED]) {
+    if (max_searches > 0 && hstat[0][ST_CAPPED]) {
         // the plain engine met its search cap: counters only, no answer
         *n_out = 0;
         if ((rc = fill_stats())) return rc;

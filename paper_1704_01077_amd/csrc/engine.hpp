@@ -296,6 +296,7 @@ bool tkc_swarm_fits(const DevGraph& g);   // the visited set fits LDS
 // searches of so many arcs and levels are faster one per workgroup than batched
 bool tkc_swarm_pays(double arcs, int64_t levels);
 bool tkc_plain_small(const DevGraph& g);
+bool tkc_plain_first(const DevGraph& g);   // ... and the plain engine is faster at complete searches
 
 // k_ring.hip: one search per workgroup, visited set in LDS (undirected graphs
 // of low degree): cut ones (lb_mode 0), complete ones with level-based updates

@@ -311,6 +311,12 @@ bool tkc_swarm_fits(const DevGraph& g) {
 // and 8 10^4 43 -> 13; the line lies where the whole chip begins to pay for
 // complete searches (16,000 and 1.6 10^5, top 1: 1.16 -> 1.79).
 bool tkc_plain_small(const DevGraph& g) { return g.n + (int64_t)g.m <= (1 << 17); }
+// A complete search takes this engine about 0.9 ns an arc, the plain engine some 75
+// us whatever the graph's size here: those that fill the top k go to the faster.
+// Social networks of 2,000 vertices and 1.2 10^5 arcs, top 10, 1.32 -> 0.84 ms, web
+// graphs of 5,000 and 10^5 arcs 1.79 -> 1.37; of 1,000 and 5.5 10^4 0.82 here
+// against 0.97 by the plain engine.
+bool tkc_plain_first(const DevGraph& g) { return g.n + (int64_t)g.m > (1 << 16); }
 
 int tkc_swarm_max_blocks(int block) {
     (void)block;

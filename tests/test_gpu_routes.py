@@ -129,14 +129,29 @@ def test_hybrid_size_line(ctx):
         dg.free()
 
 
-def test_plain_size_line(ctx):
-    """Plain mode: one workgroup up to 2^17 vertices and arcs, the plain engine
-    beyond."""
-    for arcs in (110000, 140000):
+def test_plain_size_lines(ctx):
+    """Plain mode: one workgroup up to 2^16 vertices and arcs, up to 2^17 after
+    the k searches of the plain engine that fill the top k, the plain engine
+    beyond; the same searches everywhere."""
+    for arcs, engines in ((50000, {SWARM}), (110000, {0, SWARM}), (140000, {0})):
         g = skewed(9000, arcs, True)
+        assert (g.n + len(g.edges) > 1 << 16) == (arcs > 50000)
         dg = tkc.Graph.from_graphgen(ctx, g)
-        tkc.topk_closeness(dg, 5, "nbcut", "plain")
-        a = tkc.topk_closeness(dg, 5, "nbcut", "plain")
-        assert a[4]["main_kernel"] == (SWARM if arcs == 110000 else 0), a[4]
-        same(a, tkc.topk_closeness(dg, 5, "nbcut", "batched"))
+        for k in (1, 5, 60):
+            for variant in ("nbcut", "degcut"):
+                tkc.topk_closeness(dg, k, variant, "plain")
+                a = tkc.topk_closeness(dg, k, variant, "plain")
+                assert a[4]["main_kernel"] in engines, a[4]
+                same(a, tkc.topk_closeness(dg, k, variant, "batched"))
+                done, b, st = tkc.topk_closeness_budget(dg, k, variant, 10**6)
+                assert done
+                same(a, b)
+                for key in ("bfs_started", "bfs_exact", "bfs_cut", "skipped", "m_vis", "max_level", "mode_used"):
+                    assert a[4][key] == st[key], key
+            h = tkc.topk_harmonic(dg, k, "nbcut", "plain")
+            hb = tkc.topk_harmonic(dg, k, "nbcut", "batched")
+            assert np.array_equal(h[0], hb[0]) and np.array_equal(h[1], hb[1])
+            t = tkc.topk_closeness_ties(dg, k, "nbcut", "plain")
+            tb = tkc.topk_closeness_ties(dg, k, "nbcut", "batched")
+            same(t, tb)
         dg.free()
