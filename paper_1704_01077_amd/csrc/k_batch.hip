@@ -1363,7 +1363,11 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
             a.out_S[pos - nsel + tid] = s_SD[tid];
             a.out_r[pos - nsel + tid] = s_nD[tid];
         }
-        if (a.lb_mode && !gave_up) {
+        // (searches that were all cut raise no bound, the same in every workgroup:
+        // two barriers and a pass over all vertices less, 16.6 -> 13.4 ms by
+        // DegCut + LB on a social network of 30,000 vertices)
+        const bool raise = a.lb_mode && !gave_up && __syncthreads_or(tid < nsel && s_st[tid] == 2);
+        if (raise) {
             // Lev tables per exact lane (thread per lane), then every vertex
             // takes the best level bound over the lanes that reached it
             // every level's counts and levels fit the tables (same value in
@@ -1457,13 +1461,13 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
             }
         }
         // Clear the batch's words for the next batch.  Nothing reads or sets
-        // them after the last level's barrier except the level-based update (and
-        // a batch that ran no level has set none), so
-        // only that (and the until_x decision) needs a barrier first; the
-        // next batch's selection barrier orders the clear before its level 0
-        // (and the kernel's end before the host reads anything)
-        if (a.lb_mode || a.until_x) grid_barrier(a.bar, gridDim.x, &s_bar);
-        {
+        // them after the last level's barrier except the level-based update, so
+        // only that (and the until_x decision) needs a barrier first, and a batch
+        // that ran no level has nothing to clear; the next batch's selection
+        // barrier orders the clear before its level 0 (and the kernel's end before
+        // the host reads anything)
+        if (raise || a.until_x) grid_barrier(a.bar, gridDim.x, &s_bar);
+        if (D > 0) {
             int64_t tot = (int64_t)n * NW;
             for (int64_t q = gtid; q < tot; q += nthreads) {
                 vis[q] = 0;
