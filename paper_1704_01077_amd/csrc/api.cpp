@@ -19,6 +19,7 @@
 #include <algorithm>
 #include <chrono>
 #include <cmath>
+#include <memory>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -389,6 +390,84 @@ static bool is_transpose(int32_t n, int64_t m, const int32_t* rp, const int32_t*
     return true;
 }
 
+// A small graph's block is laid out on the host and copied at once: the kernels'
+// launches, copies and waits take 0.1 ms whatever the size.  The host takes some
+// 2 ns a vertex and 0.5 ns an arc (those of the reverse CSR included), so the
+// line weighs a vertex as four arcs.  Host arrays, kernels -> host: social network
+// of 500 vertices 0.112 -> 0.017 ms, of 14,000 (weight 219,000) 0.219 -> 0.122;
+// streets of 24,000 vertices (183,000) 0.134 -> 0.096, but of 40,000 (306,000)
+// 0.140 -> 0.172.  Device tensors, copied back first: 0.124 -> 0.061,
+// 0.208 -> 0.168, 0.127 -> 0.131.
+#define UPLOAD_HOST (1 << 18)
+static int upload_small(tkc_graph* g, const int32_t* rp, const int32_t* ci, const int32_t* rrp,
+                        const int32_t* rci, const int32_t* oid, size_t bytes, hipStream_t s) {
+    const std::unique_ptr<char[]> img(new char[bytes]);
+    // where a device array lies in the block
+    auto at = [&](const void* p) { return img.get() + ((const char*)p - (const char*)g->dbase); };
+    auto put = [&](void* p, const int32_t* v, size_t k) { if (k) memcpy(at(p), v, 4 * k); };
+    const int32_t n = g->n;
+    const size_t sn = (size_t)n, sm = (size_t)g->m;
+    put(g->rp, rp, sn + 1);
+    put(g->ci, ci, sm);
+    if (g->directed) {
+        put(g->rrp, rrp, sn + 1);
+        put(g->rci, rci, sm);
+    }
+    if (g->relabeled) {
+        put(g->d_oid, oid, sn);
+        put(g->d_nid, g->h_nid.data(), sn);
+    }
+    int32_t *deg = (int32_t*)at(g->deg), *heavy = (int32_t*)at(g->heavy), *hcb = (int32_t*)at(g->hcb);
+    for (int32_t v = 0; v < n; v++) deg[v] = rp[v + 1] - rp[v];
+    auto chunks = [&](const int32_t* r, int32_t* beg, int32_t* end, int32_t* vtx, bool list) {
+        int32_t k = 0;
+        if (list) hcb[0] = 0;
+        for (int32_t v = 0; v < n; v++) {
+            if (r[v + 1] - r[v] <= HEAVY_DEG) continue;
+            for (int32_t b = r[v]; b < r[v + 1]; b += CHUNK_ARCS, k++) {
+                beg[k] = b;
+                end[k] = std::min(b + CHUNK_ARCS, r[v + 1]);
+                vtx[k] = v;
+            }
+            if (list) {
+                heavy[g->nheavy++] = v;
+                hcb[g->nheavy] = k;
+            }
+        }
+        return k;
+    };
+    g->nchunks = chunks(rp, (int32_t*)at(g->ch_beg), (int32_t*)at(g->ch_end), (int32_t*)at(g->ch_vtx), true);
+    g->rnchunks = g->directed ? chunks(rrp, (int32_t*)at(g->rch_beg), (int32_t*)at(g->rch_end),
+                                       (int32_t*)at(g->rch_vtx), false)
+                              : g->nchunks;
+    // pull items: runs of at most 64 vertices and PULL_ARCS in-arcs, longer rows
+    // in pieces of their own
+    const int32_t* ir = g->directed ? rrp : rp;
+    int4* items = (int4*)at(g->items);
+    uint8_t* own = (uint8_t*)at(g->own);
+    for (int32_t v = 0; v < n;) {
+        const int32_t b = ir[v];
+        int32_t e = v;
+        while (e < n && e - v < 64 && ir[e + 1] - b <= PULL_ARCS) {
+            memset(own + ir[e], e - v, (size_t)(ir[e + 1] - ir[e]));
+            e++;
+        }
+        if (e > v) {
+            items[g->nitems++] = int4{v, b, e - v, ir[e] - b};
+            v = e;
+            continue;
+        }
+        memset(own + b, 0, (size_t)(ir[v + 1] - b));
+        for (int32_t q = b; q < ir[v + 1]; q += PULL_ARCS)
+            items[g->nitems++] = int4{v, q, 1, std::min(PULL_ARCS, ir[v + 1] - q) | PULL_SPLIT | (q == b ? PULL_FIRST : 0)};
+        v++;
+    }
+    if (hipMemcpyAsync(g->dbase, img.get(), bytes, hipMemcpyHostToDevice, s) != hipSuccess ||
+        hipStreamSynchronize(s) != hipSuccess)
+        return tkc_fail(TKC_EDEVICE, "graph copy failed: %s", hipGetErrorString(hipGetLastError()));
+    return TKC_OK;
+}
+
 extern "C" int tkc_graph_upload(tkc_ctx* c, int32_t n, int64_t m, const int32_t* row_ptr,
                                 const int32_t* col_idx, const int32_t* rrow_ptr, const int32_t* rcol_idx,
                                 uint32_t flags, tkc_graph** out) {
@@ -407,9 +486,11 @@ extern "C" int tkc_graph_upload(tkc_ctx* c, int32_t n, int64_t m, const int32_t*
         return tkc_fail(TKC_EINVAL, "reverse CSR given for an undirected graph");
     HIPCHK(hipSetDevice(c->device));
     // the arrays the device copies are taken from: the caller's, or host copies
-    // that TKC_VALIDATE reads and TKC_RELABEL renumbers
+    // that TKC_VALIDATE reads, TKC_RELABEL renumbers and a small graph's tables
+    // are built from
     const bool dev = (flags & TKC_DEVICE_PTRS) != 0;
-    bool host = (flags & (TKC_VALIDATE | TKC_RELABEL)) != 0;
+    const bool small = 4 * (int64_t)n + (directed ? 2 : 1) * m <= UPLOAD_HOST;
+    const bool host = (small && dev) || (flags & (TKC_VALIDATE | TKC_RELABEL)) != 0;
     std::vector<int32_t> hrp, hci, hrrp, hrci;
     if (host) {
         hrp.resize(n + 1);
@@ -423,8 +504,14 @@ extern "C" int tkc_graph_upload(tkc_ctx* c, int32_t n, int64_t m, const int32_t*
             HIPCHK(hipMemcpy(hrrp.data(), rrow_ptr, 4 * (size_t)(n + 1), k));
             if (m) HIPCHK(hipMemcpy(hrci.data(), rcol_idx, 4 * (size_t)m, k));
         }
-        int rc = check_csr_bounds(n, m, hrp.data(), hci.data(), "out-arcs");
-        if (!rc && directed) rc = check_csr_bounds(n, m, hrrp.data(), hrci.data(), "in-arcs");
+        row_ptr = hrp.data();
+        col_idx = hci.data();
+        rrow_ptr = hrrp.data();
+        rcol_idx = hrci.data();
+    }
+    if (host || small) {
+        int rc = check_csr_bounds(n, m, row_ptr, col_idx, "out-arcs");
+        if (!rc && directed) rc = check_csr_bounds(n, m, rrow_ptr, rcol_idx, "in-arcs");
         if (rc) return rc;
     }
     if (flags & TKC_VALIDATE) {
@@ -464,7 +551,13 @@ extern "C" int tkc_graph_upload(tkc_ctx* c, int32_t n, int64_t m, const int32_t*
             ci.swap(ci2);
         };
         permute(hrp, hci);
-        if (directed) permute(hrrp, hrci);
+        row_ptr = hrp.data();
+        col_idx = hci.data();
+        if (directed) {
+            permute(hrrp, hrci);
+            rrow_ptr = hrrp.data();
+            rcol_idx = hrci.data();
+        }
     }
     tkc_graph* g = new tkc_graph();
     g->ctx = c;
@@ -527,17 +620,23 @@ extern "C" int tkc_graph_upload(tkc_ctx* c, int32_t n, int64_t m, const int32_t*
     }
     hipStream_t s = c->stream;
     int rc = TKC_OK;
+    if (g->relabeled) g->h_nid = nid;
+    if (small) {
+        rc = upload_small(g, row_ptr, col_idx, rrow_ptr, rcol_idx, oid.data(), (size_t)(p - (char*)g->dbase), s);
+        if (rc) {
+            hipStreamSynchronize(s);
+            hipFree(g->dbase);
+            delete g;
+            return rc;
+        }
+        *out = g;
+        return TKC_OK;
+    }
     if (g->relabeled &&
         (hipMemcpyAsync(g->d_oid, oid.data(), 4 * sn, hipMemcpyHostToDevice, s) != hipSuccess ||
          hipMemcpyAsync(g->d_nid, nid.data(), 4 * sn, hipMemcpyHostToDevice, s) != hipSuccess))
         rc = tkc_fail(TKC_EDEVICE, "vertex map copy failed");
-    if (g->relabeled) g->h_nid = nid;
-    if (host) {
-        row_ptr = hrp.data();
-        col_idx = hci.data();
-        rrow_ptr = hrrp.data();
-        rcol_idx = hrci.data();
-    } else if (dev) {
+    if (dev && !host) {
         // the caller's arrays may be work of the default stream
         hipEvent_t ready = nullptr;
         hipError_t e = hipEventCreateWithFlags(&ready, hipEventDisableTiming);
