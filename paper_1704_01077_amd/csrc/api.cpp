@@ -1607,7 +1607,10 @@ int tkc_sums_impl(tkc_ctx* c, tkc_graph* g, const int32_t* sources, int32_t coun
                   tkc_stats* stout) {
     Workspace& ws = c->ws;
     hipStream_t s = c->stream;
-    int rc = tkc_ws_reserve(c, ws, tkc_shape_for(c->tune, g, std::max(1, ws.shape.kcap), ws.shape.lb));
+    // what earlier calls had room for is kept, but not in a server's slot, whose
+    // request was admitted with its own needs only
+    const bool keep = c->tune.slice_batches == 0;
+    int rc = tkc_ws_reserve(c, ws, tkc_shape_for(c->tune, g, keep ? std::max(1, ws.shape.kcap) : 1, keep && ws.shape.lb));
     if (rc) return rc;
     rc = tkc_step_reach(c, g, ws);
     if (rc) return rc;
