@@ -115,7 +115,8 @@ typedef struct {
     int32_t max_level;      /* deepest level reached                       */
     int32_t batch_width;    /* lanes per batch (W)                         */
     int32_t variant_used;
-    int32_t mode_used;
+    int32_t mode_used;      /* the mode asked for (AUTO resolved); which engine
+                               took most of the time says main_kernel      */
     int32_t nb_rounds;      /* walk-count levels the NB bound computed
                                (full rounds and tail rounds over the open
                                vertices; with cached bounds, the count of
@@ -129,7 +130,9 @@ typedef struct {
     double ms_kernel_main;  /* HIP-event time of the dominant traversal
                                kernel launches (see main_kernel)            */
     int32_t main_launches;  /* number of such launches                     */
-    int32_t main_kernel;    /* 0 plain, 1 batched, 2 per-workgroup         */
+    int32_t main_kernel;    /* 0 plain, 1 batched, 2 one search per workgroup
+                               (the per-workgroup or the ring engine; also
+                               in plain mode, on small graphs)             */
     int64_t bytes_main;     /* algorithmic bytes of those launches         */
 } tkc_stats;
 

@@ -122,7 +122,6 @@ int tkc_lds_limit();
 
 // k_prep.hip
 int tkc_launch_degrees(const DevGraph& g, hipStream_t s);
-// g.own from g.items (g.rrp gives the rows)
 // the checks every upload runs (memory safety of the kernels): row_ptr starts
 // at 0, never decreases and ends at m; every vertex id is in [0, n)
 #define CSR_BAD_FIRST 1
@@ -143,6 +142,7 @@ struct TabOut {
 int64_t tkc_tab_spans(int32_t n);
 int tkc_launch_tab_count(const DevGraph& g, int4* tab, hipStream_t s);
 int tkc_launch_tab_fill(const DevGraph& g, int4* tab, const TabOut& o, hipStream_t s);
+// g.own from g.items (g.rrp gives the rows)
 int tkc_launch_own(const DevGraph& g, uint8_t* own, hipStream_t s);
 // size holds n+2 int64; in_giant n bytes; sample_host is unused (the
 // dominant component is found on the device)

@@ -895,7 +895,6 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
                 {
                     int64_t per = (fl_len + nwaves - 1) / nwaves;
                     if (per > 64) per = 64;
-                    int32_t* c_pre = &s_cpre[tid >> 6][0];
                     int32_t* c_beg = &s_cbeg[tid >> 6][0];
                     uint64_t* c_f = &s_cmiss[tid >> 6][0];
                     for (int64_t base = gwave * per; base < fl_len; base += nwaves * per) {
@@ -931,7 +930,6 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
                         const uint64_t rows = __ballot(len > 0);
                         const int rk = __popcll(rows & below_mask());
                         if (len > 0) {
-                            c_pre[rk] = pre;
                             c_beg[rk] = eb - pre;
 #pragma unroll
                             for (int j = 0; j < NW; j++) c_f[j * LSTR + rk] = f.w[j];
@@ -983,7 +981,7 @@ __global__ void __launch_bounds__(BB) k_batch(BatchArgs a) {
                     if (done) my_dd += deg[u];
                 }
                 PHASE(1);
-                // push, heavy frontier vertices: one wave per quarter chunk
+                // push, heavy frontier vertices: one wave per PUSH_SUB-th of a chunk
                 // (a few hubs then still spread over many waves)
                 for (int64_t cq = gwave; cq < fc_len * PUSH_SUB; cq += nwaves) {
                     const int64_t c = cq / PUSH_SUB;

@@ -11,17 +11,19 @@
 // an atomic outside LDS.
 //
 // A finished search leaves its vertices in level order in its queue; the
-// workgroup then raises the bound of each of them (level by level, one wave
-// per level) with an atomic maximum, which is sound in any order because
+// workgroup then raises the bound of each of them (four queue positions a
+// thread, their levels found in the level offsets by binary search) with an
+// atomic maximum, which is sound in any order because
 // every value written is a valid lower bound.  Numerators share one
 // denominator per component ((r - 1)^2, exact for undirected graphs), so one
 // 64-bit maximum updates a bound.
 //
-// What bounds it: on small graphs the latency of that chain (1.6 us a level on
-// a grid of 2 10^4 vertices), on large ones cache lines from beyond the L2
-// (82 of 110 ms on a grid of 10^6: 7 10^9 vertices expanded, about one 128 B
-// line each, the rate at which random lines reach the chip being 55 G/s).
-// Measured against the batched engine: 20.9 -> 2.0 ms and 690 -> 111 ms.
+// What bounds it: on small graphs the latency of that chain (under 2 us a level
+// on a grid of 2 10^4 vertices), on large ones cache lines from beyond the L2
+// (on a grid of 10^6 3,576 searches expand 3.6 10^9 vertices in 60 ms, about one
+// 128 B line each, the rate at which random lines reach the chip being 55 G/s).
+// Measured against the batched engine, top 10 by NBBound: 27.4 -> 1.9 ms and
+// 460 -> 60 ms.
 #include <algorithm>
 
 #include "dev_common.hpp"
@@ -566,8 +568,7 @@ static size_t ring_lds_bytes(int32_t n) { return 4 * (((size_t)n + 31) / 32 + 1)
 // low diameter too: batched -> ring, top 10 by NBCut of sparse random graphs
 // of 3 10^4 vertices, 4 arcs a vertex 3.8 -> 1.3 ms, 7 arcs 11.7 -> 2.0 ms; of
 // 3 10^5, 35 -> 11.7 and 74 -> 26 ms; a small world of 3 10^4, 131 -> 5.6 ms.
-// (A random tree of 3 10^5 needs few searches and each has a wide front: 2.8
-// -> 3.2 ms.)
+// (Large shallow graphs fill the top k batched: tkc_ring_seeds.)
 int tkc_ring_blocks(const DevGraph& g) {
     if (g.directed || g.nheavy > 0 || g.m > 8 * (int64_t)g.n || g.n < 2) return 0;
     if (ring_lds_bytes(g.n) + RING_STATIC_LDS > (size_t)tkc_lds_limit()) return 0;

@@ -21,11 +21,12 @@
 // L2 at every level, the traversal of a social network of 3 10^4 vertices, top
 // 100, took 1.71 ms and of a web graph of 3 10^4, top 10, 0.37; now 0.72 and
 // 0.28).  A large search wants the whole chip, and a batch shares its reads
-// among 64 of them, hence the line at TKC_SWARM_SIZE; batched -> this engine:
-// social networks of 3 10^4 vertices and 1.8 10^5 edges 2.34 -> 0.72 ms, web
-// graphs of 3 10^4 and 1.8 10^5 0.89 -> 0.54 (top 100); but of 6 10^4 and
-// 4.8 10^5 1.28 -> 2.24, of 1.5 10^5 and 1.3 10^6 1.90 -> 4.27.  Between 2 and
-// 5 10^5 arcs it depends on the graph (0.95 -> 0.43 and 1.02 -> 1.72).
+// among 64 of them.  Up to TKC_SWARM_SIZE this engine follows the batched seeds
+// at once; batched -> this engine, social networks of 3 10^4 vertices and 1.8
+// 10^5 edges 2.34 -> 0.72 ms, web graphs of 3 10^4 and 1.8 10^5 0.89 -> 0.54
+// (top 100).  Beyond, it depends on the graph (web graphs of 6 10^4 and 4.8 10^5
+// 1.28 -> 2.24, of 1.5 10^5 and 1.3 10^6 1.90 -> 4.27, others the other way), and
+// a few batches behind the seeds show which (tkc_swarm_pays).
 //
 // stop word bits: 1 = the stop rule fired, 2 = the engine closed itself.
 #include "dev_common.hpp"

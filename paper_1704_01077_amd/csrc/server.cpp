@@ -10,7 +10,8 @@
 //   - Per-graph preprocessing (reachability, initial bounds, order) is
 //     computed by the first request on a graph and reused by later ones.
 //   - Cooperative (grid-barrier) kernels of different slots never overlap:
-//     they take a process-wide lock, while ordinary kernels run freely.
+//     they take a process-wide lock, and so do the other engines' launches,
+//     which fill the chip as well.  Preprocessing and copies run freely.
 //   - Packing (tkc_server_enable_packing): the small graphs are grouped into
 //     packs (disjoint unions, pack.cpp).  A slot that takes a request on a
 //     packed graph also takes the queued requests on the pack's other
