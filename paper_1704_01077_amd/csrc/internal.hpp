@@ -116,7 +116,7 @@ struct tkc_graph {
     std::vector<int32_t> h_nid;
     int32_t server_refs = 0;
     std::atomic<int32_t> auto_variant{0};   // read by server workers without the graph lock
-    std::atomic<int32_t> levels{0};         // of AUTO's full search (0: not run yet)
+    std::atomic<int32_t> levels{0};         // of AUTO's full search or a query's seeds (0: not known yet)
     // reachability bounds of a directed graph, computed once per graph:
     // alpha, omega (n int64 each) and topological SCC ids (n int32)
     void* reach_base = nullptr;
