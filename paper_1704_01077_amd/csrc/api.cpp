@@ -394,11 +394,13 @@ static bool is_transpose(int32_t n, int64_t m, const int32_t* rp, const int32_t*
 // launches, copies and waits take 0.1 ms whatever the size.  The host takes some
 // 2 ns a vertex and 0.5 ns an arc (those of the reverse CSR included), so the
 // line weighs a vertex as four arcs.  Host arrays, kernels -> host: social network
-// of 500 vertices 0.112 -> 0.017 ms, of 14,000 (weight 219,000) 0.219 -> 0.122;
-// streets of 24,000 vertices (183,000) 0.134 -> 0.096, but of 40,000 (306,000)
-// 0.140 -> 0.172.  Device tensors, copied back first: 0.124 -> 0.061,
-// 0.208 -> 0.168, 0.127 -> 0.131.
+// of 500 vertices 0.112 -> 0.017 ms, of 14,000 (weight 219,000) 0.175 -> 0.121;
+// streets of 24,000 vertices (183,000) 0.130 -> 0.095, but of 40,000 (306,000)
+// 0.138 -> 0.172.  Device tensors are copied back first: 500 vertices 0.124 ->
+// 0.061, social network of 9,500 (148,000) 0.150 -> 0.109, but 14,000 0.157 ->
+// 0.167 and the streets of 24,000 0.119 -> 0.131.
 #define UPLOAD_HOST (1 << 18)
+#define UPLOAD_HOST_DEV (5 << 15)
 static int upload_small(tkc_graph* g, const int32_t* rp, const int32_t* ci, const int32_t* rrp,
                         const int32_t* rci, const int32_t* oid, size_t bytes, hipStream_t s) {
     const std::unique_ptr<char[]> img(new char[bytes]);
@@ -489,7 +491,7 @@ extern "C" int tkc_graph_upload(tkc_ctx* c, int32_t n, int64_t m, const int32_t*
     // that TKC_VALIDATE reads, TKC_RELABEL renumbers and a small graph's tables
     // are built from
     const bool dev = (flags & TKC_DEVICE_PTRS) != 0;
-    const bool small = 4 * (int64_t)n + (directed ? 2 : 1) * m <= UPLOAD_HOST;
+    const bool small = 4 * (int64_t)n + (directed ? 2 : 1) * m <= (dev ? UPLOAD_HOST_DEV : UPLOAD_HOST);
     const bool host = (small && dev) || (flags & (TKC_VALIDATE | TKC_RELABEL)) != 0;
     std::vector<int32_t> hrp, hci, hrrp, hrci;
     if (host) {
